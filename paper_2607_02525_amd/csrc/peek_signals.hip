@@ -1678,7 +1678,7 @@ __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const ui
 // up the interval tree adds the offsets of the ancestors, and every request
 // lands at its node's start plus its own offset.
 struct OffElem {
-  int32_t node;    // the node the piece belongs to (its first separator); INT32_MAX for padding
+  int32_t node;    // the node the piece belongs to (its first separator); INT32_MAX for padding (k2: its place)
   int32_t k1;      // 0 for a request that ends at the node, else n + 1 - the child's size
   int32_t k2;      // the request, or the child's earliest request
   int32_t owner;   // the child's node id (> 0), or -(position + 1) for a request
@@ -1717,7 +1717,8 @@ __device__ __forceinline__ int32_t off_node_of(const OffArgs& a, int32_t i) {
 struct OffSource {
   OffArgs a;
   __device__ __forceinline__ OffElem operator()(size_t j) const {
-    const OffElem pad{INT32_MAX, INT32_MAX, INT32_MAX, 0};
+    // sorts last, and differs from every other one
+    const OffElem pad{INT32_MAX, INT32_MAX, (int32_t)min(j, (size_t)INT32_MAX), 0};
     const int32_t n = a.n;
     if (j < (size_t)n) {
       const int32_t i = (int32_t)j;
@@ -2013,7 +2014,7 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
     const uint32_t* keys = ka;
     if (n > 0) {
       hipLaunchKernelGGL(k_demand_keys, dim3(blocks_for(np)), dim3(256), 0, st, last_node, n, ka, np);
-      keys = msort::sort(ka, kb, np, U32Less{}, st);
+      keys = msort::merge_sort(msort::FromArray<uint32_t>{ka}, ka, kb, np, U32Less{}, st);
     }
     launch_demand_from_sorted(*t, PlainKeys{keys}, n, P, demand, st);
   }
@@ -2076,7 +2077,11 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
   AncElem* anc_a = (AncElem*)(w + L.anc_a);
   AncElem* anc_b = (AncElem*)(w + L.anc_b);
   hipLaunchKernelGGL(k_first_compare, dim3(blocks_for(n, 4)), dim3(256), 0, st, ain, T, n, anc_a);
-  const AncElem* sorted = msort::sort_from(AncSrc{anc_a, n}, anc_a, anc_b, np, AncLess{}, st);
+  // the range-minimum tables are written after the sorts: their room serves as scratch
+  void* sort_ws = w + L.ib1;
+  const size_t sort_ws_bytes = L.st1 - L.ib1;
+  const AncElem* sorted = msort::sort_distinct(AncSrc{anc_a, n}, anc_a, anc_b, n, np, AncElem{~0ull, ~0ull, ~0ull},
+                                               AncLess{}, sort_ws, sort_ws_bytes, st);
   // The order is sorted by last node first, so demand reads it directly:
   // the segment kernel marks where each last node's run starts, the second
   // round's compare carries the fill of the prefix P over all nodes, the
@@ -2136,8 +2141,11 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
       const OffArgs oa{n, lcp, el, ix, ib2, st2, L.nb2, npar[0], start[0], rnode, roff};
       hipLaunchKernelGGL(k_off_make, dim3(blocks_for((int64_t)L.onp)), dim3(256), 0, st, OffSource{oa},
                          (OffElem*)(w + L.oel_a), (int64_t)L.onp);
-      const OffElem* sorted = msort::sort((OffElem*)(w + L.oel_a), (OffElem*)(w + L.oel_b), L.onp, OffLess{}, st);
       const int32_t m2 = 2 * n;
+      OffElem* oel = (OffElem*)(w + L.oel_a);
+      const OffElem* sorted =
+          msort::sort_distinct(msort::FromArray<OffElem>{oel}, oel, (OffElem*)(w + L.oel_b), m2, L.onp,
+                               OffElem{INT32_MAX, INT32_MAX, INT32_MAX, 0}, OffLess{}, sort_ws, sort_ws_bytes, st);
       int64_t* olocal = (int64_t*)(w + L.olocal);
       int64_t* opart = (int64_t*)(w + L.opart);
       int64_t* obase = (int64_t*)(w + L.obase);

@@ -1,7 +1,300 @@
-// Stable merge sort for the queue-signal kernels (device templates).
+// Sorting for the queue-signal kernels (device templates), by size:
 //
-// Tile pass: 256 threads x ITEMS items per workgroup; each thread orders its
-// items in registers, then runs are merged in LDS with merge-path
+//  - up to kRankMax elements, one launch: an element's place is the number of
+//    elements below it, counted by a wavefront against all of them
+//    (k_rank_sort);
+//  - up to kSampleMax elements, three launches: kSamples sampled elements are
+//    ranked the same way and every few of them becomes a splitter
+//    (k_sample_rank); every element finds its bucket among the splitters
+//    (k_bucket_scatter); one workgroup orders each bucket in LDS and writes
+//    it at its place (k_bucket_sort);
+//  - beyond, and where keys can be equal: a stable merge sort.
+//
+// The first two need distinct keys (the callers' keys carry the request).
+// They took the place of the merge sort there because each of its passes is a
+// launch whose time is a few dependent searches, whatever the size: see the
+// figures at the kernels.
+#pragma once
+
+#include <hip/hip_runtime.h>
+
+#include <algorithm>
+#include <cstddef>
+#include <cstdint>
+
+namespace peek {
+namespace msort {
+
+// Element source: a plain array, or a functor that builds element i on the
+// fly (saves a pass that would only write the input).
+template <typename T>
+struct FromArray {
+  const T* p;
+  __device__ __forceinline__ T operator()(size_t i) const { return p[i]; }
+};
+
+// ---------------------------------------------------------------- by rank
+// Bound by the comparisons, n^2 / 64 of them per launch. 1024 elements take
+// 3.1 us (the merge sort: 13.5), 2048 6.6 us (18.5), 4096 12.2 us (25); the
+// bucket sort takes 12.4 us there, so the line lies at 4096. Above 2048
+// elements a wavefront counts for two of them at once, which halves the LDS
+// reads; four at once left one wavefront per SIMD and took 15.9 us at 4096.
+constexpr int kRankMax = 4096;
+constexpr int kRankThreads = 512;
+constexpr int kRankTile = 1024;   // elements staged in LDS at a time
+constexpr int kRankLoads = kRankTile / kRankThreads;
+
+template <int I, typename T, typename Less, typename Src>
+__global__ __launch_bounds__(kRankThreads) void k_rank_sort(Src src, T* __restrict__ dst, int32_t n, Less less) {
+  __shared__ T s[kRankTile];
+  const int t = threadIdx.x, lane = t & 63;
+  const int32_t i0 = __builtin_amdgcn_readfirstlane(((int32_t)blockIdx.x * (kRankThreads / 64) + t / 64) * I);
+  T next[kRankLoads], own[I];
+  int32_t rank[I];
+  // indices clamped to the last element; what lies past it is not counted
+#pragma unroll
+  for (int q = 0; q < kRankLoads; ++q) next[q] = src((size_t)min(q * kRankThreads + t, n - 1));
+#pragma unroll
+  for (int q = 0; q < I; ++q) {
+    own[q] = src((size_t)min(i0 + q, n - 1));
+    rank[q] = 0;
+  }
+  for (int32_t base = 0; base < n; base += kRankTile) {
+    __syncthreads();   // the tile before is done with
+#pragma unroll
+    for (int q = 0; q < kRankLoads; ++q) s[q * kRankThreads + t] = next[q];
+    __syncthreads();
+    if (base + kRankTile < n) {   // the next tile travels while this one is counted
+#pragma unroll
+      for (int q = 0; q < kRankLoads; ++q)
+        next[q] = src((size_t)min(base + kRankTile + q * kRankThreads + t, n - 1));
+    }
+    const int32_t m = min(kRankTile, n - base);
+    for (int32_t j = 0; j < m; j += 64) {
+      const T e = s[j + lane];
+      const bool in = j + lane < m;
+#pragma unroll
+      for (int q = 0; q < I; ++q) rank[q] += __popcll(__ballot(in & less(e, own[q])));
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < I; ++q)
+    if (lane == q && i0 + q < n) dst[rank[q]] = own[q];
+}
+
+// ---------------------------------------------------------------- by buckets
+// Samples are jittered (one hashed place in each of S equal stretches of the
+// input), so a bucket's size depends on the hash and not on how the input is
+// laid out. With 2 samples to a bucket (65,536 elements, 512 buckets) one over
+// 16 times the mean has odds of about 1e-12, with 4 (131,072 elements) one
+// over 8 times of 1e-10. A bucket that is larger all the same (an input made
+// for it) is ordered in global memory.
+// All three launches are bound by chains of dependent accesses and by the
+// comparisons in LDS; 24-byte keys, us (merge sort / sample + scatter +
+// bucket sort): 4500 elements 31 / 12.4, 16,384 36 / 14.5, 65,536 52 / 17 to
+// 24 (random keys; a queue's 19).
+// 2048 samples instead of 1024 cost 2 us more up to 65,536 elements, and
+// above they save as much in smaller buckets.
+constexpr int64_t kSampleMax = int64_t(1) << 17;
+constexpr int32_t kFewSamples = 1024, kManySamples = 2048;
+constexpr int32_t kFewSamplesMax = 65536;   // elements
+constexpr int kMaxBuckets = 512;
+constexpr int kBucketMax = 2048;      // elements a bucket's workgroup orders in LDS
+constexpr int kCountPad = 16;         // a bucket's counter has a 64-byte line of its own
+constexpr int kSampleThreads = 512;
+constexpr int kScatterThreads = 512;
+constexpr int kBucketThreads = 512;
+
+struct Buckets {
+  int32_t n;
+  int32_t nb;       // buckets, a power of two
+  int32_t cap;      // slots of a bucket
+  int32_t* count;   // [nb * kCountPad]
+  int32_t* slots;   // [nb * cap] elements of each bucket, by input index
+};
+
+__device__ __forceinline__ uint32_t sample_hash(uint32_t x) {
+  x *= 0x9E3779B1u;
+  x ^= x >> 15;
+  x *= 0x85EBCA77u;
+  x ^= x >> 13;
+  return x;
+}
+
+// Workgroup g ranks S / gridDim.x samples, one per wavefront, against all.
+template <int S, typename T, typename Less, typename Src>
+__global__ __launch_bounds__(kSampleThreads) void k_sample_rank(Src src, T* __restrict__ split, Buckets B, Less less) {
+  constexpr int kLoads = S / kSampleThreads;
+  __shared__ T s[S];
+  const int t = threadIdx.x, lane = t & 63;
+  const int32_t gid = (int32_t)blockIdx.x * kSampleThreads + t;
+  if (gid < B.nb * kCountPad) B.count[gid] = 0;
+  T v[kLoads];
+#pragma unroll
+  for (int q = 0; q < kLoads; ++q) {
+    const uint32_t j = (uint32_t)(q * kSampleThreads + t);
+    const uint32_t lo = (uint32_t)(((uint64_t)j * (uint32_t)B.n) / S);
+    const uint32_t hi = (uint32_t)(((uint64_t)(j + 1) * (uint32_t)B.n) / S);
+    v[q] = src((size_t)(lo + sample_hash(j) % (hi - lo)));   // n > S: no stretch is empty
+  }
+#pragma unroll
+  for (int q = 0; q < kLoads; ++q) s[q * kSampleThreads + t] = v[q];
+  __syncthreads();
+  const int per = S / B.nb;
+  const T own = s[(int)blockIdx.x * (kSampleThreads / 64) + t / 64];
+  int32_t rank = 0;
+#pragma unroll 4
+  for (int j = 0; j < S; j += 64) rank += __popcll(__ballot(less(s[j + lane], own)));
+  if (lane == 0 && rank != 0 && rank % per == 0) split[rank / per - 1] = own;
+}
+
+// An element's bucket: the number of splitters at or below it.
+template <typename T, typename Less>
+__device__ __forceinline__ int bucket_of(const T* split, int nb, const T& v, Less less) {
+  int b = 0;
+  for (int w = nb >> 1; w > 0; w >>= 1) b += less(v, split[b + w - 1]) ? 0 : w;
+  return b;
+}
+
+template <typename T, typename Less, typename Src>
+__global__ __launch_bounds__(kScatterThreads) void k_bucket_scatter(Src src, const T* __restrict__ split, Buckets B,
+                                                                    Less less) {
+  __shared__ T sp[kMaxBuckets];
+  __shared__ int32_t here[kMaxBuckets];   // elements of this workgroup, then where they start
+  const int t = threadIdx.x;
+  const int32_t i = (int32_t)blockIdx.x * kScatterThreads + t;
+  const T v = src((size_t)min(i, B.n - 1));
+  static_assert(kMaxBuckets <= kScatterThreads, "one bucket per thread");
+  if (t < B.nb) here[t] = 0;
+  if (t < B.nb - 1) sp[t] = split[t];
+  __syncthreads();
+  const int b = bucket_of(sp, B.nb, v, less);
+  int32_t at = 0;
+  if (i < B.n) at = atomicAdd(&here[b], 1);
+  __syncthreads();
+  if (t < B.nb && here[t] > 0) here[t] = atomicAdd(&B.count[t * kCountPad], here[t]);
+  __syncthreads();
+  if (i < B.n) {
+    at += here[b];
+    if (at < B.cap) B.slots[(size_t)b * B.cap + at] = i;
+  }
+}
+
+template <typename T>
+__device__ __forceinline__ T shfl_xor_elem(const T& v, int mask) {
+  static_assert(sizeof(T) % 4 == 0, "whole words");
+  union {
+    T e;
+    int32_t w[sizeof(T) / 4];
+  } u;
+  u.e = v;
+#pragma unroll
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) u.w[k] = __shfl_xor(u.w[k], mask);
+  return u.e;
+}
+
+// Bitonic sort of 64 elements held one per lane, ascending.
+template <typename T, typename Less>
+__device__ __forceinline__ void wave_sort(T& v, int lane, Less less) {
+#pragma unroll
+  for (int k = 2; k <= 64; k <<= 1) {
+#pragma unroll
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      const T o = shfl_xor_elem(v, j);
+      const bool low = ((lane & j) == 0) == ((lane & k) == 0);   // this lane keeps the smaller one
+      if (low == less(o, v)) v = o;
+    }
+  }
+}
+
+// Workgroup b orders bucket b. Runs of 64 are sorted in registers, one per
+// wavefront, and put into LDS; an element's place in the bucket is its place
+// in its own run plus, for every other run, the elements below it (a search
+// of 7 steps, those of different runs independent of each other).
+template <typename T, typename Less, typename Src>
+__global__ __launch_bounds__(kBucketThreads) void k_bucket_sort(Src src, T* __restrict__ dst,
+                                                                const T* __restrict__ split, Buckets B, T pad,
+                                                                Less less) {
+  __shared__ T s[kBucketMax];
+  __shared__ int32_t wsum[kBucketThreads / 64];
+  __shared__ int32_t found;
+  const int t = threadIdx.x, lane = t & 63, wave = t / 64;
+  const int b = blockIdx.x;
+  static_assert(kMaxBuckets <= kBucketThreads, "one bucket per thread");
+  const int32_t mine = B.count[min(t, B.nb - 1) * kCountPad];
+  const int32_t c = B.count[b * kCountPad];
+  int32_t sum = t < b ? mine : 0;
+  for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+  if (lane == 0) wsum[wave] = sum;
+  if (t == 0) found = 0;
+  const int32_t* __restrict__ slots = B.slots + (size_t)b * B.cap;
+  const bool fits = c <= min(B.cap, kBucketMax);
+  constexpr int kWaves = kBucketThreads / 64;
+  if (fits) {
+    for (int r = wave; r * 64 < c; r += kWaves) {
+      const int p = r * 64 + lane;
+      T v = src((size_t)slots[min(p, c - 1)]);
+      if (p >= c) v = pad;
+      wave_sort(v, lane, less);
+      s[p] = v;
+    }
+  }
+  __syncthreads();
+  int32_t base = 0;
+#pragma unroll
+  for (int w = 0; w < kWaves; ++w) base += wsum[w];
+  if (fits) {
+    const int runs = (c + 63) / 64;
+    for (int r = wave; r < runs; r += kWaves) {
+      const int p = r * 64 + lane;
+      const T v = s[p];
+      int32_t rank = lane;
+#pragma unroll 4
+      for (int o = 0; o < runs; ++o) {
+        if (o == r) continue;
+        // elements of run o below v; its padding is never below
+        int k = 0;
+#pragma unroll
+        for (int w = 32; w > 0; w >>= 1) k += less(s[o * 64 + k + w - 1], v) ? w : 0;
+        k += less(s[o * 64 + k], v) ? 1 : 0;
+        rank += k;
+      }
+      if (p < c) dst[base + rank] = v;
+    }
+    return;
+  }
+  // Too large for LDS or for its slots: its elements are found again among
+  // all of them and ordered in place (a bitonic network whose comparisons all
+  // ascend, so the places past the end need not exist).
+  T* d = dst + base;
+  const T lo = split[max(b - 1, 0)], hi = split[min(b, B.nb - 2)];
+  for (int32_t i = t; i < B.n; i += kBucketThreads) {
+    const T v = src((size_t)i);
+    const bool in = (b == 0 || !less(v, lo)) && (b == B.nb - 1 || less(v, hi));
+    if (in) d[atomicAdd(&found, 1)] = v;
+  }
+  __syncthreads();
+  for (int64_t k = 2; k < 2 * (int64_t)c; k <<= 1) {
+    for (int64_t j = k >> 1; j > 0; j >>= 1) {
+      const int64_t flip = j == k >> 1 ? k - 1 : j;
+      for (int64_t x = t; x < c; x += kBucketThreads) {
+        const int64_t y = x ^ flip;
+        if (y > x && y < c) {
+          const T ex = d[x], ey = d[y];
+          if (less(ey, ex)) {
+            d[x] = ey;
+            d[y] = ex;
+          }
+        }
+      }
+      __syncthreads();
+    }
+  }
+}
+
+// ---------------------------------------------------------------- merge sort
+// Stable. Tile pass: 256 threads x ITEMS items per workgroup; each thread
+// orders its items in registers, then runs are merged in LDS with merge-path
 // partitioning (every thread produces its outputs after a binary search on
 // its diagonal).
 // Global passes: each workgroup emits a tile's worth of outputs of a pair of
@@ -10,21 +303,7 @@
 // Tile size: 512 elements (2 items) keeps a 64K-element sort spread over
 // 128 workgroups; from 512K elements up, 1024-element tiles (4 items) save a
 // pass and amortize each workgroup's dependent diagonal searches over more
-// outputs. Measured on the 64K-element anchor sort: 256-element tiles (128
-// threads) take 8.0 us for the tile pass and 8 x 5.8 us for the merge
-// passes, 512-element tiles 10.4 + 7 x 5.9 us; more items per thread (4
-// or 8) are slower (12.2 + 7 x 6.9 us and 20.6 + 6 x 9.1 us).
-// Ties keep input order (stable), so results are deterministic.
-#pragma once
-
-#include <hip/hip_runtime.h>
-
-#include <cstddef>
-#include <cstdint>
-
-namespace peek {
-namespace msort {
-
+// outputs.
 constexpr int kThreads = 256;
 constexpr int kItems = 2;
 constexpr int kTile = kThreads * kItems;            // 512: the smallest tile, so np is a multiple of it
@@ -76,32 +355,11 @@ __device__ __forceinline__ void merge_seq_flat(const T* A, int la, const T* B, i
   }
 }
 
-// Element source of the tile pass: a plain array, or a functor that builds
-// element i on the fly (saves a pass that would only write the input).
-template <typename T>
-struct FromArray {
-  const T* p;
-  __device__ __forceinline__ T operator()(size_t i) const { return p[i]; }
-};
-
-// A gated sort (gate != nullptr and *gate == 0) is skipped: the tile pass
-// copies its input to its output and every merge pass returns at once. The
-// buffer the host expects then holds the unsorted input either way: after
-// an even number of merge passes it is the tile pass's copy, after an odd
-// number it is the untouched input.
-template <int TILE, typename T, typename Src>
-__device__ __forceinline__ bool gated_copy(const int32_t* gate, const Src& src, T* __restrict__ dst, size_t base) {
-  if (gate == nullptr || *gate != 0) return false;
-  for (int q = threadIdx.x; q < TILE; q += kThreads) dst[base + q] = src(base + q);
-  return true;
-}
-
 template <int I, typename T, typename Less, typename Src>
-__global__ __launch_bounds__(kThreads) void k_tile_sort(Src src, T* __restrict__ dst, Less less, const int32_t* gate) {
+__global__ __launch_bounds__(kThreads) void k_tile_sort(Src src, T* __restrict__ dst, Less less) {
   __shared__ T s[(kThreads * I)];
   const int t = threadIdx.x;
   const size_t base = (size_t)blockIdx.x * (kThreads * I);
-  if (gated_copy<kThreads * I>(gate, src, dst, base)) return;
   T v[I];
 #pragma unroll
   for (int q = 0; q < I; ++q) v[q] = src(base + t * I + q);
@@ -167,12 +425,11 @@ __device__ __forceinline__ int wave_merge_path(const T* A, int64_t la, const T* 
 // Merge pass: runs of width w (power of two, >= (kThreads * I)) in src, pairs merged into dst.
 template <int I, typename T, typename Less>
 __global__ __launch_bounds__(kThreads) void k_merge_pass(const T* __restrict__ src, T* __restrict__ dst, int64_t w,
-                                                         Less less, const int32_t* gate) {
+                                                         Less less) {
   __shared__ T s[(kThreads * I)];
   __shared__ int64_t split[2];
   const int t = threadIdx.x;
   const int64_t out0 = (int64_t)blockIdx.x * (kThreads * I);
-  if (gate != nullptr && *gate == 0) return;
   const int64_t pair = out0 & ~(2 * w - 1);
   const T* A = src + pair;
   const T* B = A + w;
@@ -200,18 +457,16 @@ __global__ __launch_bounds__(kThreads) void k_merge_pass(const T* __restrict__ s
 
 // Sorts np elements (np a power of two, >= kThreads * I) taken from `src`
 // (element i = src(i)), using a and b as buffers; returns the one that holds
-// the result. With a gate, the sort happens only if *gate != 0 when the
-// passes run (otherwise the data is copied).
+// the result.
 template <int I, typename T, typename Less, typename Src>
-T* sort_from_tiles(Src src, T* a, T* b, size_t np, Less less, hipStream_t st, const int32_t* gate) {
+T* sort_from_tiles(Src src, T* a, T* b, size_t np, Less less, hipStream_t st) {
   constexpr int tile = kThreads * I;
   const unsigned tiles = (unsigned)(np / tile);
-  hipLaunchKernelGGL((k_tile_sort<I, T, Less, Src>), dim3(tiles), dim3(kThreads), 0, st, src, b, less, gate);
+  hipLaunchKernelGGL((k_tile_sort<I, T, Less, Src>), dim3(tiles), dim3(kThreads), 0, st, src, b, less);
   T* cur = b;
   T* oth = a;
   for (size_t w = tile; w < np; w <<= 1) {
-    hipLaunchKernelGGL((k_merge_pass<I, T, Less>), dim3(tiles), dim3(kThreads), 0, st, cur, oth, (int64_t)w, less,
-                       gate);
+    hipLaunchKernelGGL((k_merge_pass<I, T, Less>), dim3(tiles), dim3(kThreads), 0, st, cur, oth, (int64_t)w, less);
     T* x = cur;
     cur = oth;
     oth = x;
@@ -221,15 +476,54 @@ T* sort_from_tiles(Src src, T* a, T* b, size_t np, Less less, hipStream_t st, co
 
 // The tile size by sort size (np a power of two, >= kTile).
 template <typename T, typename Less, typename Src>
-T* sort_from(Src src, T* a, T* b, size_t np, Less less, hipStream_t st, const int32_t* gate = nullptr) {
-  if (np >= kBigSort) return sort_from_tiles<kBigItems>(src, a, b, np, less, st, gate);
-  return sort_from_tiles<kItems>(src, a, b, np, less, st, gate);
+T* merge_sort(Src src, T* a, T* b, size_t np, Less less, hipStream_t st) {
+  if (np >= kBigSort) return sort_from_tiles<kBigItems>(src, a, b, np, less, st);
+  return sort_from_tiles<kItems>(src, a, b, np, less, st);
 }
 
-// Sorts np elements from a into a or b (see sort_from).
-template <typename T, typename Less>
-T* sort(T* a, T* b, size_t np, Less less, hipStream_t st, const int32_t* gate = nullptr) {
-  return sort_from(FromArray<T>{a}, a, b, np, less, st, gate);
+// Sorts elements 0 .. n-1 of `src`, whose keys are distinct; `np` is n rounded
+// up to a power of two (at least kTile), the room of a and b, and `src` gives
+// `pad`, which no key exceeds, from n on. Returns a or b, whichever holds the
+// result. `src` may read a. `scratch` (any contents) is 36 bytes or more an
+// element: room for buckets of 7 times their mean and more.
+template <typename T, typename Less, typename Src>
+T* sort_distinct(Src src, T* a, T* b, int32_t n, size_t np, T pad, Less less, void* scratch, size_t scratch_bytes,
+                 hipStream_t st) {
+  if (n <= kRankMax) {
+    constexpr int waves = kRankThreads / 64;
+    auto grid = [&](int per) { return dim3((unsigned)((n + waves * per - 1) / (waves * per))); };
+    // elements per wavefront: 1024 wavefronts (one per SIMD) are enough
+    if (n <= 1024)
+      hipLaunchKernelGGL((k_rank_sort<1, T, Less, Src>), grid(1), dim3(kRankThreads), 0, st, src, b, n, less);
+    else if (n <= 2048)
+      hipLaunchKernelGGL((k_rank_sort<2, T, Less, Src>), grid(2), dim3(kRankThreads), 0, st, src, b, n, less);
+    else
+      hipLaunchKernelGGL((k_rank_sort<2, T, Less, Src>), grid(2), dim3(kRankThreads), 0, st, src, b, n, less);
+    return b;
+  }
+  if (n > kSampleMax) return merge_sort(src, a, b, np, less, st);
+  Buckets B{};
+  B.n = n;
+  B.nb = kMaxBuckets;
+  while (B.nb > 32 && n / B.nb < 128) B.nb >>= 1;
+  T* split = (T*)scratch;
+  B.count = (int32_t*)((char*)scratch + sizeof(T) * kMaxBuckets);
+  B.slots = B.count + kMaxBuckets * kCountPad;
+  const size_t room = (scratch_bytes - ((char*)B.slots - (char*)scratch)) / sizeof(int32_t);
+  B.cap = (int32_t)std::min<size_t>(room / B.nb, kBucketMax);
+  constexpr int own = kSampleThreads / 64;   // samples per workgroup
+  static_assert(kFewSamples / own * kSampleThreads >= kMaxBuckets * kCountPad, "every counter is cleared");
+  if (n <= kFewSamplesMax)
+    hipLaunchKernelGGL((k_sample_rank<kFewSamples, T, Less, Src>), dim3(kFewSamples / own), dim3(kSampleThreads), 0, st,
+                       src, split, B, less);
+  else
+    hipLaunchKernelGGL((k_sample_rank<kManySamples, T, Less, Src>), dim3(kManySamples / own), dim3(kSampleThreads), 0,
+                       st, src, split, B, less);
+  hipLaunchKernelGGL((k_bucket_scatter<T, Less, Src>), dim3((unsigned)((n + kScatterThreads - 1) / kScatterThreads)),
+                     dim3(kScatterThreads), 0, st, src, split, B, less);
+  hipLaunchKernelGGL((k_bucket_sort<T, Less, Src>), dim3((unsigned)B.nb), dim3(kBucketThreads), 0, st, src, b, split, B,
+                     pad, less);
+  return b;
 }
 
 }  // namespace msort
