@@ -34,18 +34,17 @@
 //     parent's K differs), and from each top the sort element of its leaf
 //     (E, leaf, run length), with the byte histograms of E and the OR and
 //     AND of all keys.
-//  4. k_ev_pass, one launch per byte of E that can be nonzero: a stable
-//     least-significant-digit radix pass over the leaves, one tile of 4096
-//     per workgroup. Tiles take ids in launch order from a counter and
-//     publish their per-digit counts; a tile's offsets come from the counts
-//     of the earlier tiles of its group of 16 plus the group totals of the
-//     earlier groups (the last tile of a group publishes its total). Every
-//     tile runs at once, so a look-back chain from tile to tile would wait
-//     for its predecessors one after another; two levels wait twice. A byte
-//     on which all keys agree is skipped on the device.
-//  5. k_ev_scan: S of every leaf, the exclusive prefix of run lengths over
-//     the sorted leaves (one total per tile: a tile sums the earlier ones).
+//  4. k_ev_segs: the segments (consecutive leaves of equal E), which is all
+//     that is left to sort.
+//  5. k_ev_sort: where each segment starts in the victim order. Up to 4096
+//     segments every one is counted against all; more go through stable
+//     least-significant-digit radix passes over 4096-segment tiles, a byte on
+//     which all keys agree being skipped, and a prefix of the run lengths.
+//     All passes are one launch: workgroups take (pass, tile) tickets in
+//     order and a tile waits until the pass before it is complete.
 //  6. k_ev_place: every node to S(K.id) + level(K.id) - level(c).
+// A tree of up to 4096 nodes is ranked by one workgroup in LDS instead
+// (k_ev_small), in one launch.
 #include <algorithm>
 
 #include "peek_internal.h"
@@ -243,11 +242,12 @@ constexpr int kHistCopies = 8;        // ... and to histogram copy g % 8
 constexpr int kMaxDigits = 8;
 constexpr int kRadix = 256;
 
-// Tile counters, in Counters::ticket: the radix passes, then the segment
-// pass and the segment scan.
-constexpr int kTicketSegs = kMaxDigits;
-constexpr int kTicketScan = kMaxDigits + 1;
-constexpr int kTickets = kMaxDigits + 2;
+// Counters::ticket: tickets of the segment kernel and of the sort, then the
+// finished tiles of each radix pass.
+constexpr int kTicketSegs = 0;
+constexpr int kTicketSort = 1;
+constexpr int kTicketDone = 2;
+constexpr int kTickets = kTicketDone + kMaxDigits;
 
 struct Counters {
   uint32_t* ticket;   // [kTickets]
@@ -436,7 +436,7 @@ __global__ __launch_bounds__(kKeyThreads) void k_ev_keys(KeyArgs a) {
   }
 }
 
-// ---- 4-6. segments, radix passes over them, segment starts ----
+// ---- 4-5. segments and their starts ----
 
 constexpr int kPThreads = 512;
 constexpr int kPWaves = kPThreads / kWave;
@@ -643,7 +643,7 @@ static_assert(sizeof(SegElem) == 16, "SegElem is 16 bytes");
 
 // Segments: maximal runs of consecutive leaves (by leaf rank) with equal E.
 // Sorting the leaves by (E, id) is sorting the segments by E stably, so only
-// segments go through the radix passes. Per leaf rank: its segment and the
+// segments are sorted. Per leaf rank: its segment and the
 // exclusive prefix RP of run lengths in leaf order; per segment: its sort
 // element, RP at its first leaf, the byte histograms and OR/AND of E.
 // Prefix values pack the segment count (bits 31..61) and the run lengths
@@ -662,98 +662,6 @@ struct SegArgs {
   uint64_t* agg;      // [tiles]
   Counters z;
 };
-
-struct SmallLds {
-  uint64_t key[kPTile];          // E of segment i (segments are in leaf order)
-  uint16_t ibuf[kPTile];         // the order being built
-  uint32_t whist[kPWaves][kRadix];
-  uint32_t tstart[kRadix];
-  uint32_t wsum[kRadix / kWave];
-  uint64_t wsum64[kPWaves];
-};
-static_assert(kPTile <= 65536, "segment indices fit 16 bits");
-
-// One workgroup sorts L <= kPTile segments by E (stable radix passes over
-// the bytes that differ; the keys stay in LDS and only segment indices
-// move) and writes each segment's start in the victim order: the exclusive
-// prefix of the segments' run totals.
-__device__ void small_sort(const SegElem* __restrict__ el, const int32_t* __restrict__ segRP, int32_t* __restrict__ Sseg,
-                           int32_t L, int32_t nn, int n_digits, uint64_t diff, SmallLds& sh) {
-  const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  int32_t ix[kPItems];
-  bool valid[kPItems];
-  uint64_t key[kPItems];
-#pragma unroll
-  for (int q = 0; q < kPItems; ++q) {
-    ix[q] = w * (kWave * kPItems) + q * kWave + lane;
-    valid[q] = ix[q] < L;
-    key[q] = el[valid[q] ? ix[q] : L - 1].ke;   // el[i] is segment i
-  }
-#pragma unroll
-  for (int q = 0; q < kPItems; ++q)
-    if (valid[q]) sh.key[ix[q]] = key[q];
-  for (int p = 0; p < n_digits; ++p) {
-    if (((diff >> (8 * p)) & 255u) == 0) continue;   // uniform
-    uint32_t dg[kPItems], rk[kPItems];
-#pragma unroll
-    for (int q = 0; q < kPItems; ++q) dg[q] = valid[q] ? (uint32_t)(key[q] >> (8 * p)) & 255u : 0;
-    for (int i = t; i < kPWaves * kRadix; i += kPThreads) (&sh.whist[0][0])[i] = 0;
-    __syncthreads();
-    wave_rank(dg, valid, rk, sh.whist[w], lane);
-    __syncthreads();
-    if (t < kRadix) {
-      uint32_t cnt = 0;
-#pragma unroll
-      for (int j = 0; j < kPWaves; ++j) {
-        const uint32_t c = sh.whist[j][t];
-        sh.whist[j][t] = cnt;
-        cnt += c;
-      }
-      uint32_t x = cnt;
-#pragma unroll
-      for (int k = 1; k < kWave; k <<= 1) {
-        const uint32_t o = __shfl(x, lane >= k ? lane - k : lane);
-        if (lane >= k) x += o;
-      }
-      if (lane == kWave - 1) sh.wsum[w] = x;
-      sh.tstart[t] = x - cnt;
-    }
-    __syncthreads();
-    if (t < kRadix)
-      for (int j = 0; j < w; ++j) sh.tstart[t] += sh.wsum[j];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kPItems; ++q)
-      if (valid[q]) sh.ibuf[sh.tstart[dg[q]] + sh.whist[w][dg[q]] + rk[q]] = (uint16_t)ix[q];
-    __syncthreads();
-#pragma unroll
-    for (int q = 0; q < kPItems; ++q) {
-      if (valid[q]) {
-        ix[q] = sh.ibuf[w * (kWave * kPItems) + q * kWave + lane];
-        key[q] = sh.key[ix[q]];
-      }
-    }
-    __syncthreads();
-  }
-  // run totals in sorted order (segRP staged in LDS where the keys were),
-  // then their prefix
-  int32_t* srp = (int32_t*)sh.key;
-  static_assert(sizeof(sh.key) >= sizeof(int32_t) * (kPTile + 1), "segRP fits where the keys were");
-  __syncthreads();   // the keys are dead (also when no pass ran)
-  for (int i = t; i < L; i += kPThreads) srp[i] = segRP[i];
-  if (t == 0) srp[L] = nn;
-  __syncthreads();
-  uint64_t val[kPItems], pre[kPItems];
-#pragma unroll
-  for (int q = 0; q < kPItems; ++q) {
-    const int32_t sg = valid[q] ? ix[q] : 0;
-    val[q] = valid[q] ? (uint64_t)(uint32_t)(srp[sg + 1] - srp[sg]) : 0;
-  }
-  tile_prefix(val, pre, sh.wsum64);
-#pragma unroll
-  for (int q = 0; q < kPItems; ++q)
-    if (valid[q]) Sseg[ix[q]] = (int32_t)pre[q];
-}
 
 __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
   __shared__ int32_t s_tile;
@@ -837,61 +745,95 @@ __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
   }
 }
 
-struct PassArgs {
+struct SortArgs {
   SegElem* a;
   SegElem* b;
-  int p;               // byte of E
   int n_digits;
-  uint64_t* agg;       // [tiles][kRadix] of this pass
-  uint64_t* grp;       // [groups][kRadix] of this pass
+  uint64_t* status;      // per byte of E: [tiles][kRadix], then [groups][kRadix] status words
+  int64_t per_pass;      // words of one byte
+  int64_t grp_at;        // where the group words start
+  uint64_t* scan;        // [tiles]
   const int32_t* segRP;
   int32_t* Sseg;
   int32_t nn;
   Counters z;
 };
 
-// Workgroups beyond the segments' tiles return at once (the launch covers
-// the most segments there can be, one per leaf). When the segments fit one
-// tile, the first pass's workgroup 0 sorts them all and writes their
-// starts (small_sort), and the later passes and the scan have nothing to do.
-__global__ __launch_bounds__(kPThreads) void k_ev_pass(PassArgs A) {
-  __shared__ uint64_t oa[2];
-  __shared__ int32_t s_tile;
-  __shared__ uint32_t cnt_s[kRadix];
-  __shared__ uint32_t part[2][kRadix];
-  __shared__ uint32_t gbase[kRadix];
-  __shared__ uint32_t wsum[kRadix / kWave];
-  __shared__ uint32_t whist[kPWaves][kRadix];
-  extern __shared__ unsigned char dyn_lds[];   // SmallLds, first pass only
-  const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  const int p = A.p;
-  const int d = t & (kRadix - 1), half = t / kRadix;
-  const int32_t L = *A.z.nseg;
-  if (L <= kPTile) {
-    if (p != 0 || blockIdx.x != 0) return;
-    fold_orand(A.z.orand, oa);
-    small_sort(A.a, A.segRP, A.Sseg, L, A.nn, A.n_digits, oa[0] ^ oa[1], *(SmallLds*)dyn_lds);
-    return;
+// Segments move between passes inside one launch, so they are written
+// through to where every XCD sees them, and read from there.
+__device__ __forceinline__ SegElem load_shared(const SegElem* p) {
+  const uint64_t* w = reinterpret_cast<const uint64_t*>(p);
+  const uint64_t k = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  const uint64_t g = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  return SegElem{k, (int32_t)(uint32_t)g, 0};
+}
+__device__ __forceinline__ void store_shared(SegElem* p, const SegElem& v) {
+  uint64_t* w = reinterpret_cast<uint64_t*>(p);
+  __hip_atomic_store(w, v.ke, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __hip_atomic_store(w + 1, (uint64_t)(uint32_t)v.seg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+struct PassLds {
+  uint32_t cnt[kRadix];
+  uint32_t part[2][kRadix];
+  uint32_t gbase[kRadix];
+  uint32_t wsum[kRadix / kWave];
+  uint32_t whist[kPWaves][kRadix];
+};
+struct RankLds {
+  uint64_t key[kPTile];
+  uint32_t run[kPTile];
+};
+
+// Every segment's start, counted: the run lengths of the segments before it
+// in (E, leaf) order. Every workgroup stages all keys and run lengths (at
+// most 48 KB) and its wavefronts count kOwn segments at a time.
+__device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
+  constexpr int kOwn = 2;
+  const int t = threadIdx.x, lane = t & (kWave - 1);
+  for (int i = t; i < L; i += kPThreads) {
+    sh.key[i] = A.a[i].ke;   // a[i] is segment i
+    sh.run[i] = (uint32_t)((i + 1 < L ? A.segRP[i + 1] : A.nn) - A.segRP[i]);
   }
-  const int32_t tiles = (L + kPTile - 1) / kPTile;
-  if ((int32_t)blockIdx.x >= tiles) return;
-  fold_orand(A.z.orand, oa);
-  const uint64_t diff = oa[0] ^ oa[1];
-  if (!pass_runs(diff, p)) return;   // workgroup-uniform
-  int before = 0;
-  for (int q = 0; q < p; ++q) before += pass_runs(diff, q) ? 1 : 0;
-  const SegElem* __restrict__ src = (before & 1) ? A.b : A.a;
-  SegElem* __restrict__ dst = (before & 1) ? A.a : A.b;
-  // the digit's histogram is loaded alongside the ticket and the tile
+  __syncthreads();
+  const int32_t waves = (int32_t)gridDim.x * kPWaves;
+  const int32_t wv = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x * kPWaves + t / kWave);
+  for (int32_t i0 = wv * kOwn; i0 < L; i0 += waves * kOwn) {
+    uint64_t own[kOwn];
+    uint32_t sum[kOwn];
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      own[q] = sh.key[min(i0 + q, L - 1)];
+      sum[q] = 0;
+    }
+    for (int32_t j0 = 0; j0 < L; j0 += kWave) {
+      const int32_t j = j0 + lane;
+      const uint64_t k = sh.key[min(j, L - 1)];
+      const uint32_t r = j < L ? sh.run[min(j, L - 1)] : 0;
+#pragma unroll
+      for (int q = 0; q < kOwn; ++q) sum[q] += (k < own[q]) | ((k == own[q]) & (j < i0 + q)) ? r : 0;
+    }
+#pragma unroll
+    for (int q = 0; q < kOwn; ++q) {
+      for (int d = 1; d < kWave; d <<= 1) sum[q] += __shfl_xor(sum[q], d);
+      if (lane == 0 && i0 + q < L) A.Sseg[i0 + q] = (int32_t)sum[q];
+    }
+  }
+}
+
+// One tile of the radix pass over byte p, src to dst.
+__device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, bool first, int p, int32_t tile,
+                           int32_t tiles, int32_t L, PassLds& sh) {
+  const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
+  const int d = t & (kRadix - 1), half = t / kRadix;
+  // the digit's histogram is loaded alongside the tile
   uint32_t h = 0;
   if (half == 0) {
 #pragma unroll
     for (int q = 0; q < kHistCopies; ++q) h += A.z.hist[((size_t)q * kMaxDigits + p) * kRadix + d];
   }
-  if (t == 0) s_tile = (int32_t)atomicAdd(&A.z.ticket[p], 1u);
-  for (int i = t; i < kPWaves * kRadix; i += kPThreads) (&whist[0][0])[i] = 0;
+  for (int i = t; i < kPWaves * kRadix; i += kPThreads) (&sh.whist[0][0])[i] = 0;
   __syncthreads();
-  const int32_t tile = s_tile;
   const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
   SegElem v[kPItems];
   uint32_t dg[kPItems], rk[kPItems];
@@ -902,25 +844,27 @@ __global__ __launch_bounds__(kPThreads) void k_ev_pass(PassArgs A) {
   for (int q = 0; q < kPItems; ++q) {
     const int64_t idx = base + q * kWave + lane;
     valid[q] = idx < L;
-    v[q] = src[valid[q] ? idx : L - 1];
+    v[q] = first ? src[valid[q] ? idx : L - 1] : load_shared(src + (valid[q] ? idx : L - 1));
   }
 #pragma unroll
   for (int q = 0; q < kPItems; ++q) dg[q] = valid[q] ? (uint32_t)(v[q].ke >> (8 * p)) & 255u : 0;
-  wave_rank(dg, valid, rk, whist[w], lane);
+  wave_rank(dg, valid, rk, sh.whist[w], lane);
   __syncthreads();
   if (half == 0) {
     // the waves' exclusive offsets of digit d and the tile's count
     uint32_t cnt = 0;
 #pragma unroll
     for (int j = 0; j < kPWaves; ++j) {
-      const uint32_t c = whist[j][d];
-      whist[j][d] = cnt;
+      const uint32_t c = sh.whist[j][d];
+      sh.whist[j][d] = cnt;
       cnt += c;
     }
-    cnt_s[d] = cnt;
+    sh.cnt[d] = cnt;
   }
   __syncthreads();
-  part[half][d] = (uint32_t)two_level_part(A.agg + d, A.grp + d, kRadix, tile, tiles, cnt_s[d], half, A.z.err);
+  uint64_t* agg = A.status + (int64_t)p * A.per_pass;
+  sh.part[half][d] = (uint32_t)two_level_part(agg + d, agg + A.grp_at + d, kRadix, tile, tiles, sh.cnt[d], half,
+                                              A.z.err);
   if (half == 0) {
     // the digit's start over all segments: counts of smaller digits
     // (exclusive scan of the histogram over the 4 waves of half 0)
@@ -930,62 +874,34 @@ __global__ __launch_bounds__(kPThreads) void k_ev_pass(PassArgs A) {
       const uint32_t o = __shfl(x, lane >= e ? lane - e : lane);
       if (lane >= e) x += o;
     }
-    if (lane == kWave - 1) wsum[w] = x;
-    gbase[d] = x - h;
+    if (lane == kWave - 1) sh.wsum[w] = x;
+    sh.gbase[d] = x - h;
   }
   __syncthreads();
   if (half == 0) {
-    uint32_t g = gbase[d] + part[0][d] + part[1][d];
-    for (int j = 0; j < w; ++j) g += wsum[j];
-    gbase[d] = g;
+    uint32_t g = sh.gbase[d] + sh.part[0][d] + sh.part[1][d];
+    for (int j = 0; j < w; ++j) g += sh.wsum[j];
+    sh.gbase[d] = g;
   }
   __syncthreads();
 #pragma unroll
   for (int q = 0; q < kPItems; ++q) {
     if (!valid[q]) continue;
-    const uint32_t pos = gbase[dg[q]] + whist[w][dg[q]] + rk[q];
-    if (pos < (uint32_t)L) dst[pos] = v[q];
+    const uint32_t pos = sh.gbase[dg[q]] + sh.whist[w][dg[q]] + rk[q];
+    if (pos < (uint32_t)L) store_shared(dst + pos, v[q]);
   }
 }
 
-// Start of every segment in the victim order: the exclusive prefix of the
-// segments' run totals over the sorted segments (in the buffer the last
-// pass that ran wrote). A segment's run total is RP at the next segment's
-// first leaf (or the node count) minus RP at its own. Nothing to do when
-// the segment pass sorted them.
-struct ScanArgs {
-  const SegElem* a;
-  const SegElem* b;
-  const int32_t* segRP;
-  int32_t nn;
-  int n_digits;
-  uint64_t* agg;   // [tiles]
-  int32_t* Sseg;   // [segments]
-  Counters z;
-};
-
-__global__ __launch_bounds__(kPThreads) void k_ev_scan(ScanArgs A) {
-  __shared__ uint64_t oa[2];
-  __shared__ int32_t s_tile;
-  __shared__ uint64_t wsum[kPWaves];
-  __shared__ uint64_t s_excl;
+// One tile of the prefix of run lengths over the sorted segments, which is
+// every segment's start in the victim order. A segment's run total is RP at
+// the next segment's first leaf (or the node count) minus RP at its own.
+__device__ void scan_tile(const SortArgs& A, const SegElem* el, int32_t tile, int32_t L, uint64_t* wsum,
+                          uint64_t* s_excl) {
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  const int32_t L = *A.z.nseg;
-  if (L <= kPTile) return;   // the first pass did it
-  fold_orand(A.z.orand, oa);
-  const int32_t tiles = (L + kPTile - 1) / kPTile;
-  if ((int32_t)blockIdx.x >= tiles) return;
-  const uint64_t diff = oa[0] ^ oa[1];
-  int ran = 0;
-  for (int q = 0; q < A.n_digits; ++q) ran += pass_runs(diff, q) ? 1 : 0;
-  const SegElem* __restrict__ el = (ran & 1) ? A.b : A.a;
-  if (t == 0) s_tile = (int32_t)atomicAdd(&A.z.ticket[kTicketScan], 1u);
-  __syncthreads();
-  const int32_t tile = s_tile;
   const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
   int32_t seg[kPItems], r0[kPItems], r1[kPItems];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) seg[i] = el[min(base + i * kWave + lane, (int64_t)L - 1)].seg;   // clamped
+  for (int i = 0; i < kPItems; ++i) seg[i] = load_shared(el + min(base + i * kWave + lane, (int64_t)L - 1)).seg;
 #pragma unroll
   for (int i = 0; i < kPItems; ++i) {
     const int32_t sc = (uint32_t)seg[i] < (uint32_t)L ? seg[i] : 0;
@@ -1001,16 +917,79 @@ __global__ __launch_bounds__(kPThreads) void k_ev_scan(ScanArgs A) {
   }
   const uint64_t total = tile_prefix(val, pre, wsum);
   if (w == 0) {
-    if (lane == 0) publish(&A.agg[tile], total);
-    const uint64_t ex = sum_before(A.agg, tile, A.z.err);
-    if (lane == 0) s_excl = ex;
+    if (lane == 0) publish(&A.scan[tile], total);
+    const uint64_t ex = sum_before(A.scan, tile, A.z.err);
+    if (lane == 0) *s_excl = ex;
   }
   __syncthreads();
-  const uint64_t start = s_excl;
+  const uint64_t start = *s_excl;
 #pragma unroll
   for (int i = 0; i < kPItems; ++i) {
     const int64_t idx = base + i * kWave + lane;
     if (idx < L && (uint32_t)seg[i] < (uint32_t)L) A.Sseg[seg[i]] = (int32_t)(start + pre[i]);
+  }
+}
+
+// The start of every segment in the victim order. Whether the segments are
+// few is known on the device only, so one launch holds both ways. Measured
+// on a million nodes (some 3,500 segments): 4.4 us, where a launch per byte of E,
+// the first of which sorted the segments in one workgroup, and one for the
+// prefix took 31 us.
+// The passes need no launch each and no resident grid: a workgroup that
+// waits holds one ticket, and what it waits for (the tiles of the pass
+// before, earlier tiles of its own pass) holds lower tickets, whose
+// workgroups are running and wait for still lower ones only.
+__global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
+  __shared__ union {
+    RankLds rank;
+    PassLds pass;
+  } sh;
+  __shared__ uint64_t oa[2], wsum[kPWaves], s_excl;
+  __shared__ int32_t s_ticket;
+  const int t = threadIdx.x;
+  const int32_t L = *A.z.nseg;
+  if (L <= kPTile) {
+    rank_segments(A, L, sh.rank);
+    return;
+  }
+  fold_orand(A.z.orand, oa);
+  const uint64_t diff = oa[0] ^ oa[1];
+  int passes = 0;
+  for (int q = 0; q < A.n_digits; ++q) passes += pass_runs(diff, q) ? 1 : 0;
+  const int32_t tiles = (L + kPTile - 1) / kPTile;
+  while (true) {
+    __syncthreads();   // the tile before is done with LDS
+    if (t == 0) s_ticket = (int32_t)atomicAdd(&A.z.ticket[kTicketSort], 1u);
+    __syncthreads();
+    const int32_t ticket = s_ticket;
+    if (ticket >= (passes + 1) * tiles) return;
+    const int k = ticket / tiles;   // the pass; after the last one the prefix
+    const int32_t tile = ticket % tiles;
+    if (k > 0 && t == 0) {
+      uint32_t* done = &A.z.ticket[kTicketDone + k - 1];
+      for (uint32_t spins = 0; __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)tiles;
+           ++spins) {
+        if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
+          atomicOr(A.z.err, 1u);
+          break;
+        }
+        __builtin_amdgcn_s_sleep(2);
+      }
+    }
+    __syncthreads();
+    SegElem* src = (k & 1) ? A.b : A.a;
+    if (k == passes) {
+      scan_tile(A, src, tile, L, wsum, &s_excl);
+      continue;
+    }
+    int p = -1;
+    for (int q = 0, seen = 0; q < A.n_digits; ++q)
+      if (pass_runs(diff, q) && seen++ == k) p = q;
+    radix_tile(A, src, (k & 1) ? A.a : A.b, k == 0, p, tile, tiles, L, sh.pass);
+    // the written-through segments have arrived once the stores are answered
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (t == 0) __hip_atomic_fetch_add(&A.z.ticket[kTicketDone + k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
 }
 
@@ -1040,6 +1019,219 @@ __global__ void k_ev_place(PlaceArgs A) {
   if ((uint32_t)sg >= (uint32_t)A.L) return;
   const int64_t pos = (int64_t)A.Sseg[sg] + rp - A.segRP[sg] + dl;
   if (pos >= 0 && pos < A.nn - 1) A.order[pos] = c;
+}
+
+// ---- small trees ----
+
+// A tree of up to kSmallMax nodes, whole, by one workgroup: E by pointer
+// jumping, K by doubling windows (a subtree of len nodes is covered by two
+// windows of 2^floor(log2 len)), segments as in k_ev_segs, a bitonic network
+// over the segments, prefixes of their run lengths, placement. Keys pack
+// (E, id) into E << 12 | id. Bound by LDS accesses and barriers of some 60
+// steps, so a thread holds no more nodes than the tree needs (kPer) and only
+// segments are sorted: 1,519 cached chat prompts take 14.7 us (28.7 with all
+// leaves sorted and four nodes per thread), the launches of the general path
+// 28 to 30 us at this size. The line lies where LDS does: as many segments as
+// leaves at 4096 nodes are the one case in which the general path would do
+// better.
+constexpr int kSmallMax = 4096;
+constexpr int kSmallThreads = 1024;
+constexpr int kSmallBits = 12;
+static_assert((1 << kSmallBits) == kSmallMax, "ids fit the low bits of a key");
+
+// Inclusive prefix sum over the workgroup; wsum: a word per wavefront.
+__device__ __forceinline__ int32_t small_scan(int32_t v, int32_t* wsum) {
+  const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int32_t o = __shfl(v, lane >= d ? lane - d : lane);
+    if (lane >= d) v += o;
+  }
+  if (lane == kWave - 1) wsum[w] = v;
+  __syncthreads();
+  for (int i = 0; i < w; ++i) v += wsum[i];
+  return v;
+}
+
+template <int kPer>
+__global__ __launch_bounds__(kSmallThreads) void k_ev_small(EvictTree T, const int32_t* __restrict__ demand,
+                                                            int32_t nn, int32_t max_level,
+                                                            int64_t* __restrict__ score, int32_t* __restrict__ order) {
+  constexpr int N = kPer * kSmallThreads;
+  __shared__ uint64_t a[N];
+  __shared__ int32_t b[N];
+  __shared__ uint16_t lvl[N], run[N], seg_of[N], start[N];
+  __shared__ uint16_t seg_rp[N + 1];
+  __shared__ int32_t wsum[2][kSmallThreads / kWave];
+  const int t = threadIdx.x;
+  EvNode r[kPer];
+  int64_t e[kPer];
+  int32_t up[kPer], rank[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t cc = min(q * kSmallThreads + t, nn - 1);
+    r[q] = T.nodes[cc];
+    rank[q] = T.leaf_rank[cc];
+    e[q] = (int64_t)demand[cc] * r[q].depth;
+    up[q] = r[q].parent;
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;
+    a[c] = (uint64_t)e[q];
+    b[c] = up[q];
+    lvl[c] = (uint16_t)r[q].level;
+  }
+  __syncthreads();
+  // after each round a node covers twice as many nodes of its chain
+  for (int32_t span = 1; span <= max_level; span <<= 1) {
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (up[q] >= 0) {
+        e[q] = max(e[q], (int64_t)a[up[q]]);
+        up[q] = b[up[q]];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int32_t c = q * kSmallThreads + t;
+      a[c] = (uint64_t)e[q];
+      b[c] = up[q];
+    }
+    __syncthreads();
+  }
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;
+    if (c < nn && score != nullptr) score[c] = e[q];
+  }
+  if (order == nullptr) return;
+  // K: the largest key of every subtree (E is not negative: the root's is 0)
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;
+    a[c] = c < nn ? ((uint64_t)e[q] << kSmallBits) | (uint64_t)c : 0;
+  }
+  __syncthreads();
+  int32_t kid[kPer];
+  for (int k = 0; (1 << k) <= nn; ++k) {
+    uint64_t x[kPer];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      const int32_t c = q * kSmallThreads + t;
+      x[q] = a[c];
+      if (c < nn && 31 - __clz(r[q].end - c) == k)
+        kid[q] = (int32_t)(max(x[q], a[r[q].end - (1 << k)]) & (kSmallMax - 1));
+      if (c + (1 << k) < N) x[q] = max(x[q], a[c + (1 << k)]);   // past the nodes there are zeros
+    }
+    __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) a[q * kSmallThreads + t] = x[q];
+    __syncthreads();
+  }
+  // each node's place in the run of its leaf; by leaf: E, and (from the top
+  // of the run, whose parent follows another leaf) the run's length
+  int32_t dl[kPer];
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;
+    if (c >= nn) kid[q] = 0;
+    dl[q] = (int32_t)lvl[kid[q]] - r[q].level;
+    b[c] = kid[q];
+    if (c < nn && r[q].end == c + 1) {
+      a[rank[q]] = (uint64_t)e[q];
+      seg_of[c] = (uint16_t)rank[q];   // until the segments are known
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;
+    rank[q] = seg_of[kid[q]];   // the leaf's
+    if (c < nn && (r[q].parent < 0 || b[r[q].parent] != kid[q])) run[rank[q]] = (uint16_t)(dl[q] + 1);
+  }
+  __syncthreads();
+  // segments: thread t holds leaves kPer * t and on, in preorder
+  const int32_t L = T.n_leaves;
+  uint64_t key[kPer];
+  int32_t val[kPer], sum = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t i = kPer * t + q;
+    key[q] = a[min(i, L - 1)];
+    const bool head = i < L && (i == 0 || a[i - 1] != key[q]);
+    val[q] = i < L ? ((int32_t)head << 16) | (int32_t)run[i] : 0;
+    sum += val[q];
+  }
+  int32_t at = small_scan(sum, wsum[0]) - sum;
+  __syncthreads();   // E and the run lengths are read
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t i = kPer * t + q;
+    if (i < L) {
+      const int32_t s = (at >> 16) + (val[q] >> 16) - 1;   // the leaf's segment
+      seg_of[i] = (uint16_t)s;
+      run[i] = (uint16_t)at;   // the run lengths before it
+      if (val[q] >> 16) {
+        a[s] = (key[q] << kSmallBits) | (uint64_t)s;
+        seg_rp[s] = (uint16_t)at;
+      }
+    }
+    at += val[q];
+    if (i == N - 1) b[0] = at >> 16;
+  }
+  __syncthreads();
+  const int32_t S = b[0];
+  int32_t m = 2 * kWave;
+  while (m < S) m <<= 1;
+  for (int32_t i = S + t; i < m; i += kSmallThreads) a[i] = ~uint64_t(0);
+  if (t == 0) seg_rp[S] = (uint16_t)nn;
+  __syncthreads();
+  for (int32_t k = 2; k <= m; k <<= 1) {
+    for (int32_t j = k >> 1; j > 0; j >>= 1) {
+      const int32_t flip = j == k >> 1 ? k - 1 : j;
+      for (int32_t p = t; p < m / 2; p += kSmallThreads) {
+        const int32_t x = 2 * p - (p & (j - 1)), y = x ^ flip;
+        const uint64_t vx = a[x], vy = a[y];
+        a[x] = min(vx, vy);
+        a[y] = max(vx, vy);
+      }
+      // a wavefront's pairs stay inside 128 places while j <= 64: then only
+      // its own accesses need ordering
+      if (j > kWave || (j == 1 && k >= 2 * kWave)) {
+        __syncthreads();
+      } else {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+      }
+    }
+  }
+  __syncthreads();
+  // starts of the segments: thread t holds kPer of the order
+  int32_t sg[kPer];
+  sum = 0;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t i = kPer * t + q;
+    sg[q] = i < S ? (int32_t)(a[i] & (kSmallMax - 1)) : -1;
+    val[q] = sg[q] >= 0 ? (int32_t)seg_rp[sg[q] + 1] - (int32_t)seg_rp[sg[q]] : 0;
+    sum += val[q];
+  }
+  at = small_scan(sum, wsum[1]) - sum;
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    if (sg[q] >= 0) start[sg[q]] = (uint16_t)at;
+    at += val[q];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < kPer; ++q) {
+    const int32_t c = q * kSmallThreads + t;   // the root goes last and stays out
+    if (c < 1 || c >= nn) continue;
+    const int32_t s = seg_of[rank[q]];
+    const int32_t pos = (int32_t)start[s] + (int32_t)run[rank[q]] - (int32_t)seg_rp[s] + dl[q];
+    if (pos >= 0 && pos < nn - 1) order[pos] = c;
+  }
 }
 
 // ---- host ----
@@ -1119,6 +1311,18 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
   int n_digits = 0;
   const uint64_t e_bound = (uint64_t)INT32_MAX * (uint64_t)std::max<int64_t>(c->max_depth, 1);
   while (n_digits < kMaxDigits && (e_bound >> (8 * n_digits)) != 0) ++n_digits;
+  if (nn <= kSmallMax && (e_bound >> (64 - kSmallBits)) == 0) {
+    int32_t* out = ordered ? order : nullptr;
+    const dim3 one(1), threads(kSmallThreads);
+    if (nn <= kSmallThreads)
+      hipLaunchKernelGGL(k_ev_small<1>, one, threads, 0, st, t, demand, nn, c->max_level, score, out);
+    else if (nn <= 2 * kSmallThreads)
+      hipLaunchKernelGGL(k_ev_small<2>, one, threads, 0, st, t, demand, nn, c->max_level, score, out);
+    else
+      hipLaunchKernelGGL(k_ev_small<4>, one, threads, 0, st, t, demand, nn, c->max_level, score, out);
+    PEEK_HIP_TRY(hipGetLastError());
+    return PEEK_OK;
+  }
   const int32_t n_leaves = std::max(t.n_leaves, 1);
   const int32_t tiles = (n_leaves + kPTile - 1) / kPTile;
   const int32_t groups = (tiles + kGrp - 1) / kGrp;
@@ -1185,14 +1389,10 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     uint64_t* ss = status + (size_t)n_digits * per_pass;
     SegArgs ga{Er, runr, n_leaves, nn, tiles, n_digits, seg_of, RP, el_a, segRP, ss, z};
     hipLaunchKernelGGL(k_ev_segs, dim3((unsigned)tiles), dim3(kPThreads), 0, st, ga);
-    for (int p = 0; p < n_digits; ++p) {
-      uint64_t* ps = status + (size_t)p * per_pass;
-      PassArgs pa{el_a, el_b, p, n_digits, ps, ps + (size_t)kRadix * tiles, segRP, Sseg, nn, z};
-      hipLaunchKernelGGL(k_ev_pass, dim3((unsigned)tiles), dim3(kPThreads), p == 0 ? sizeof(SmallLds) : 0, st, pa);
-    }
-    uint64_t* sc = ss + tiles;
-    ScanArgs sa{el_a, el_b, segRP, nn, n_digits, sc, Sseg, z};
-    hipLaunchKernelGGL(k_ev_scan, dim3((unsigned)tiles), dim3(kPThreads), 0, st, sa);
+    SortArgs sa{el_a, el_b, n_digits, status, per_pass, (int64_t)kRadix * tiles, ss + tiles, segRP, Sseg, nn, z};
+    // a workgroup per tile there can be; 64 at least, to count few segments
+    const unsigned sort_blocks = (unsigned)std::min(std::max(tiles, 64), 1024);
+    hipLaunchKernelGGL(k_ev_sort, dim3(sort_blocks), dim3(kPThreads), 0, st, sa);
     PlaceArgs la{krank, kdl, seg_of, RP, segRP, Sseg, nn, n_leaves, order};
     hipLaunchKernelGGL(k_ev_place, dim3(blocks_of(nn - 1)), dim3(256), 0, st, la);
   }
