@@ -307,6 +307,10 @@ struct ClElem {
   uint32_t len;
 };
 
+// Flags after the first round: [any active segment, a segment the second
+// round takes]; then the small queue's counters (see k_small_refine).
+constexpr int kFlags = 5;
+
 constexpr uint64_t kLenMax = 0x7FFFFFFFull;   // also the mask of a request in a key's low 31 bits
 
 // Largest segment the second round orders inside one workgroup.
@@ -640,15 +644,11 @@ __global__ __launch_bounds__(256) void k_first_compare(AnchorIn in, HeadTable T,
 // position of each last node's run also records P[c] and the node's bit in
 // ride.keyed (the order is sorted by last node first), for
 // demand_fill_block.
-__global__ __launch_bounds__(256) void k_first_groups(int32_t n, const AncElem* __restrict__ sd, AnchorIn in,
-                                                      DeviceTree t, ClElem* __restrict__ el,
-                                                      int32_t* __restrict__ nseg, int32_t* __restrict__ gsize,
-                                                      int32_t* __restrict__ depth, uint8_t* __restrict__ active,
-                                                      uint64_t* __restrict__ head, int32_t* __restrict__ lcp,
-                                                      int32_t* __restrict__ flags, DemandRide ride) {
-  const int lane = threadIdx.x & (kWave - 1);
-  const int32_t base = __builtin_amdgcn_readfirstlane(((int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x / kWave)) * kWave);
-  if (base >= n) return;
+// One wavefront, positions base .. base + 63.
+__device__ __forceinline__ void first_groups(int32_t base, int lane, int32_t n, const AncElem* sd, const AnchorIn& in,
+                                             const DeviceTree& t, ClElem* el, int32_t* nseg, int32_t* gsize,
+                                             int32_t* depth, uint8_t* active, uint64_t* head, int32_t* lcp,
+                                             int32_t* flags, const DemandRide& ride) {
   const int32_t i = base + lane;
   const bool valid = i < n;
   // this position and both neighbours, loaded together (clamped indices; a
@@ -730,6 +730,17 @@ __global__ __launch_bounds__(256) void k_first_groups(int32_t n, const AncElem* 
   } else if (code1 == 0) {
     lcp[i] = (int32_t)(m + 1 + ell); // identical prompts that ended together after m
   }
+}
+
+__global__ __launch_bounds__(256) void k_first_groups(int32_t n, const AncElem* __restrict__ sd, AnchorIn in,
+                                                      DeviceTree t, ClElem* __restrict__ el,
+                                                      int32_t* __restrict__ nseg, int32_t* __restrict__ gsize,
+                                                      int32_t* __restrict__ depth, uint8_t* __restrict__ active,
+                                                      uint64_t* __restrict__ head, int32_t* __restrict__ lcp,
+                                                      int32_t* __restrict__ flags, DemandRide ride) {
+  const int lane = threadIdx.x & (kWave - 1);
+  const int32_t base = __builtin_amdgcn_readfirstlane(((int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x / kWave)) * kWave);
+  if (base < n) first_groups(base, lane, n, sd, in, t, el, nseg, gsize, depth, active, head, lcp, flags, ride);
 }
 
 // Head of a segment in the workgroup-local tail: the member at a hashed
@@ -819,7 +830,6 @@ constexpr int kTailThreads = 512;
 constexpr int kTailWaves = kTailThreads / kWave;
 constexpr int kTailCap = 4096;              // members the workgroup sorts in LDS
 constexpr int kTailList = 1024;              // sub-segments collected per pass and kind
-constexpr int kTailRoots = kTailRange / 2;   // segments of >= 2 members starting in one range
 constexpr uint64_t kCodeMask = (1ull << 33) - 1;
 static_assert(kSegSortMax <= kTailCap, "the second round's segments are sorted in LDS");
 
@@ -850,7 +860,7 @@ __device__ __forceinline__ bool tail_key_less(uint32_t ea, uint64_t ca, uint32_t
 // the first active group in the lanes and regroups it. `keyed`: the first
 // round's keys are in the elements already (hi = l << 33 | code), written
 // by the second round against its own head.
-__device__ void tail_wave_settle(const TailArgs& A, int32_t s, int32_t size, int32_t d0, int lane, bool keyed) {
+__device__ __forceinline__ void tail_wave_settle(const TailArgs& A, int32_t s, int32_t size, int32_t d0, int lane, bool keyed) {
   const bool in = lane < size;
   ClElem e{};
   if (in) e = A.el[s + lane];
@@ -958,7 +968,8 @@ __device__ void tail_wave_settle(const TailArgs& A, int32_t s, int32_t size, int
 // workgroup. Keys are written into the elements' hi/lo fields (hi = l << 33 |
 // code, lo = request), which nothing after the refinement reads; `keyed`:
 // the second round has written them already.
-__device__ void tail_wg_round(const TailArgs& A, int32_t s, int32_t sz, int32_t d, uint64_t* sa, uint64_t* sb,
+template <int kCap>
+__device__ __forceinline__ void tail_wg_round(const TailArgs& A, int32_t s, int32_t sz, int32_t d, uint64_t* sa, uint64_t* sb,
                               uint32_t* sp, uint64_t* cmask, bool keyed) {
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
   const int32_t hp = head_pos(s, d, sz);
@@ -992,7 +1003,7 @@ __device__ void tail_wg_round(const TailArgs& A, int32_t s, int32_t sz, int32_t 
     }
   }
   __syncthreads();
-  const bool fits = sz <= kTailCap;
+  const bool fits = sz <= kCap;
   if (fits) {
     const int M = ldssort::pow2_at_least(sz);
     for (int r = t; r < M; r += kTailThreads) {
@@ -1010,7 +1021,7 @@ __device__ void tail_wg_round(const TailArgs& A, int32_t s, int32_t sz, int32_t 
     ldssort::lds_sort<kTailThreads>(sa, sb, sp, M);
     // the permutation goes through registers, field by field (an array of
     // whole elements would be kept in scratch memory)
-    constexpr int kPer = kTailCap / kTailThreads;
+    constexpr int kPer = kCap / kTailThreads;
     uint64_t vh[kPer], vl[kPer];
     uint32_t vr[kPer], vn[kPer];
 #pragma unroll
@@ -1106,22 +1117,27 @@ __device__ void tail_wg_round(const TailArgs& A, int32_t s, int32_t sz, int32_t 
   __syncthreads();
 }
 
-static_assert(kTailRange <= kTailThreads, "one position per thread in the root scan");
-__global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
+template <int kRange, int kCap>
+struct TailLds {
+  uint64_t sa[kCap];
+  uint64_t sb[kCap];
+  uint32_t sp[kCap];
+  uint64_t cmask[kCap / kWave];
+  int32_t root_s[kRange / 2], root_e[kRange / 2];   // segments of >= 2 members starting in the range
+  int32_t small_l[kTailList], big_l[kTailList];
+  int32_t n_roots, n_small, n_big;
+};
+
+// The segments that start in positions [p0, p0 + kRange), by one workgroup.
+template <int kRange, int kCap>
+__device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailLds<kRange, kCap>& S) {
+  static_assert(kRange <= kTailThreads, "one position per thread in the root scan");
   const int32_t f0 = A.flags[0];        // tested once the root loads below are issued
   const bool keyed = A.flags[1] != 0;   // the second round compared its segments
   const int32_t* depth = A.depth;
   const uint8_t* active = A.active;
-  __shared__ uint64_t sa[kTailCap];
-  __shared__ uint64_t sb[kTailCap];
-  __shared__ uint32_t sp[kTailCap];
-  __shared__ uint64_t cmask[kTailCap / kWave];
-  __shared__ int32_t root_s[kTailRoots], root_e[kTailRoots];
-  __shared__ int32_t small_l[kTailList], big_l[kTailList];
-  __shared__ int32_t n_roots, n_small, n_big;
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  const int32_t p0 = (int32_t)blockIdx.x * kTailRange;
-  const int32_t p1 = min(A.n, p0 + kTailRange);
+  const int32_t p1 = min(A.n, p0 + kRange);
   // the three loads of this thread's position are issued with the gate's (a
   // load behind a branch on another one would wait for it)
   const int32_t p = p0 + t, pc = min(p, A.n - 1);
@@ -1129,31 +1145,31 @@ __global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
   const uint8_t ac = active[pc];
   const int32_t gz = A.gsize[pc];
   if (f0 == 0) return;
-  if (t == 0) n_roots = 0;
+  if (t == 0) S.n_roots = 0;
   __syncthreads();
   if (p < p1 && sg == p && ac) {
-    const int k = atomicAdd(&n_roots, 1);
-    root_s[k] = p;
-    root_e[k] = p + gz;
+    const int k = atomicAdd(&S.n_roots, 1);
+    S.root_s[k] = p;
+    S.root_e[k] = p + gz;
   }
   __syncthreads();
-  const int nr = n_roots;
+  const int nr = S.n_roots;
   if (nr == 0) return;
   // the second round's segments of at most 64 members, from the keys it
   // wrote: each is settled completely by one wavefront and leaves the list
   // (its range is emptied)
   if (keyed) {
     for (int k = wave; k < nr; k += kTailWaves) {
-      const int32_t s = root_s[k], sz = root_e[k] - s;
+      const int32_t s = S.root_s[k], sz = S.root_e[k] - s;
       if (sz <= kWave) {
         tail_wave_settle(A, s, sz, depth[s], lane, true);
-        if (lane == 0) root_e[k] = s;
+        if (lane == 0) S.root_e[k] = s;
       }
     }
     __syncthreads();
   }
   for (int k = 0; k < nr; ++k) {
-    const int32_t s = root_s[k], e = root_e[k];
+    const int32_t s = S.root_s[k], e = S.root_e[k];
     for (int32_t q = s + t; q < e; q += kTailThreads) A.tact[q] = q == s;
     if (t == 0 && e > s) {
       A.tdep[s] = depth[s];
@@ -1165,8 +1181,8 @@ __global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
   // (their parts are then collected by the passes below)
   if (keyed) {
     for (int k = 0; k < nr; ++k) {
-      const int32_t s = root_s[k], sz = root_e[k] - s;
-      if (sz > kWave && round_takes(sz)) tail_wg_round(A, s, sz, depth[s], sa, sb, sp, cmask, true);
+      const int32_t s = S.root_s[k], sz = S.root_e[k] - s;
+      if (sz > kWave && round_takes(sz)) tail_wg_round<kCap>(A, s, sz, depth[s], S.sa, S.sb, S.sp, S.cmask, true);
     }
   }
   // Each pass settles at least one small segment or gives at least one large
@@ -1175,41 +1191,46 @@ __global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
   // bound only guards the device against a broken invariant.
   for (int64_t pass = 0; pass <= 2 * (int64_t)A.n + 2; ++pass) {
     if (t == 0) {
-      n_small = 0;
-      n_big = 0;
+      S.n_small = 0;
+      S.n_big = 0;
     }
     __syncthreads();
     for (int k = 0; k < nr; ++k) {
-      const int32_t s = root_s[k], e = root_e[k];
+      const int32_t s = S.root_s[k], e = S.root_e[k];
       for (int32_t q = s + t; q < e; q += kTailThreads) {
         const uint8_t ac = A.tact[q];
         const int32_t z = A.tsize[q];
         if (ac) {
           if (z <= kWave) {
-            const int x = atomicAdd(&n_small, 1);
-            if (x < kTailList) small_l[x] = q;
+            const int x = atomicAdd(&S.n_small, 1);
+            if (x < kTailList) S.small_l[x] = q;
           } else {
-            const int x = atomicAdd(&n_big, 1);
-            if (x < kTailList) big_l[x] = q;
+            const int x = atomicAdd(&S.n_big, 1);
+            if (x < kTailList) S.big_l[x] = q;
           }
         }
       }
     }
     __syncthreads();
-    const int ns = min(n_small, kTailList), nb = min(n_big, kTailList);
+    const int ns = min(S.n_small, kTailList), nb = min(S.n_big, kTailList);
     if (ns == 0 && nb == 0) break;
     for (int x = wave; x < ns; x += kTailWaves) {
-      const int32_t q = small_l[x];
+      const int32_t q = S.small_l[x];
       tail_wave_settle(A, q, A.tsize[q], A.tdep[q], lane, false);
       if (lane == 0) A.tact[q] = 0;
     }
     __syncthreads();
     for (int x = 0; x < nb; ++x) {
-      const int32_t q = big_l[x];
-      tail_wg_round(A, q, A.tsize[q], A.tdep[q], sa, sb, sp, cmask, false);
+      const int32_t q = S.big_l[x];
+      tail_wg_round<kCap>(A, q, A.tsize[q], A.tdep[q], S.sa, S.sb, S.sp, S.cmask, false);
     }
     __syncthreads();
   }
+}
+
+__global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
+  __shared__ TailLds<kTailRange, kTailCap> S;
+  refine_tail(A, (int32_t)blockIdx.x * kTailRange, S);
 }
 
 // The rest of cLPM's per-request signals (Sec. 3.2, Alg. 2), computed from
@@ -1248,33 +1269,11 @@ constexpr int kInBlockLevels = 6;
 
 // share, the (share, request) key of every position (the request alone when
 // key_is_request), the in-block tables of lcp and of the key, and the
-// 64-wide block minima of both.
-__global__ __launch_bounds__(256) void k_final_blocks(int32_t n, const ClElem* __restrict__ el,
-                                                      const int32_t* __restrict__ lcp, uint64_t* __restrict__ key2,
-                                                      int32_t* __restrict__ ib1, uint64_t* __restrict__ ib2,
-                                                      int64_t ib_stride, int32_t* __restrict__ st1,
-                                                      uint64_t* __restrict__ st2, int32_t nb1, int32_t nb2,
-                                                      ClpmArgs cl, bool key_is_request, DemandRide ride) {
-  if ((int32_t)blockIdx.x >= ride.first_block) {
-    // kDiffNodes nodes per thread (fewer workgroups to dispatch), their
-    // loads issued together with clamped indices
-    const int32_t c0 = ((int32_t)blockIdx.x - ride.first_block) * (256 * kDiffNodes) + (int32_t)threadIdx.x;
-    int32_t end[kDiffNodes], pc[kDiffNodes], pe[kDiffNodes];
-#pragma unroll
-    for (int r = 0; r < kDiffNodes; ++r) {
-      const int32_t c = max(min(c0 + 256 * r, ride.nn - 1), 0);
-      end[r] = ride.nodes[c].subtree_end;
-      pc[r] = ride.P[c];
-    }
-#pragma unroll
-    for (int r = 0; r < kDiffNodes; ++r) pe[r] = ride.P[end[r]];
-#pragma unroll
-    for (int r = 0; r < kDiffNodes; ++r)
-      if (c0 + 256 * r < ride.nn) ride.demand[c0 + 256 * r] = pe[r] - pc[r];
-    return;
-  }
-  const int lane = threadIdx.x & (kWave - 1);
-  const int32_t b = (int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x / kWave);
+// 64-wide block minima of both. One wavefront, block b.
+__device__ __forceinline__ void final_block(int32_t b, int lane, int32_t n, const ClElem* el, const int32_t* lcp,
+                                            uint64_t* key2, int32_t* ib1, uint64_t* ib2, int64_t ib_stride,
+                                            int32_t* st1, uint64_t* st2, int32_t nb1, int32_t nb2, const ClpmArgs& cl,
+                                            bool key_is_request) {
   const int32_t i = b * kWave + lane;
   // both lcps and the element loaded together (clamped indices; loads
   // behind the range checks would wait one after another)
@@ -1321,6 +1320,35 @@ __global__ __launch_bounds__(256) void k_final_blocks(int32_t n, const ClElem* _
     if (b < nb1) st1[b] = b1;
     if (b < nb2) st2[b] = b2;
   }
+}
+
+// final_block of every block, and the demand difference.
+__global__ __launch_bounds__(256) void k_final_blocks(int32_t n, const ClElem* __restrict__ el,
+                                                      const int32_t* __restrict__ lcp, uint64_t* __restrict__ key2,
+                                                      int32_t* __restrict__ ib1, uint64_t* __restrict__ ib2,
+                                                      int64_t ib_stride, int32_t* __restrict__ st1,
+                                                      uint64_t* __restrict__ st2, int32_t nb1, int32_t nb2,
+                                                      ClpmArgs cl, bool key_is_request, DemandRide ride) {
+  if ((int32_t)blockIdx.x >= ride.first_block) {
+    // kDiffNodes nodes per thread (fewer workgroups to dispatch), their
+    // loads issued together with clamped indices
+    const int32_t c0 = ((int32_t)blockIdx.x - ride.first_block) * (256 * kDiffNodes) + (int32_t)threadIdx.x;
+    int32_t end[kDiffNodes], pc[kDiffNodes], pe[kDiffNodes];
+#pragma unroll
+    for (int r = 0; r < kDiffNodes; ++r) {
+      const int32_t c = max(min(c0 + 256 * r, ride.nn - 1), 0);
+      end[r] = ride.nodes[c].subtree_end;
+      pc[r] = ride.P[c];
+    }
+#pragma unroll
+    for (int r = 0; r < kDiffNodes; ++r) pe[r] = ride.P[end[r]];
+#pragma unroll
+    for (int r = 0; r < kDiffNodes; ++r)
+      if (c0 + 256 * r < ride.nn) ride.demand[c0 + 256 * r] = pe[r] - pc[r];
+    return;
+  }
+  final_block((int32_t)blockIdx.x * 4 + (int32_t)(threadIdx.x / kWave), threadIdx.x & (kWave - 1), n, el, lcp, key2, ib1,
+              ib2, ib_stride, st1, st2, nb1, nb2, cl, key_is_request);
 }
 
 __device__ __forceinline__ uint64_t umin64(uint64_t a, uint64_t b) { return a < b ? a : b; }
@@ -1391,7 +1419,7 @@ __global__ void k_final_tables_high(int32_t* __restrict__ st1, uint64_t* __restr
 // Minimum of a[lo..hi] inside one 64-block, from the in-block table: two
 // windows of the largest stored width (at most 32) that cover the range.
 template <typename T>
-__device__ __forceinline__ T in_block_min(const T* __restrict__ ib, int64_t stride, int32_t lo, int32_t hi) {
+__device__ __forceinline__ T in_block_min(const T* ib, int64_t stride, int32_t lo, int32_t hi) {
   const int k = min(31 - __clz(hi - lo + 1), kInBlockLevels - 1);
   const T x = ib[k * stride + lo], y = ib[k * stride + hi - (1 << k) + 1];
   return x < y ? x : y;
@@ -1409,10 +1437,10 @@ static_assert(kInBlockLevels > 3 && (1 << 3) == kWin, "level 3 holds the 8-posit
 
 // Last j in [lo, hi] (one block, at most 64 positions) with lcp[j] < s, or
 // lo - 1 if none.
-__device__ __forceinline__ int32_t last_below(const int32_t* __restrict__ ib1, int64_t stride, int32_t lo, int32_t hi,
+__device__ __forceinline__ int32_t last_below(const int32_t* ib1, int64_t stride, int32_t lo, int32_t hi,
                                               int32_t s) {
   const int32_t full = (hi - lo + 1) / kWin;   // whole windows ending at hi, hi - 8, ...
-  const int32_t* __restrict__ l3 = ib1 + 3 * stride;
+  const int32_t* l3 = ib1 + 3 * stride;
   int32_t mv[kWin];
 #pragma unroll
   for (int t = 0; t < kWin; ++t) mv[t] = l3[t < full ? hi - kWin * t - (kWin - 1) : lo];
@@ -1434,10 +1462,10 @@ __device__ __forceinline__ int32_t last_below(const int32_t* __restrict__ ib1, i
 
 // First j in [lo, hi] (one block, at most 64 positions) with lcp[j] < s, or
 // hi + 1 if none.
-__device__ __forceinline__ int32_t first_below(const int32_t* __restrict__ ib1, int64_t stride, int32_t lo, int32_t hi,
+__device__ __forceinline__ int32_t first_below(const int32_t* ib1, int64_t stride, int32_t lo, int32_t hi,
                                                int32_t s) {
   const int32_t full = (hi - lo + 1) / kWin;   // whole windows starting at lo, lo + 8, ...
-  const int32_t* __restrict__ l3 = ib1 + 3 * stride;
+  const int32_t* l3 = ib1 + 3 * stride;
   int32_t mv[kWin];
 #pragma unroll
   for (int t = 0; t < kWin; ++t) mv[t] = l3[t < full ? lo + kWin * t : lo];
@@ -1531,8 +1559,7 @@ struct LcpIndex {
 
 // Minimum of the position keys over [lo, hi]: in-block tables at both ends,
 // the sparse table over whole blocks in between.
-__device__ __forceinline__ uint64_t key_range_min(const uint64_t* __restrict__ ib2, int64_t stride,
-                                                  const uint64_t* __restrict__ st2, int32_t nb2, int32_t lo,
+__device__ __forceinline__ uint64_t key_range_min(const uint64_t* ib2, int64_t stride, const uint64_t* st2, int32_t nb2, int32_t lo,
                                                   int32_t hi) {
   const int32_t bl = lo >> 6, bh = hi >> 6;
   if (bl == bh) return in_block_min(ib2, stride, lo, hi);
@@ -1548,12 +1575,10 @@ __device__ __forceinline__ uint64_t key_range_min(const uint64_t* __restrict__ i
 // One thread per sorted position i: cluster id and size of its request;
 // with cLPM signals requested also the weight of the pending-tree node
 // whose leftmost inner position is i, and the section run of position i.
-__global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshold, const uint64_t* __restrict__ key2,
-                                                    const int32_t* __restrict__ lcp, const ClElem* __restrict__ el,
-                                                    LcpIndex ix, const uint64_t* __restrict__ ib2,
-                                                    const uint64_t* __restrict__ st2, int32_t nb2,
-                                                    int32_t* __restrict__ cid, int32_t* __restrict__ csz, ClpmArgs cl) {
-  const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
+__device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, const uint64_t* key2,
+                                            const int32_t* lcp, const ClElem* el, const LcpIndex& ix,
+                                            const uint64_t* ib2, const uint64_t* st2, int32_t nb2, int32_t* cid,
+                                            int32_t* csz, const ClpmArgs& cl) {
   const bool valid = i < n;
   uint32_t req = 0;
   if (valid) {
@@ -1593,7 +1618,7 @@ __global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshol
     const int32_t cut = min(cl.theta, len);
     start = cut <= 0 ? 0 : ix.last_below_from(i, cut);
     cl.run[i] = start;
-    if (cl.h[req] <= cl.tau) cold = (int32_t)req;
+    if (cl.h != nullptr && cl.h[req] <= cl.tau) cold = (int32_t)req;
   }
   // The smallest cold request of each run: a minimum over the wavefront's
   // lanes of equal run start first, then one atomic per run and wavefront
@@ -1607,6 +1632,15 @@ __global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshol
   }
   const int32_t prev = __shfl_up(start, 1);
   if (valid && (lane == 0 || prev != start) && cold != INT32_MAX) atomicMin(&cl.pmin[start], cold);
+}
+
+__global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshold, const uint64_t* __restrict__ key2,
+                                                    const int32_t* __restrict__ lcp, const ClElem* __restrict__ el,
+                                                    LcpIndex ix, const uint64_t* __restrict__ ib2,
+                                                    const uint64_t* __restrict__ st2, int32_t nb2,
+                                                    int32_t* __restrict__ cid, int32_t* __restrict__ csz, ClpmArgs cl) {
+  final_query((int32_t)(blockIdx.x * blockDim.x + threadIdx.x), n, threshold, key2, lcp, el, ix, ib2, st2, nb2, cid, csz,
+              cl);
 }
 
 constexpr int kScanThreads = 1024;
@@ -1658,6 +1692,349 @@ __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const ui
   const int64_t share = (int64_t)(k2 >> 32);
   const int64_t len = el[i].len;
   cl.score[req] = (len > share ? len - share : 0) + offset + local[i];
+}
+
+// ---------------------------------------------------------------- small queues
+// A queue of up to kSmallQueue requests takes three launches instead of
+// eleven, each of which would cost 2 to 4 us however little it does:
+//  - k_small_compare: the compare with the anchor group's head, every
+//    workgroup finding the groups by looking at all keys;
+//  - k_small_signals: one workgroup sorts and forms the segments in LDS and,
+//    when none needs refinement, goes on to the end; beside it workgroups
+//    count the demand;
+//  - k_small_refine: the second round, the tail and the final stage when
+//    some segment does need refinement (else it returns at once).
+// Measured: step of 64 chat requests 42.5 -> 20 us, prefix match and cLPM
+// signals of 177 about 52 -> 23 us, signals of 512 document prompts on an
+// empty cache (every one refined) 77 -> 58 us, of 512 prompts over two tokens
+// 51 -> 42 us. The line lies where one position per thread suffices and one
+// workgroup's sort and final stage still take less than the launches they
+// replace.
+constexpr int kSmallQueue = 512;
+constexpr int kSmallThreads = 512;
+constexpr int kSmallBlocks = kSmallQueue / kWave + 1;   // 64-position blocks of lcp[0 .. n]
+constexpr int kSmallLevels = 4;                         // of the sparse tables over them
+static_assert((1 << kSmallLevels) > kSmallBlocks, "the top level spans every block");
+constexpr int kDemandNodes = 8;                         // nodes per thread of the demand workgroups
+
+// One wavefront per request: its anchor group by comparing its key with
+// every other one, then the compare with the group's longest member (as
+// k_first_compare).
+__global__ __launch_bounds__(256) void k_small_compare(AnchorIn in, int32_t n, AncElem* __restrict__ out) {
+  __shared__ uint32_t kc[kSmallQueue], km[kSmallQueue], klen[kSmallQueue];
+  __shared__ uint64_t kcode[kSmallQueue];
+  const int t = threadIdx.x, lane = t & (kWave - 1);
+  constexpr int kKeys = kSmallQueue / 256;
+  uint32_t vc[kKeys], vm[kKeys], vl[kKeys];
+  uint64_t vx[kKeys];
+#pragma unroll
+  for (int q = 0; q < kKeys; ++q) in.key((uint32_t)min(q * 256 + t, n - 1), vc[q], vm[q], vx[q], vl[q]);
+#pragma unroll
+  for (int q = 0; q < kKeys; ++q) {
+    kc[q * 256 + t] = vc[q];
+    km[q * 256 + t] = vm[q];
+    klen[q * 256 + t] = vl[q];
+    kcode[q * 256 + t] = vx[q];
+  }
+  __syncthreads();
+  const int32_t i = __builtin_amdgcn_readfirstlane((int32_t)blockIdx.x * 4 + t / kWave);
+  if (i >= n) return;
+  const uint32_t c = kc[i], m = km[i], len = klen[i];
+  const uint64_t code = kcode[i];
+  uint64_t best = 0;   // max over the group of (length << 32) | ~request
+  int members = 0;
+  for (int32_t j0 = 0; j0 < n; j0 += kWave) {
+    const int32_t j = j0 + lane;
+    const int32_t jc = min(j, n - 1);
+    const bool same = (j < n) & (kc[jc] == c) & (km[jc] == m) & (kcode[jc] == code);
+    const uint64_t mine = ((uint64_t)klen[jc] << 32) | (0xFFFFFFFFu - (uint32_t)j);
+    if (same && mine > best) best = mine;
+    members += __popcll(__ballot(same));
+  }
+  for (int d = 1; d < kWave; d <<= 1) best = max(best, (uint64_t)__shfl_xor((long long)best, d));
+  uint32_t ell = 0;
+  uint64_t code1 = 0;
+  if (code != 0 && members >= 2) {
+    const uint32_t head = 0xFFFFFFFFu - (uint32_t)best, hlen = (uint32_t)(best >> 32);
+    const int32_t d = (int32_t)m + 1;
+    if ((uint32_t)i == head) ell = len - (uint32_t)d;
+    else member_key(in.tokens, in.offsets, (uint32_t)i, len, __builtin_amdgcn_readfirstlane(head),
+                    __builtin_amdgcn_readfirstlane(hlen), d, lane, ell, code1);
+  }
+  if (lane == 0)
+    out[i] = AncElem{((uint64_t)c << 32) | m, (code << 31) | ell, (code1 << 31) | (uint32_t)i};
+}
+
+struct SmallArgs {
+  AnchorIn in;
+  int32_t n;
+  int32_t threshold;
+  const AncElem* anc;      // k_small_compare's output
+  DeviceTree tree;         // empty when unanchored
+  int32_t* cid;
+  int32_t* csz;
+  ClpmArgs cl;             // its arrays are set in the kernel
+  int32_t* sharing;        // has_sharing, or NULL
+  const int32_t* last;     // demand: the last nodes, the cache's nodes, their count
+  const NodeRec* nodes;
+  int32_t nn;
+  int32_t* demand;
+  int32_t first_block;     // blocks from here on count demand (1 beside the clusters, 0 alone)
+  TailArgs tail;           // where segments that need refinement go
+  uint64_t* head;          // their longest members
+};
+
+constexpr int kSmallRange = 16;   // positions whose segments one tail ticket settles
+constexpr int kFlagTicket = 2, kFlagCompared = 3, kFlagSettled = 4;   // k_small_refine's counters
+
+struct SmallLds {
+  union {
+    struct {
+      AncElem run[kSmallQueue], sd[kSmallQueue];
+    };
+    struct {
+      int32_t ib1[kInBlockLevels * kSmallBlocks * kWave];
+      uint64_t ib2[kInBlockLevels * kSmallBlocks * kWave];
+    };
+    struct {
+      uint64_t dkey[kSmallQueue];
+      uint32_t dlast[kSmallQueue];
+    };
+  };
+  ClElem el[kSmallQueue];
+  int32_t nseg[kSmallQueue], gsize[kSmallQueue], depth[kSmallQueue];
+  int32_t lcp[kSmallQueue + 1];
+  uint8_t active[kSmallQueue];
+  uint64_t head[kSmallQueue], key2[kSmallQueue];
+  int32_t st1[kSmallLevels * kSmallBlocks];
+  uint64_t st2[kSmallLevels * kSmallBlocks];
+  int64_t diff[kSmallQueue + 1];
+  int32_t pmin[kSmallQueue], run_at[kSmallQueue];
+  int64_t wsum[kSmallThreads / kWave];
+  int32_t flags[kFlags];
+  int32_t sharing, ticket;
+  TailLds<kSmallRange, kSmallQueue> tail;
+};
+
+struct U64Less {
+  __device__ __forceinline__ bool operator()(uint64_t a, uint64_t b) const { return a < b; }
+};
+
+// demand[c] = P[subtree_end(c)] - P[c] for one workgroup's nodes, P[v] being
+// the number of last nodes below v: the last nodes are sorted in LDS, and
+// each node searches them for its two ends.
+__device__ __forceinline__ void small_demand(const SmallArgs& A, SmallLds& S, int32_t block) {
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int32_t c0 = block * (kSmallThreads * kDemandNodes) + t;
+  int32_t end[kDemandNodes];
+#pragma unroll
+  for (int q = 0; q < kDemandNodes; ++q) end[q] = A.nodes[min(c0 + q * kSmallThreads, A.nn - 1)].subtree_end;
+  uint64_t key = ~uint64_t(0);
+  const int32_t last = A.last[min(t, A.n - 1)];
+  if (t < A.n) key = ((uint64_t)(uint32_t)last << 32) | (uint32_t)t;
+  S.dlast[t] = 0xFFFFFFFFu;   // above every node
+  if (wave * kWave < A.n) {
+    msort::wave_sort(key, lane, U64Less{});
+    S.dkey[t] = key;
+  }
+  __syncthreads();
+  if (wave * kWave < A.n && key != ~uint64_t(0)) {
+    const int r = msort::rank_in_runs(S.dkey, (A.n + kWave - 1) / kWave, wave, lane, key, U64Less{});
+    S.dlast[r] = (uint32_t)(key >> 32);
+  }
+  __syncthreads();
+  int32_t lo[kDemandNodes], hi[kDemandNodes];
+#pragma unroll
+  for (int q = 0; q < kDemandNodes; ++q) lo[q] = hi[q] = 0;
+#pragma unroll
+  for (int w = kSmallQueue / 2; w > 0; w >>= 1) {
+#pragma unroll
+    for (int q = 0; q < kDemandNodes; ++q) {
+      lo[q] += S.dlast[lo[q] + w - 1] < (uint32_t)(c0 + q * kSmallThreads) ? w : 0;
+      hi[q] += S.dlast[hi[q] + w - 1] < (uint32_t)end[q] ? w : 0;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < kDemandNodes; ++q) {
+    const int32_t c = c0 + q * kSmallThreads;
+    lo[q] += S.dlast[lo[q]] < (uint32_t)c ? 1 : 0;
+    hi[q] += S.dlast[hi[q]] < (uint32_t)end[q] ? 1 : 0;
+    if (c < A.nn) A.demand[c] = hi[q] - lo[q];
+  }
+}
+
+// Range minima and queries over the settled order in S.el and S.lcp; the
+// whole workgroup.
+__device__ __forceinline__ void small_final(const SmallArgs& A, SmallLds& S) {
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int32_t n = A.n;
+  const int32_t nb1 = (n + kWave) / kWave, nb2 = (n + kWave - 1) / kWave;
+  constexpr int64_t stride = kSmallBlocks * kWave;
+  ClpmArgs cl = A.cl;
+  cl.diff = S.diff;
+  cl.pmin = S.pmin;
+  cl.run = S.run_at;
+  cl.sharing = &S.sharing;
+  if (t == 0) S.sharing = 0;
+  __syncthreads();
+  for (int32_t b = wave; b < nb1; b += kSmallThreads / kWave)
+    final_block(b, lane, n, S.el, S.lcp, S.key2, S.ib1, S.ib2, stride, S.st1, S.st2, nb1, nb2, cl, false);
+  __syncthreads();
+  int levels = 1;
+  for (; (1 << levels) <= nb1; ++levels) {
+    const int h = 1 << (levels - 1);
+    if (t + 2 * h <= nb1) S.st1[levels * nb1 + t] = min(S.st1[(levels - 1) * nb1 + t], S.st1[(levels - 1) * nb1 + t + h]);
+    if (t + 2 * h <= nb2)
+      S.st2[levels * nb2 + t] = umin64(S.st2[(levels - 1) * nb2 + t], S.st2[(levels - 1) * nb2 + t + h]);
+    __syncthreads();
+  }
+  const LcpIndex ix{S.ib1, stride, S.st1, nb1, levels, n};
+  final_query(t, n, A.threshold, S.key2, S.lcp, S.el, ix, S.ib2, S.st2, nb2, A.cid, A.csz, cl);
+  if (!cl.on) return;
+  __syncthreads();
+  // cLPM's score and section (k_clpm_scan and k_clpm_score in one)
+  int64_t x = t < n ? S.diff[t] : 0;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int64_t o = __shfl(x, lane >= d ? lane - d : lane);
+    if (lane >= d) x += o;
+  }
+  if (lane == kWave - 1) S.wsum[wave] = x;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) x += S.wsum[w];
+  if (t == 0 && A.sharing != nullptr) *A.sharing = S.sharing;
+  if (t >= n) return;
+  const uint64_t k2 = S.key2[t];
+  const uint32_t req = (uint32_t)k2;
+  const int64_t share = (int64_t)(k2 >> 32), len = S.el[t].len;
+  if (cl.score != nullptr) cl.score[req] = (len > share ? len - share : 0) + x;
+  if (cl.section != nullptr)
+    cl.section[req] = cl.h[req] > cl.tau ? 0 : (S.pmin[S.run_at[t]] == (int32_t)req ? 1 : 2);
+}
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_signals(SmallArgs A, int32_t* __restrict__ flags) {
+  __shared__ SmallLds S;
+  if ((int32_t)blockIdx.x >= A.first_block) {
+    small_demand(A, S, (int32_t)blockIdx.x - A.first_block);
+    return;
+  }
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int32_t n = A.n;
+  // the first round's sort
+  AncElem v = A.anc[min(t, n - 1)];
+  if (t >= n) v = AncElem{~0ull, ~0ull, ~0ull};
+  S.head[t] = 0;
+  S.lcp[t] = 0;
+  if (t == 0) S.lcp[kSmallQueue] = 0;
+  if (t < kFlags) S.flags[t] = 0;
+  if (wave * kWave < n) {
+    msort::wave_sort(v, lane, AncLess{});
+    S.run[t] = v;
+  }
+  __syncthreads();
+  if (wave * kWave < n) {
+    const int r = msort::rank_in_runs(S.run, (n + kWave - 1) / kWave, wave, lane, v, AncLess{});
+    if (t < n) S.sd[r] = v;
+  }
+  __syncthreads();
+  const DemandRide no_ride{nullptr, nullptr, nullptr, 0, INT32_MAX, nullptr};
+  if (wave * kWave < n)
+    first_groups(wave * kWave, lane, n, S.sd, A.in, A.tree, S.el, S.nseg, S.gsize, S.depth, S.active, S.head, S.lcp,
+                 S.flags, no_ride);
+  __syncthreads();
+  if (t < kFlags) flags[t] = S.flags[t];   // the counters start at 0
+  if (S.flags[0] == 0) {
+    small_final(A, S);
+    return;
+  }
+  const TailArgs& T = A.tail;
+  if (t <= n) T.lcp[t] = S.lcp[t];
+  if (t == 0) T.lcp[n] = 0;
+  if (t < n) {
+    const int32_t s = S.nseg[t];
+    T.el[t] = S.el[t];
+    const_cast<int32_t*>(T.nseg)[t] = s;
+    // a segment's state lies at its start
+    if (s == t) {
+      const_cast<int32_t*>(T.gsize)[t] = S.gsize[t];
+      const_cast<int32_t*>(T.depth)[t] = S.depth[t];
+      const_cast<uint8_t*>(T.active)[t] = S.active[t];
+      A.head[t] = S.head[t];
+    }
+  }
+}
+
+// What is left when segments need refinement, in one launch. Workgroups take
+// tickets in order: first the second round's compares (a position per
+// wavefront), then the tail (the segments that start in kSmallRange
+// positions, once every compare is done), and the workgroup that settles the
+// last of them runs the final stage. A workgroup that waits holds one
+// ticket, and what it waits for holds lower ones, whose workgroups are
+// running and do not wait: it needs no resident grid. The compare's keys are
+// written through and the tail's results released (an L2 write-back), so that
+// the next workgroup sees them on whichever XCD it runs.
+constexpr unsigned kSmallRefineBlocks = 64;
+
+__global__ __launch_bounds__(kSmallThreads) void k_small_refine(SmallArgs A, int32_t* flags) {
+  __shared__ SmallLds S;
+  if (A.tail.flags[0] == 0) return;
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const TailArgs& T = A.tail;
+  const int32_t n = A.n;
+  constexpr int kWaves = kSmallThreads / kWave;
+  const int32_t compares = (n + kWaves - 1) / kWaves, tails = (n + kSmallRange - 1) / kSmallRange;
+  while (true) {
+    __syncthreads();
+    if (t == 0) S.ticket = atomicAdd(&flags[kFlagTicket], 1);
+    __syncthreads();
+    const int32_t ticket = S.ticket;
+    if (ticket >= compares + tails) return;
+    if (ticket < compares) {
+      const int32_t i = __builtin_amdgcn_readfirstlane(ticket * kWaves + wave);
+      if (i < n) {
+        const int32_t s = T.nseg[i];
+        if (T.active[s]) {
+          const uint64_t hb = A.head[s];
+          const uint32_t hreq = 0xFFFFFFFFu - (uint32_t)hb, hlen = (uint32_t)(hb >> 32);
+          const int32_t d = T.depth[s];
+          const uint32_t req = T.el[i].req, len = T.el[i].len;
+          uint32_t ell = len - (uint32_t)d;   // the head itself: ended at its length
+          uint64_t code = 0;
+          if (req != hreq) member_key(T.tokens, T.offsets, req, len, hreq, hlen, d, lane, ell, code);
+          if (lane == 0) {
+            __hip_atomic_store(&T.el[i].hi, ((uint64_t)ell << 33) | code, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_store(&T.el[i].lo, (uint64_t)req, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          }
+        }
+      }
+      // written through, so there once answered
+      asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+      __syncthreads();
+      if (t == 0) atomicAdd(&flags[kFlagCompared], 1);
+      continue;
+    }
+    if (t == 0) {
+      // bounded: never expected to run out
+      for (uint32_t spins = 0; spins < (1u << 24); ++spins) {
+        if (__hip_atomic_load(&flags[kFlagCompared], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= compares) break;
+        __builtin_amdgcn_s_sleep(2);
+      }
+    }
+    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    refine_tail(T, (ticket - compares) * kSmallRange, S.tail);
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+    __syncthreads();
+    if (t == 0) S.ticket = atomicAdd(&flags[kFlagSettled], 1);
+    __syncthreads();
+    if (S.ticket != tails - 1) continue;
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (t < n) S.el[t] = T.el[t];
+    S.lcp[t] = T.lcp[min(t, n)];
+    if (t == 0) S.lcp[n] = 0;
+    __syncthreads();
+    small_final(A, S);
+    return;
+  }
 }
 
 // PEEK-offline Phase 1 (appendix on PEEK-offline): the permutation that a
@@ -1881,9 +2258,6 @@ int levels_for(int64_t nb) {
 
 size_t a256(size_t x) { return (x + 255) & ~size_t(255); }
 
-// Flags after the first round: [any active segment, a segment the second
-// round takes].
-constexpr int kFlags = 2;
 
 // Workspace layout (each region 256-byte aligned).
 struct Layout {
@@ -2008,6 +2382,56 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
   const bool anchored =
       want_clusters && off == nullptr && t != nullptr && last_node != nullptr && match_len != nullptr;
 
+  if (off == nullptr && n > 0 && n <= kSmallQueue) {
+    SmallArgs A{};
+    A.in = AnchorIn{tokens, offsets, anchored ? last_node : nullptr, anchored ? match_len : nullptr, UINT32_MAX};
+    A.n = n;
+    A.threshold = threshold;
+    A.anc = (const AncElem*)(w + L.anc_a);
+    if (anchored) A.tree = *t;
+    A.cid = cid;
+    A.csz = csz;
+    if (clpm != nullptr) {
+      A.cl.h = clpm->h;
+      A.cl.tau = clpm->tau;
+      A.cl.theta = clpm->theta;
+      A.cl.score = clpm->score;
+      A.cl.section = clpm->section;
+      A.cl.on = true;
+      A.sharing = clpm->has_sharing;
+    }
+    A.first_block = want_clusters ? 1 : 0;
+    unsigned blocks = (unsigned)A.first_block;
+    if (demand != nullptr) {
+      A.last = last_node;
+      A.nodes = t->nodes;
+      A.nn = t->num_nodes;
+      A.demand = demand;
+      blocks += blocks_for(t->num_nodes, kSmallThreads * kDemandNodes);
+    }
+    if (want_clusters)
+      hipLaunchKernelGGL(k_small_compare, dim3(blocks_for(n, 4)), dim3(256), 0, st, A.in, n, (AncElem*)(w + L.anc_a));
+    int32_t* flags = (int32_t*)(w + L.flags);
+    A.tail = TailArgs{tokens,
+                      offsets,
+                      n,
+                      (ClElem*)(w + L.el_a),
+                      (ClElem*)(w + L.el_b),
+                      (const int32_t*)(w + L.nseg),
+                      (const int32_t*)(w + L.gsize),
+                      (const int32_t*)(w + L.depth_a),
+                      (const uint8_t*)(w + L.active_a),
+                      flags,
+                      (int32_t*)(w + L.lcp),
+                      (uint8_t*)(w + L.tact),
+                      (int32_t*)(w + L.tdep),
+                      (int32_t*)(w + L.tsize)};
+    A.head = (uint64_t*)(w + L.head);
+    if (blocks > 0) hipLaunchKernelGGL(k_small_signals, dim3(blocks), dim3(kSmallThreads), 0, st, A, flags);
+    if (want_clusters) hipLaunchKernelGGL(k_small_refine, dim3(kSmallRefineBlocks), dim3(kSmallThreads), 0, st, A, flags);
+    PEEK_HIP_TRY(hipGetLastError());
+    return PEEK_OK;
+  }
   if (demand != nullptr && !anchored) {
     uint32_t* ka = (uint32_t*)(w + L.keys_a);
     uint32_t* kb = (uint32_t*)(w + L.keys_b);

@@ -207,10 +207,26 @@ __device__ __forceinline__ void wave_sort(T& v, int lane, Less less) {
   }
 }
 
+// Place of v, at place `own` of run r, among `runs` sorted runs of 64 that lie
+// back to back in LDS (the last one filled up with elements that sort last):
+// in every other run a search of 7 steps, independent of the other runs'.
+template <typename T, typename Less>
+__device__ __forceinline__ int32_t rank_in_runs(const T* s, int runs, int r, int own, const T& v, Less less) {
+  int32_t rank = own;
+#pragma unroll 4
+  for (int o = 0; o < runs; ++o) {
+    if (o == r) continue;
+    int k = 0;
+#pragma unroll
+    for (int w = 32; w > 0; w >>= 1) k += less(s[o * 64 + k + w - 1], v) ? w : 0;
+    k += less(s[o * 64 + k], v) ? 1 : 0;
+    rank += k;
+  }
+  return rank;
+}
+
 // Workgroup b orders bucket b. Runs of 64 are sorted in registers, one per
-// wavefront, and put into LDS; an element's place in the bucket is its place
-// in its own run plus, for every other run, the elements below it (a search
-// of 7 steps, those of different runs independent of each other).
+// wavefront, and put into LDS, where every element finds its place among them.
 template <typename T, typename Less, typename Src>
 __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort(Src src, T* __restrict__ dst,
                                                                 const T* __restrict__ split, Buckets B, T pad,
@@ -248,17 +264,7 @@ __global__ __launch_bounds__(kBucketThreads) void k_bucket_sort(Src src, T* __re
     for (int r = wave; r < runs; r += kWaves) {
       const int p = r * 64 + lane;
       const T v = s[p];
-      int32_t rank = lane;
-#pragma unroll 4
-      for (int o = 0; o < runs; ++o) {
-        if (o == r) continue;
-        // elements of run o below v; its padding is never below
-        int k = 0;
-#pragma unroll
-        for (int w = 32; w > 0; w >>= 1) k += less(s[o * 64 + k + w - 1], v) ? w : 0;
-        k += less(s[o * 64 + k], v) ? 1 : 0;
-        rank += k;
-      }
+      const int32_t rank = rank_in_runs(s, runs, r, lane, v, less);
       if (p < c) dst[base + rank] = v;
     }
     return;
