@@ -376,7 +376,7 @@ __device__ __forceinline__ int32_t lca_depth(const DeviceTree& t, int32_t c1, in
 //  - k_first_clear empties the table (and clears the lcp array, the round
 //    flags and the has_sharing output);
 //  - k_first_insert puts every request's key into the table. A workgroup
-//    first groups its own 1024 requests in an LDS table, so a group of
+//    first groups its own requests in an LDS table, so a group of
 //    thousands touches the global table once per workgroup, not once per
 //    member (accesses to one global word serialize, atomic or not). Then
 //    each local group's representative inserts it globally: a slot holds
@@ -476,10 +476,19 @@ __global__ void k_first_clear(HeadTable T, int32_t n, int32_t* __restrict__ lcp,
   if (i == 0 && sharing != nullptr) *sharing = 0;
 }
 
-constexpr int kInsThreads = 1024;
-constexpr int kInsSlots = 2 * kInsThreads;   // the workgroup's LDS table
+// Requests per workgroup. The keys' next tokens lie in as many places as
+// there are requests, and one CU gets through its 1024 slowly: smaller
+// workgroups spread them (us with 1024 / 512 / 256 / 128: 4096 document
+// prompts 12.0 / 10.8 / 10.2 / 10.3, 16,384 prompts of their own 23.0 / 18.1 /
+// 16.3 / 16.1, 20,000 mixed 12.6 / 12.7 / 10.2 / 11.3). At 65,536 requests
+// there are enough of them either way, and the more workgroups the more of
+// them meet at one group's word (16.5 / 15.9 / 18.6 / 29.3).
+constexpr int kInsFew = 256, kInsMany = 512;
+constexpr int32_t kInsFewMax = 32768;   // requests
 
+template <int kInsThreads>
 __global__ __launch_bounds__(kInsThreads) void k_first_insert(AnchorIn in, HeadTable T, int32_t n) {
+  constexpr int kInsSlots = 2 * kInsThreads;   // the workgroup's LDS table
   __shared__ uint32_t lrep[kInsSlots];            // 0: empty; else the local representative + 1
   __shared__ unsigned long long lbest[kInsSlots];
   __shared__ uint32_t lcnt[kInsSlots];
@@ -2497,7 +2506,10 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
   uint64_t* head = (uint64_t*)(w + L.head);
   hipLaunchKernelGGL(k_first_clear, dim3(blocks_for(clear_span)), dim3(256), 0, st, T, n, lcp, head, flags, n_flags,
                      cl.on ? cl.sharing : nullptr, keyed, n_keyed);
-  hipLaunchKernelGGL(k_first_insert, dim3(blocks_for(n, kInsThreads)), dim3(kInsThreads), 0, st, ain, T, n);
+  if (n <= kInsFewMax)
+    hipLaunchKernelGGL(k_first_insert<kInsFew>, dim3(blocks_for(n, kInsFew)), dim3(kInsFew), 0, st, ain, T, n);
+  else
+    hipLaunchKernelGGL(k_first_insert<kInsMany>, dim3(blocks_for(n, kInsMany)), dim3(kInsMany), 0, st, ain, T, n);
   AncElem* anc_a = (AncElem*)(w + L.anc_a);
   AncElem* anc_b = (AncElem*)(w + L.anc_b);
   hipLaunchKernelGGL(k_first_compare, dim3(blocks_for(n, 4)), dim3(256), 0, st, ain, T, n, anc_a);
