@@ -1494,37 +1494,187 @@ __device__ __forceinline__ int32_t first_below(const int32_t* ib1, int64_t strid
   return ans;
 }
 
-// Range queries over lcp[0..n] from the in-block tables and the sparse
-// table over 64-position blocks.
+// Searches over the 64-position blocks: the last block at or before pl whose
+// lcp minimum is below sL and the first at or after pr whose minimum is below
+// sR (each only if asked for; it exists then, as lcp[0] = lcp[n] = 0 < s), and
+// the smallest position key of blocks x .. y.
+//
+// From the sparse tables in memory (or in LDS), by binary lifting; both
+// searches advance in the same steps. Indices are clamped so that the side
+// that is not asked for still loads inside the tables.
+struct TableBlocks {
+  const int32_t* st1;
+  const uint64_t* st2;
+  int32_t nb1, nb2;
+  int levels;
+
+  __device__ __forceinline__ void pair(bool needL, int32_t& pl, int32_t sL, bool needR, int32_t& pr, int32_t sR) const {
+    for (int k = levels - 1; k >= 0; --k) {
+      const int32_t w = 1 << k;
+      const int32_t vl = st1[(int64_t)k * nb1 + max(pl - w + 1, 0)];
+      const int32_t vr = st1[(int64_t)k * nb1 + max(min(pr, nb1 - 1), 0)];
+      if (needL && pl - w + 1 >= 0 && vl >= sL) pl -= w;
+      if (needR && pr + w <= nb1 && vr >= sR) pr += w;
+    }
+    pl = max(pl, 0);
+    pr = max(min(pr, nb1 - 1), 0);
+  }
+  __device__ __forceinline__ uint64_t key_min(int32_t x, int32_t y) const {
+    const int k = 31 - __clz(y - x + 1);
+    return umin64(st2[(int64_t)k * nb2 + x], st2[(int64_t)k * nb2 + y - (1 << k) + 1]);
+  }
+};
+
+// From the block minima alone: every workgroup loads them (12 KB at 65,536
+// requests) into LDS, with the minima of every kBlockGroup blocks and sparse
+// tables over those. No launch builds tables then (5 us at 4096 requests, 6.7
+// at 65,536), and a search that leaves its block waits on LDS instead of on
+// up to eleven loads one after another; loading costs the query kernel 3 to 4
+// us, which the cLPM queries win back. Signals of 8192 agentic requests 93 ->
+// 85 us (with the insert kernel's 2.6), offline order of 5000 84 -> 79 us.
+// Beyond kLdsBlocks blocks every workgroup would load too much, and the
+// tables are built once.
+constexpr int kLdsBlocks = 1040;
+constexpr int kBlockGroup = 16;
+constexpr int kLdsGroups = kLdsBlocks / kBlockGroup;   // 65
+constexpr int kLdsLevels = 7;
+static_assert((1 << kLdsLevels) > kLdsGroups, "the top level spans every group");
+
+struct BlockLds {
+  int32_t a1[kLdsBlocks];
+  uint64_t a2[kLdsBlocks];
+  int32_t b1[kLdsLevels][kLdsGroups];
+  uint64_t b2[kLdsLevels][kLdsGroups];
+};
+
+// The whole workgroup; what lies past the blocks never is a minimum.
+__device__ __forceinline__ void load_blocks(BlockLds& S, const int32_t* __restrict__ st1,
+                                            const uint64_t* __restrict__ st2, int32_t nb1, int32_t nb2) {
+  const int t = threadIdx.x, nt = blockDim.x;
+  const int32_t ng = (nb1 + kBlockGroup - 1) / kBlockGroup;   // nb2 <= nb1
+  for (int32_t b = t; b < ng * kBlockGroup; b += nt) {
+    S.a1[b] = b < nb1 ? st1[b] : INT32_MAX;
+    S.a2[b] = b < nb2 ? st2[b] : ~0ull;
+  }
+  __syncthreads();
+  if (t < kWave) {   // one wavefront: its LDS accesses keep their order
+    for (int32_t g = t; g < ng; g += kWave) {
+      int32_t m1 = INT32_MAX;
+      uint64_t m2 = ~0ull;
+#pragma unroll
+      for (int q = 0; q < kBlockGroup; ++q) {
+        // a lane's own order spreads the banks
+        const int32_t b = g * kBlockGroup + ((q + t) & (kBlockGroup - 1));
+        m1 = min(m1, S.a1[b]);
+        m2 = umin64(m2, S.a2[b]);
+      }
+      S.b1[0][g] = m1;
+      S.b2[0][g] = m2;
+    }
+    for (int k = 1; (1 << k) <= ng; ++k) {
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      __builtin_amdgcn_wave_barrier();
+      const int32_t h = 1 << (k - 1);
+      for (int32_t g = t; g + 2 * h <= ng; g += kWave) {
+        S.b1[k][g] = min(S.b1[k - 1][g], S.b1[k - 1][g + h]);
+        S.b2[k][g] = umin64(S.b2[k - 1][g], S.b2[k - 1][g + h]);
+      }
+    }
+  }
+  __syncthreads();
+}
+
+struct LdsIndexBlocks {
+  const BlockLds* S;
+  int32_t nb1;
+
+  // the last block of group g at or before hi below s, or -1
+  __device__ __forceinline__ int32_t last_in_group(int32_t g, int32_t hi, int32_t s) const {
+    int32_t at = -1;
+#pragma unroll
+    for (int q = 0; q < kBlockGroup; ++q) {
+      const int32_t b = g * kBlockGroup + q;
+      if (b <= hi && S->a1[b] < s) at = b;
+    }
+    return at;
+  }
+  // the first block of group g at or after lo below s, or -1
+  __device__ __forceinline__ int32_t first_in_group(int32_t g, int32_t lo, int32_t s) const {
+    int32_t at = -1;
+#pragma unroll
+    for (int q = kBlockGroup - 1; q >= 0; --q) {
+      const int32_t b = g * kBlockGroup + q;
+      if (b >= lo && S->a1[b] < s) at = b;
+    }
+    return at;
+  }
+  __device__ __forceinline__ void pair(bool needL, int32_t& pl, int32_t sL, bool needR, int32_t& pr, int32_t sR) const {
+    const int32_t ng = (nb1 + kBlockGroup - 1) / kBlockGroup;
+    if (needL) {
+      int32_t g = pl / kBlockGroup;   // pl >= 0: block 0 answers every search
+      int32_t at = last_in_group(g, pl, sL);
+      if (at < 0) {
+        --g;
+        for (int k = kLdsLevels - 1; k >= 0; --k) {
+          const int32_t w = 1 << k;
+          if (g - w + 1 >= 0 && S->b1[k][max(g - w + 1, 0)] >= sL) g -= w;
+        }
+        g = max(g, 0);
+        at = last_in_group(g, g * kBlockGroup + kBlockGroup - 1, sL);
+      }
+      pl = max(at, 0);
+    }
+    if (needR) {
+      int32_t g = min(pr, nb1 - 1) / kBlockGroup;   // pr <= nb1 - 1: the last block answers
+      int32_t at = first_in_group(g, pr, sR);
+      if (at < 0) {
+        ++g;
+        for (int k = kLdsLevels - 1; k >= 0; --k) {
+          const int32_t w = 1 << k;
+          if (g + w <= ng && S->b1[k][min(g, kLdsGroups - 1)] >= sR) g += w;
+        }
+        g = min(g, ng - 1);
+        at = first_in_group(g, g * kBlockGroup, sR);
+      }
+      pr = at < 0 ? nb1 - 1 : at;
+    }
+    pl = max(pl, 0);
+    pr = max(min(pr, nb1 - 1), 0);
+  }
+  __device__ __forceinline__ uint64_t key_min(int32_t x, int32_t y) const {
+    const int32_t gx = x / kBlockGroup, gy = y / kBlockGroup;
+    uint64_t m = ~0ull;
+#pragma unroll
+    for (int q = 0; q < kBlockGroup; ++q) {
+      const int32_t bx = gx * kBlockGroup + q, by = gy * kBlockGroup + q;
+      const uint64_t vx = S->a2[bx], vy = S->a2[by];
+      m = umin64(m, bx >= x && bx <= y ? vx : ~0ull);
+      m = umin64(m, by >= x && by <= y ? vy : ~0ull);
+    }
+    if (gy - gx >= 2) {
+      const int k = 31 - __clz(gy - gx - 1);
+      m = umin64(m, umin64(S->b2[k][gx + 1], S->b2[k][gy - (1 << k)]));
+    }
+    return m;
+  }
+};
+
+// Range queries over lcp[0..n] from the in-block tables and a search over
+// the 64-position blocks.
+template <typename Blocks>
 struct LcpIndex {
   const int32_t* ib1;
+  const uint64_t* ib2;
   int64_t stride;
-  const int32_t* st1;
-  int32_t nb1;
-  int levels;
   int32_t n;
-
-  // Last j <= i with lcp[j] < s, for s >= 1 (lcp[0] = 0, so one exists).
-  __device__ __forceinline__ int32_t last_below_from(int32_t i, int32_t s) const {
-    const int32_t bi = i >> 6;
-    int32_t L = last_below(ib1, stride, bi << 6, i, s);
-    if (L < (bi << 6)) {
-      int32_t pos = bi - 1;   // the last block <= pos whose minimum is < s
-      for (int k = levels - 1; k >= 0; --k) {
-        const int32_t w = 1 << k;
-        if (pos - w + 1 >= 0 && st1[(int64_t)k * nb1 + pos - w + 1] >= s) pos -= w;
-      }
-      L = last_below(ib1, stride, pos << 6, min((pos << 6) + 63, n), s);
-    }
-    return L;
-  }
+  Blocks blocks;
 
   // last_below_from(iL, sL) and first_below_from(iR, sR) (iL < n, iR <= n)
   // computed together: the two chains of dependent loads (in-block rounds,
-  // then the lifting over the sparse table, then the in-block rounds of the
-  // block found) advance in the same steps, so the pair waits about as long
-  // as one of them. Indices are clamped so that the side that needs no
-  // lifting still loads inside the tables; its results are not used.
+  // then the search over the blocks, then the in-block rounds of the block
+  // found) advance in the same steps, so the pair waits about as long as one
+  // of them. The side that needs no other block still loads inside the
+  // tables; its results are not used.
   __device__ __forceinline__ void pair_from(int32_t iL, int32_t sL, int32_t iR, int32_t sR, int32_t& L,
                                             int32_t& R) const {
     const int32_t bL = iL >> 6, bR = iR >> 6;
@@ -1533,20 +1683,25 @@ struct LcpIndex {
     R = first_below(ib1, stride, iR, bendR, sR);
     const bool needL = L < (bL << 6), needR = R > bendR;
     if (needL || needR) {
-      int32_t pl = bL - 1, pr = bR + 1;   // as in the single searches
-      for (int k = levels - 1; k >= 0; --k) {
-        const int32_t w = 1 << k;
-        const int32_t vl = st1[(int64_t)k * nb1 + max(pl - w + 1, 0)];
-        const int32_t vr = st1[(int64_t)k * nb1 + max(min(pr, nb1 - 1), 0)];
-        if (needL && pl - w + 1 >= 0 && vl >= sL) pl -= w;
-        if (needR && pr + w <= nb1 && vr >= sR) pr += w;
-      }
-      const int32_t ql = max(pl, 0), qr = max(min(pr, nb1 - 1), 0);
-      const int32_t l2 = last_below(ib1, stride, ql << 6, min((ql << 6) + 63, n), sL);
-      const int32_t r2 = first_below(ib1, stride, qr << 6, min((qr << 6) + 63, n), sR);
+      int32_t pl = bL - 1, pr = bR + 1;
+      blocks.pair(needL, pl, sL, needR, pr, sR);
+      const int32_t l2 = last_below(ib1, stride, pl << 6, min((pl << 6) + 63, n), sL);
+      const int32_t r2 = first_below(ib1, stride, pr << 6, min((pr << 6) + 63, n), sR);
       if (needL) L = l2;
       if (needR) R = r2;
     }
+  }
+
+  // Last j <= i with lcp[j] < s, for s >= 1 (lcp[0] = 0, so one exists).
+  __device__ __forceinline__ int32_t last_below_from(int32_t i, int32_t s) const {
+    const int32_t bi = i >> 6;
+    int32_t L = last_below(ib1, stride, bi << 6, i, s);
+    if (L < (bi << 6)) {
+      int32_t pl = bi - 1, pr = bi;
+      blocks.pair(true, pl, s, false, pr, s);
+      L = last_below(ib1, stride, pl << 6, min((pl << 6) + 63, n), s);
+    }
+    return L;
   }
 
   // First j >= i (i <= n) with lcp[j] < s, for s >= 1 (lcp[n] = 0).
@@ -1555,43 +1710,34 @@ struct LcpIndex {
     const int32_t bend = min((bi << 6) + 63, n);
     int32_t R = first_below(ib1, stride, i, bend, s);
     if (R > bend) {
-      int32_t pos = bi + 1;   // the first block >= pos whose minimum is < s
-      for (int k = levels - 1; k >= 0; --k) {
-        const int32_t w = 1 << k;
-        if (pos + w <= nb1 && st1[(int64_t)k * nb1 + pos] >= s) pos += w;
-      }
-      R = first_below(ib1, stride, pos << 6, min((pos << 6) + 63, n), s);
+      int32_t pl = bi, pr = bi + 1;
+      blocks.pair(false, pl, s, true, pr, s);
+      R = first_below(ib1, stride, pr << 6, min((pr << 6) + 63, n), s);
     }
     return R;
   }
-};
 
-// Minimum of the position keys over [lo, hi]: in-block tables at both ends,
-// the sparse table over whole blocks in between.
-__device__ __forceinline__ uint64_t key_range_min(const uint64_t* ib2, int64_t stride, const uint64_t* st2, int32_t nb2, int32_t lo,
-                                                  int32_t hi) {
-  const int32_t bl = lo >> 6, bh = hi >> 6;
-  if (bl == bh) return in_block_min(ib2, stride, lo, hi);
-  uint64_t m = umin64(in_block_min(ib2, stride, lo, (bl << 6) + 63), in_block_min(ib2, stride, bh << 6, hi));
-  if (bh - bl >= 2) {
-    const int32_t x = bl + 1, y = bh - 1;
-    const int k = 31 - __clz(y - x + 1);
-    m = umin64(m, umin64(st2[(int64_t)k * nb2 + x], st2[(int64_t)k * nb2 + y - (1 << k) + 1]));
+  // Minimum of the position keys over [lo, hi]: in-block tables at both
+  // ends, the blocks in between.
+  __device__ __forceinline__ uint64_t key_min(int32_t lo, int32_t hi) const {
+    const int32_t bl = lo >> 6, bh = hi >> 6;
+    if (bl == bh) return in_block_min(ib2, stride, lo, hi);
+    const uint64_t m = umin64(in_block_min(ib2, stride, lo, (bl << 6) + 63), in_block_min(ib2, stride, bh << 6, hi));
+    return bh - bl >= 2 ? umin64(m, blocks.key_min(bl + 1, bh - 1)) : m;
   }
-  return m;
-}
+};
 
 // One thread per sorted position i: cluster id and size of its request;
 // with cLPM signals requested also the weight of the pending-tree node
 // whose leftmost inner position is i, and the section run of position i.
-__device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, const uint64_t* key2,
-                                            const int32_t* lcp, const ClElem* el, const LcpIndex& ix,
-                                            const uint64_t* ib2, const uint64_t* st2, int32_t nb2, int32_t* cid,
+// `own` is key2[i], `lcp_i` lcp[i].
+template <typename Ix>
+__device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, uint64_t own, int32_t lcp_i,
+                                            const int32_t* lcp, const ClElem* el, const Ix& ix, int32_t* cid,
                                             int32_t* csz, const ClpmArgs& cl) {
   const bool valid = i < n;
   uint32_t req = 0;
   if (valid) {
-    const uint64_t own = key2[i];
     const int32_t s = (int32_t)(own >> 32);
     req = (uint32_t)own;
     if (s < threshold) {
@@ -1602,7 +1748,7 @@ __device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t thresh
       int32_t L, R;
       ix.pair_from(i, s, i + 1, s, L, R);
       // id: minimum of (share, request) over [L, R)
-      const uint64_t m = key_range_min(ib2, ix.stride, st2, nb2, L, R - 1);
+      const uint64_t m = ix.key_min(L, R - 1);
       cid[req] = (int32_t)(uint32_t)m;
       csz[req] = R - L;
     }
@@ -1612,7 +1758,7 @@ __device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t thresh
   if (valid) {
     // the node of depth D = lcp[i] > 0 is counted once, at its leftmost
     // inner position: the previous position with lcp <= D must have lcp < D
-    const int32_t D = i >= 1 ? lcp[i] : 0;
+    const int32_t D = i >= 1 ? lcp_i : 0;
     if (D > 0) {
       int32_t L, R;   // R is only used when L is the node's leftmost position
       ix.pair_from(i - 1, D + 1, i + 1, D, L, R);
@@ -1643,13 +1789,39 @@ __device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t thresh
   if (valid && (lane == 0 || prev != start) && cold != INT32_MAX) atomicMin(&cl.pmin[start], cold);
 }
 
+// What the searches read, whichever way they go over the blocks.
+struct IndexArgs {
+  const int32_t* ib1;
+  const uint64_t* ib2;
+  int64_t stride;
+  const int32_t* st1;
+  const uint64_t* st2;
+  int32_t nb1, nb2;
+  int levels;
+  int32_t n;
+  __device__ __forceinline__ LcpIndex<TableBlocks> tables() const {
+    return LcpIndex<TableBlocks>{ib1, ib2, stride, n, TableBlocks{st1, st2, nb1, nb2, levels}};
+  }
+  __device__ __forceinline__ LcpIndex<LdsIndexBlocks> lds(BlockLds& S) const {
+    load_blocks(S, st1, st2, nb1, nb2);
+    return LcpIndex<LdsIndexBlocks>{ib1, ib2, stride, n, LdsIndexBlocks{&S, nb1}};
+  }
+};
+
+template <bool kLds>
 __global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshold, const uint64_t* __restrict__ key2,
                                                     const int32_t* __restrict__ lcp, const ClElem* __restrict__ el,
-                                                    LcpIndex ix, const uint64_t* __restrict__ ib2,
-                                                    const uint64_t* __restrict__ st2, int32_t nb2,
-                                                    int32_t* __restrict__ cid, int32_t* __restrict__ csz, ClpmArgs cl) {
-  final_query((int32_t)(blockIdx.x * blockDim.x + threadIdx.x), n, threshold, key2, lcp, el, ix, ib2, st2, nb2, cid, csz,
-              cl);
+                                                    IndexArgs ix, int32_t* __restrict__ cid, int32_t* __restrict__ csz,
+                                                    ClpmArgs cl) {
+  const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
+  const uint64_t own = key2[min(i, n - 1)];
+  const int32_t lcp_i = lcp[min(i, n)];
+  if constexpr (kLds) {
+    __shared__ BlockLds S;
+    final_query(i, n, threshold, own, lcp_i, lcp, el, ix.lds(S), cid, csz, cl);
+  } else {
+    final_query(i, n, threshold, own, lcp_i, lcp, el, ix.tables(), cid, csz, cl);
+  }
 }
 
 constexpr int kScanThreads = 1024;
@@ -1897,8 +2069,8 @@ __device__ __forceinline__ void small_final(const SmallArgs& A, SmallLds& S) {
       S.st2[levels * nb2 + t] = umin64(S.st2[(levels - 1) * nb2 + t], S.st2[(levels - 1) * nb2 + t + h]);
     __syncthreads();
   }
-  const LcpIndex ix{S.ib1, stride, S.st1, nb1, levels, n};
-  final_query(t, n, A.threshold, S.key2, S.lcp, S.el, ix, S.ib2, S.st2, nb2, A.cid, A.csz, cl);
+  const LcpIndex<TableBlocks> ix{S.ib1, S.ib2, stride, n, TableBlocks{S.st1, S.st2, nb1, nb2, levels}};
+  final_query(t, n, A.threshold, S.key2[t], S.lcp[t], S.lcp, S.el, ix, A.cid, A.csz, cl);
   if (!cl.on) return;
   __syncthreads();
   // cLPM's score and section (k_clpm_scan and k_clpm_score in one)
@@ -2079,10 +2251,7 @@ struct OffArgs {
   int32_t n;
   const int32_t* lcp;         // [n + 1], capped at D, lcp[0] = lcp[n] = 0
   const ClElem* el;           // the order
-  LcpIndex ix;
-  const uint64_t* ib2;        // range minimum of the requests (keys are the requests)
-  const uint64_t* st2;
-  int32_t nb2;
+  IndexArgs ix;               // range minima of lcp and of the requests (keys are the requests)
   int32_t* nparent;           // [n] per boundary: the parent node of the node it names, -1 otherwise
   int64_t* start;             // [n] per boundary: offset of its node inside the parent (0 at the top)
   int32_t* rnode;             // [n] per position: the node of its request's piece
@@ -2090,18 +2259,21 @@ struct OffArgs {
 };
 
 // The node (first separator) of the interval of depth lcp[i] around inner boundary i.
-__device__ __forceinline__ int32_t off_node_of(const OffArgs& a, int32_t i) {
+template <typename Ix>
+__device__ __forceinline__ int32_t off_node_of(const OffArgs& a, const Ix& ix, int32_t i) {
   const int32_t d = a.lcp[i];
-  const int32_t L = d == 0 ? 0 : a.ix.last_below_from(i - 1, d);
-  return a.ix.first_below_from(L + 1, d + 1);
+  const int32_t L = d == 0 ? 0 : ix.last_below_from(i - 1, d);
+  return ix.first_below_from(L + 1, d + 1);
 }
 
 // Piece j of the sort: j < n is the request at position j; n < j < 2n is
 // the node named by boundary j - n (padding unless j - n is a first
 // separator and not the top interval). Also records each node's parent and
 // each request's node.
+template <typename Ix>
 struct OffSource {
-  OffArgs a;
+  const OffArgs& a;
+  const Ix ix;
   __device__ __forceinline__ OffElem operator()(size_t j) const {
     // sorts last, and differs from every other one
     const OffElem pad{INT32_MAX, INT32_MAX, (int32_t)min(j, (size_t)INT32_MAX), 0};
@@ -2110,7 +2282,7 @@ struct OffSource {
       const int32_t i = (int32_t)j;
       const int32_t bl = i >= 1 ? a.lcp[i] : -1, br = i + 1 <= n - 1 ? a.lcp[i + 1] : -1;
       const int32_t b = bl >= br ? i : i + 1;   // the deeper of its boundaries
-      const int32_t node = off_node_of(a, b);
+      const int32_t node = off_node_of(a, ix, b);
       a.rnode[i] = node;
       const bool ends = (int32_t)a.el[i].len == a.lcp[b];
       return OffElem{node, ends ? 0 : n, (int32_t)a.el[i].req, -(i + 1)};
@@ -2125,9 +2297,9 @@ struct OffSource {
     const int32_t d = a.lcp[i];
     // the interval's two ends, searched together (R is wasted on padding)
     int32_t L = 0, R = n;
-    if (d != 0) a.ix.pair_from(i - 1, d, i + 1, d, L, R);
+    if (d != 0) ix.pair_from(i - 1, d, i + 1, d, L, R);
     a.start[i] = 0;
-    if (a.ix.first_below_from(L + 1, d + 1) != i) {
+    if (ix.first_below_from(L + 1, d + 1) != i) {
       a.nparent[i] = -1;
       return pad;
     }
@@ -2136,9 +2308,9 @@ struct OffSource {
       a.nparent[i] = -1;
       return pad;
     }
-    const int32_t parent = off_node_of(a, lL >= lR ? L : R);
+    const int32_t parent = off_node_of(a, ix, lL >= lR ? L : R);
     a.nparent[i] = parent;
-    const int32_t first = (int32_t)(uint32_t)key_range_min(a.ib2, a.ix.stride, a.st2, a.nb2, L, R - 1);
+    const int32_t first = (int32_t)(uint32_t)ix.key_min(L, R - 1);
     return OffElem{parent, n + 1 - (R - L), first, i};
   }
 };
@@ -2147,9 +2319,17 @@ struct OffSource {
 // the sort's tile pass (two per thread, each a chain of dependent range
 // searches) made that pass the longest of the sort; on their own they run
 // one chain per thread (offline order 4-6 us faster on the workload queues).
-__global__ __launch_bounds__(256) void k_off_make(OffSource src, OffElem* __restrict__ out, int64_t np) {
+template <bool kLds>
+__global__ __launch_bounds__(256) void k_off_make(OffArgs a, OffElem* __restrict__ out, int64_t np) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (j < np) out[j] = src((size_t)j);
+  if constexpr (kLds) {
+    __shared__ BlockLds S;
+    const OffSource<LcpIndex<LdsIndexBlocks>> src{a, a.ix.lds(S)};
+    if (j < np) out[j] = src((size_t)j);
+  } else {
+    const OffSource<LcpIndex<TableBlocks>> src{a, a.ix.tables()};
+    if (j < np) out[j] = src((size_t)j);
+  }
 }
 
 __device__ __forceinline__ int64_t off_size(const OffElem& e, int32_t n) {
@@ -2489,7 +2669,8 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
     cl.on = true;
   }
   int64_t* local = (int64_t*)(w + L.local);
-  const LcpIndex ix{ib1, L.ib_stride, st1, L.nb1, L.levels, n};
+  const IndexArgs ix{ib1, ib2, L.ib_stride, st1, st2, L.nb1, L.nb2, L.levels, n};
+  const bool lds_blocks = L.nb1 <= kLdsBlocks;
 
   // 1. The first round: anchor groups and their heads from a hash table,
   // every member compared with its head, one sort, then the segments.
@@ -2558,7 +2739,7 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
   hipLaunchKernelGGL(k_final_blocks, dim3(fb_blocks + (ride_demand ? blocks_for(t->num_nodes, 256 * kDiffNodes) : 0)),
                      dim3(256), 0,
                      st, n, el, lcp, key2, ib1, ib2, L.ib_stride, st1, st2, L.nb1, L.nb2, cl, off != nullptr, fr);
-  {
+  if (!lds_blocks) {
     const int32_t nbm = std::max(L.nb1, L.nb2);
     hipLaunchKernelGGL(k_final_tables, dim3(blocks_for(nbm, kTabChunk)), dim3(kTabChunk), 0, st, st1, st2, L.nb1,
                        L.nb2, L.levels);
@@ -2574,9 +2755,13 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
     int64_t* roff = (int64_t*)(w + L.roff);
     int pc = 0;
     if (n >= 2) {
-      const OffArgs oa{n, lcp, el, ix, ib2, st2, L.nb2, npar[0], start[0], rnode, roff};
-      hipLaunchKernelGGL(k_off_make, dim3(blocks_for((int64_t)L.onp)), dim3(256), 0, st, OffSource{oa},
-                         (OffElem*)(w + L.oel_a), (int64_t)L.onp);
+      const OffArgs oa{n, lcp, el, ix, npar[0], start[0], rnode, roff};
+      if (lds_blocks)
+        hipLaunchKernelGGL(k_off_make<true>, dim3(blocks_for((int64_t)L.onp)), dim3(256), 0, st, oa,
+                           (OffElem*)(w + L.oel_a), (int64_t)L.onp);
+      else
+        hipLaunchKernelGGL(k_off_make<false>, dim3(blocks_for((int64_t)L.onp)), dim3(256), 0, st, oa,
+                           (OffElem*)(w + L.oel_a), (int64_t)L.onp);
       const int32_t m2 = 2 * n;
       OffElem* oel = (OffElem*)(w + L.oel_a);
       const OffElem* sorted =
@@ -2600,8 +2785,12 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
     }
     hipLaunchKernelGGL(k_off_place, dim3(blocks_for(n)), dim3(256), 0, st, n, el, rnode, roff, start[pc], off->perm);
   } else {
-    hipLaunchKernelGGL(k_final_query, dim3(blocks_for(n)), dim3(256), 0, st, n, threshold, key2, lcp, el, ix, ib2,
-                       st2, L.nb2, cid, csz, cl);
+    if (lds_blocks)
+      hipLaunchKernelGGL(k_final_query<true>, dim3(blocks_for(n)), dim3(256), 0, st, n, threshold, key2, lcp, el, ix,
+                         cid, csz, cl);
+    else
+      hipLaunchKernelGGL(k_final_query<false>, dim3(blocks_for(n)), dim3(256), 0, st, n, threshold, key2, lcp, el, ix,
+                         cid, csz, cl);
     if (cl.on) {
       const unsigned sb = blocks_for(n, kScanThreads);
       hipLaunchKernelGGL(k_clpm_scan, dim3(sb), dim3(kScanThreads), 0, st, n, key2, local, cl);
