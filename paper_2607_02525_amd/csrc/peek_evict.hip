@@ -29,14 +29,14 @@
 //     the 2^k nearest nodes of its chain).
 //  2. k_ev_top: the sparse table over the superblock maxima (one workgroup
 //     up to 1024 superblocks, one launch per level beyond the eleventh for
-//     more); it also clears the sort's counters.
+//     more).
 //  3. k_ev_keys: K of every node, whether the node tops its run (its
 //     parent's K differs), and from each top the sort element of its leaf
 //     (E, leaf, run length), with the byte histograms of E and the OR and
 //     AND of all keys.
 //  4. k_ev_segs: the segments (consecutive leaves of equal E), which is all
 //     that is left to sort.
-//  5. k_ev_sort: where each segment starts in the victim order. Up to 4096
+//  5. k_ev_sort: where each segment starts in the victim order. Up to 8192
 //     segments every one is counted against all; more go through stable
 //     least-significant-digit radix passes over 4096-segment tiles, a byte on
 //     which all keys agree being skipped, and a prefix of the run lengths.
@@ -67,6 +67,50 @@ __device__ __forceinline__ bool ekey_less(const EKey& a, const EKey& b) {
 __device__ __forceinline__ EKey ekey_max(const EKey& a, const EKey& b) { return ekey_less(a, b) ? b : a; }
 __device__ __forceinline__ EKey shfl_key(const EKey& k, int src) {
   return EKey{__shfl(k.e, src), __shfl(k.id, src), 0};
+}
+
+// v moved between lanes by a DPP control (every lane active); `old` where the
+// control names no lane or the row of 16 lanes is not in kRows. Such a move
+// is part of a VALU instruction, where a shuffle is a round trip through LDS;
+// the shuffles of prefix and suffix steps alone kept a CU's LDS busy for a
+// third of k_ev_blocks.
+template <int kCtrl, int kRows = 0xF>
+__device__ __forceinline__ uint64_t dpp64(uint64_t old, uint64_t v) {
+  const uint32_t lo = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)old, (int)(uint32_t)v, kCtrl, kRows, 0xF, false);
+  const uint32_t hi = (uint32_t)__builtin_amdgcn_update_dpp((int)(uint32_t)(old >> 32), (int)(uint32_t)(v >> 32), kCtrl,
+                                                            kRows, 0xF, false);
+  return ((uint64_t)hi << 32) | lo;
+}
+constexpr int kRowShl = 0x100, kRowShr = 0x110;          // + n: from n lanes above, below, in the row
+constexpr int kRowLast15 = 0x142, kRowLast31 = 0x143;    // the last lane of the row (of the half) before
+
+__device__ __forceinline__ uint64_t lane64(uint64_t v, int lane) {   // a uniform lane's value
+  return ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(v >> 32), lane) << 32) |
+         (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)v, lane);
+}
+
+// Inclusive prefix and suffix maxima over a wave (T: uint64_t or int64_t).
+template <int kCtrl, int kRows, typename T>
+__device__ __forceinline__ T dpp_max(T v) {
+  return max(v, (T)dpp64<kCtrl, kRows>((uint64_t)v, (uint64_t)v));
+}
+template <typename T>
+__device__ __forceinline__ T wave_prefix_max(T v) {
+  v = dpp_max<kRowShr + 1, 0xF>(v);
+  v = dpp_max<kRowShr + 2, 0xF>(v);
+  v = dpp_max<kRowShr + 4, 0xF>(v);
+  v = dpp_max<kRowShr + 8, 0xF>(v);
+  v = dpp_max<kRowLast15, 0xA>(v);
+  return dpp_max<kRowLast31, 0xC>(v);
+}
+__device__ __forceinline__ uint64_t wave_suffix_max(uint64_t v, int lane) {
+  v = dpp_max<kRowShl + 1, 0xF>(v);
+  v = dpp_max<kRowShl + 2, 0xF>(v);
+  v = dpp_max<kRowShl + 4, 0xF>(v);
+  v = dpp_max<kRowShl + 8, 0xF>(v);
+  // no move goes down a row: the rows' maxima lie in their first lanes
+  const uint64_t r3 = lane64(v, 48), r2 = max(lane64(v, 32), r3), r1 = max(lane64(v, 16), r2);
+  return max(v, lane < 16 ? r1 : lane < 32 ? r2 : lane < 48 ? r3 : 0);
 }
 
 // ---- scores on deep trees: pointer jumping on the parent links ----
@@ -149,11 +193,11 @@ __global__ __launch_bounds__(kBlkThreads) void k_ev_blocks(EvictTree t, const in
       const int32_t ac = a >= 0 ? a : 0;
       const int32_t adm = demand[ac];
       const int32_t adp = t.nodes[ac].depth;
-      // in-block part of the chain: jump over parent lanes (6 rounds cover 64)
+      // in-block part of the chain: jump over parent lanes (at most 6 rounds
+      // cover 64; none is left once every lane has reached its topmost one)
       int64_t v = valid ? (int64_t)dm * r.depth : INT64_MIN;
       int32_t pl = (valid && r.parent >= b * kWave) ? r.parent - b * kWave : -1;
-#pragma unroll
-      for (int s = 0; s < 6; ++s) {
+      while (__ballot(pl >= 0) != 0) {
         const int src = pl >= 0 ? pl : lane;
         const int64_t ov = __shfl(v, src);
         const int32_t op = __shfl(pl, src);
@@ -163,12 +207,7 @@ __global__ __launch_bounds__(kBlkThreads) void k_ev_blocks(EvictTree t, const in
         }
       }
       // above the block: prefix maxima over the first node's ancestors by level
-      int64_t pm = a >= 0 ? (int64_t)adm * adp : INT64_MIN;
-#pragma unroll
-      for (int d = 1; d < kWave; d <<= 1) {
-        const int64_t q = __shfl(pm, lane >= d ? lane - d : lane);
-        if (lane >= d) pm = max(pm, q);
-      }
+      const int64_t pm = wave_prefix_max(a >= 0 ? (int64_t)adm * adp : INT64_MIN);
       const int64_t up = __shfl(pm, epl >= 0 ? epl : 0);
       e = epl >= 0 ? max(v, up) : v;
     } else {
@@ -178,14 +217,7 @@ __global__ __launch_bounds__(kBlkThreads) void k_ev_blocks(EvictTree t, const in
     if (o.tables) {
       if constexpr (kPacked) {
         const uint64_t k = valid ? ((uint64_t)e << 6) | (uint64_t)lane : 0;
-        uint64_t p = k, s = k;
-#pragma unroll
-        for (int d = 1; d < kWave; d <<= 1) {
-          const uint64_t x = __shfl(p, lane >= d ? lane - d : lane);
-          if (lane >= d) p = max(p, x);
-          const uint64_t y = __shfl(s, lane + d < kWave ? lane + d : lane);
-          if (lane + d < kWave) s = max(s, y);
-        }
+        const uint64_t p = wave_prefix_max(k), s = wave_suffix_max(k, lane);
         if (valid) {
           ((uint64_t*)o.pre)[c] = p;
           ((uint64_t*)o.suf)[c] = s;
@@ -233,7 +265,7 @@ __global__ __launch_bounds__(kBlkThreads) void k_ev_blocks(EvictTree t, const in
   }
 }
 
-// ---- 2. sparse table over the superblock maxima; counters cleared ----
+// ---- 2. sparse table over the superblock maxima ----
 
 constexpr int kTabChunk = 1024;
 constexpr int kTabLocalLevels = 11;   // levels 0..10: windows of up to kTabChunk entries
@@ -249,27 +281,19 @@ constexpr int kTicketSort = 1;
 constexpr int kTicketDone = 2;
 constexpr int kTickets = kTicketDone + kMaxDigits;
 
+// All of it cleared by k_ev_blocks.
 struct Counters {
   uint32_t* ticket;   // [kTickets]
   uint32_t* hist;     // [kHistCopies][kMaxDigits][kRadix]: segments per byte value of E
-  uint64_t* orand;    // [kOrCopies][2]: OR and AND of the keys
+  uint64_t* orand;    // [kOrCopies][2]: OR of the keys and of their complements
   uint32_t* err;      // set when a wait gives up
   int32_t* nseg;      // segments (written by the segment pass)
 };
 
-__device__ __forceinline__ void clear_counters(const Counters& z) {
-  for (int i = threadIdx.x; i < kHistCopies * kMaxDigits * kRadix; i += blockDim.x) z.hist[i] = 0;
-  if (threadIdx.x < 2 * kOrCopies) z.orand[threadIdx.x] = (threadIdx.x & 1) ? ~uint64_t(0) : 0;
-  if (threadIdx.x < kTickets) z.ticket[threadIdx.x] = 0;
-  if (threadIdx.x == 0) *z.err = 0;
-}
-
 // Up to kTabChunk entries: one workgroup, thread j holds entry j of the
 // current level and reads its partner from LDS.
-__global__ __launch_bounds__(kTabChunk) void k_ev_top_small(EKey* __restrict__ top, int32_t n, int levels,
-                                                            Counters z) {
+__global__ __launch_bounds__(kTabChunk) void k_ev_top_small(EKey* __restrict__ top, int32_t n, int levels) {
   __shared__ EKey sh[kTabChunk];
-  clear_counters(z);
   const int j = threadIdx.x;
   EKey v = j < n ? top[j] : no_key();
   for (int k = 1; k < levels; ++k) {
@@ -288,9 +312,8 @@ __global__ __launch_bounds__(kTabChunk) void k_ev_top_small(EKey* __restrict__ t
 // More entries: workgroup g owns entries [g * kTabChunk, (g + 1) * kTabChunk)
 // and stages the level-0 maxima of twice as many in LDS, enough for every
 // level whose window fits in kTabChunk + 1 entries.
-__global__ __launch_bounds__(1024) void k_ev_top(EKey* __restrict__ top, int32_t n, int levels, Counters z) {
+__global__ __launch_bounds__(1024) void k_ev_top(EKey* __restrict__ top, int32_t n, int levels) {
   __shared__ EKey a[2][2 * kTabChunk];
-  if (blockIdx.x == 0) clear_counters(z);
   const int32_t c0 = (int32_t)blockIdx.x * kTabChunk;
   for (int32_t j = threadIdx.x; j < 2 * kTabChunk; j += blockDim.x)
     a[0][j] = c0 + j < n ? top[c0 + j] : no_key();
@@ -394,25 +417,44 @@ __global__ __launch_bounds__(kKeyThreads) void k_ev_keys(KeyArgs a) {
     const int32_t pend = a.t.pend[cc];
     const int32_t rank0 = a.t.leaf_rank[cc];
     const EvNode r = valid ? r0 : EvNode{-1, 0, c + 1, 0};
-    EKey tt[6];
-    tt[0] = valid ? EKey{e0, c, 0} : no_key();
-#pragma unroll
-    for (int k = 1; k < 6; ++k) {
-      const int d = 1 << (k - 1);
-      const EKey o = shfl_key(tt[k - 1], lane + d < kWave ? lane + d : lane);
-      tt[k] = lane + d < kWave ? ekey_max(tt[k - 1], o) : tt[k - 1];
-    }
     const int32_t hi = r.end - 1;
     const bool inside = (hi >> 6) == b;
     // [c, hi] inside the block, else [c, end of block]: two windows of 2^lv
     const int qhi = inside ? hi - b * kWave : kWave - 1;
     const int lv = min(31 - __clz(qhi - lane + 1), 5);
     const int src2 = qhi - (1 << lv) + 1;
-    EKey kc = tt[0];
+    EKey kc;
+    if constexpr (kPacked) {   // (E, id) as in the in-block tables: two words a shuffle, not three
+      uint64_t tt[6];
+      tt[0] = valid ? ((uint64_t)e0 << 6) | (uint64_t)lane : 0;
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
-      const EKey o = shfl_key(tt[k], src2);
-      if (k == lv) kc = ekey_max(tt[k], o);
+      for (int k = 1; k < 6; ++k) {
+        const int d = 1 << (k - 1);
+        const uint64_t o = __shfl(tt[k - 1], lane + d < kWave ? lane + d : lane);
+        tt[k] = max(tt[k - 1], o);   // a lane past the end reads itself
+      }
+      uint64_t m = 0;
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const uint64_t o = __shfl(tt[k], src2);
+        if (k == lv) m = max(tt[k], o);
+      }
+      kc = EKey{(int64_t)(m >> 6), b * kWave + (int32_t)(m & (kWave - 1)), 0};
+    } else {
+      EKey tt[6];
+      tt[0] = valid ? EKey{e0, c, 0} : no_key();
+#pragma unroll
+      for (int k = 1; k < 6; ++k) {
+        const int d = 1 << (k - 1);
+        const EKey o = shfl_key(tt[k - 1], lane + d < kWave ? lane + d : lane);
+        tt[k] = lane + d < kWave ? ekey_max(tt[k - 1], o) : tt[k - 1];
+      }
+      kc = tt[0];
+#pragma unroll
+      for (int k = 0; k < 6; ++k) {
+        const EKey o = shfl_key(tt[k], src2);
+        if (k == lv) kc = ekey_max(tt[k], o);
+      }
     }
     if (valid && !inside) kc = span_max<kPacked>(a.R, kc, c, hi);
     // the parent's K
@@ -452,23 +494,21 @@ constexpr uint64_t kStSet = uint64_t(1) << 62;
 constexpr uint64_t kStVal = kStSet - 1;
 constexpr uint32_t kSpinCap = 1u << 24;
 
-// The OR/AND copies folded into sh[2] (the first wave loads them, every
-// thread of the workgroup calls this).
-__device__ __forceinline__ void fold_orand(const uint64_t* __restrict__ orand, uint64_t* sh) {
+// The bits on which the keys differ, from the copies (the first wave loads
+// them, every thread of the workgroup calls this).
+__device__ __forceinline__ uint64_t fold_orand(const uint64_t* __restrict__ orand, uint64_t* sh) {
   const int t = threadIdx.x;
   if (t < kWave) {
     static_assert(kOrCopies == kWave, "one copy per lane");
     uint64_t o = orand[2 * t], n = orand[2 * t + 1];
     for (int d = 1; d < kWave; d <<= 1) {
       o |= __shfl_xor(o, d);
-      n &= __shfl_xor(n, d);
+      n |= __shfl_xor(n, d);
     }
-    if (t == 0) {
-      sh[0] = o;
-      sh[1] = n;
-    }
+    if (t == 0) *sh = o & n;
   }
   __syncthreads();
+  return *sh;
 }
 
 // Whether pass p runs: its byte differs between keys, or no byte does and
@@ -602,24 +642,30 @@ __device__ __forceinline__ void wave_rank(const uint32_t (&dg)[kPItems], const b
   }
 }
 
-// The prefix of a tile's (wave-blocked) items: wave w owns items
-// base .. base + 511 of the tile, item i of lane l being base + 64i + l.
-// Returns the exclusive prefix of each item within the tile in pre[] and
-// the tile total; wsum: kPWaves words of LDS.
-__device__ __forceinline__ uint64_t tile_prefix(const uint64_t (&val)[kPItems], uint64_t (&pre)[kPItems],
-                                                uint64_t* wsum) {
+// Inclusive prefix sum over a wave (every lane active).
+__device__ __forceinline__ uint64_t wave_prefix(uint64_t v) {
+  v += dpp64<kRowShr + 1>(0, v);
+  v += dpp64<kRowShr + 2>(0, v);
+  v += dpp64<kRowShr + 4>(0, v);
+  v += dpp64<kRowShr + 8>(0, v);
+  v += dpp64<kRowLast15, 0xA>(0, v);
+  return v + dpp64<kRowLast31, 0xC>(0, v);
+}
+
+// The prefix of a tile's (wave-blocked) items: wave w owns 64 * I items of
+// the tile, item i of lane l being 64i + l of them. Returns the exclusive
+// prefix of each item within the tile in pre[] and the tile total; wsum:
+// kPWaves words of LDS.
+template <int I>
+__device__ __forceinline__ uint64_t tile_prefix(const uint64_t (&val)[I], uint64_t (&pre)[I], uint64_t* wsum) {
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
   uint64_t carry = 0;
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
-    uint64_t x = val[i];
-#pragma unroll
-    for (int k = 1; k < kWave; k <<= 1) {
-      const uint64_t o = __shfl(x, lane >= k ? lane - k : lane);
-      if (lane >= k) x += o;
-    }
+  for (int i = 0; i < I; ++i) {
+    const uint64_t x = wave_prefix(val[i]);
     pre[i] = carry + x - val[i];
-    carry += __shfl(x, kWave - 1);
+    carry += ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(x >> 32), kWave - 1) << 32) |
+             (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)x, kWave - 1);
   }
   if (lane == 0) wsum[w] = carry;
   __syncthreads();
@@ -629,7 +675,7 @@ __device__ __forceinline__ uint64_t tile_prefix(const uint64_t (&val)[kPItems], 
     total += wsum[j];
   }
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) pre[i] += before;
+  for (int i = 0; i < I; ++i) pre[i] += before;
   return total;
 }
 
@@ -643,9 +689,9 @@ static_assert(sizeof(SegElem) == 16, "SegElem is 16 bytes");
 
 // Segments: maximal runs of consecutive leaves (by leaf rank) with equal E.
 // Sorting the leaves by (E, id) is sorting the segments by E stably, so only
-// segments are sorted. Per leaf rank: its segment and the
-// exclusive prefix RP of run lengths in leaf order; per segment: its sort
-// element, RP at its first leaf, the byte histograms and OR/AND of E.
+// segments are sorted. Per leaf rank: its segment and the exclusive prefix RP
+// of run lengths in leaf order; per segment: its sort element, RP at its
+// first leaf, the byte histograms of E, the OR of E and of its complement.
 // Prefix values pack the segment count (bits 31..61) and the run lengths
 // (bits 0..30).
 struct SegArgs {
@@ -663,33 +709,40 @@ struct SegArgs {
   Counters z;
 };
 
+// Leaves per thread: few, so that 90,000 leaves are spread over 86 CUs (22
+// with tiles of 4096: 7.8 against 11.2 us), until the tiles are so many that
+// waiting for the totals of all earlier ones is the longest part (a million
+// leaves: 11.8 us with 8 per thread, 15.5 with 4, 23.5 with 2).
+constexpr int kSegFew = 2, kSegMany = 8;
+constexpr int32_t kSegFewMax = 131072;   // leaves
+constexpr uint32_t kSegDirect = 64;       // segments that start in a tile
+
+template <int kSegItems>
 __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
+  constexpr int kSegTile = kPThreads * kSegItems;
   __shared__ int32_t s_tile;
   __shared__ uint32_t lh[kMaxDigits * kRadix];
-  __shared__ unsigned long long red[2];
   __shared__ uint64_t wsum[kPWaves];
   __shared__ uint64_t s_excl;
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  for (int i = t; i < A.n_digits * kRadix; i += kPThreads) lh[i] = 0;
-  if (t < 2) red[t] = t ? ~0ull : 0ull;
   if (t == 0) s_tile = (int32_t)atomicAdd(&A.z.ticket[kTicketSegs], 1u);
   __syncthreads();
   const int32_t tile = s_tile;
-  const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
-  int64_t e[kPItems], pe[kPItems];
-  int32_t run[kPItems];
+  const int64_t base = (int64_t)tile * kSegTile + (int64_t)w * (kWave * kSegItems);
+  int64_t e[kSegItems], pe[kSegItems];
+  int32_t run[kSegItems];
   // clamped loads, all in flight at once
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < kSegItems; ++i) {
     const int64_t idx = min(base + i * kWave + lane, (int64_t)A.L - 1);
     e[i] = A.Er[idx];
     pe[i] = A.Er[idx > 0 ? idx - 1 : 0];
     run[i] = A.runr[idx];
   }
-  uint64_t val[kPItems], pre[kPItems];
-  bool head[kPItems];
+  uint64_t val[kSegItems], pre[kSegItems];
+  bool head[kSegItems];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < kSegItems; ++i) {
     const int64_t idx = base + i * kWave + lane;
     const bool in = idx < A.L;
     head[i] = in && (idx == 0 || e[i] != pe[i]);
@@ -706,9 +759,17 @@ __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
   __syncthreads();
   const uint64_t start = s_excl;
   if (tile == A.tiles - 1 && t == 0) *A.z.nseg = (int32_t)((start + total) >> 31);
-  uint64_t or_e = 0, and_e = ~uint64_t(0);
+  // few segments start in most tiles of a queue's demand: those are counted
+  // in memory at once, many in LDS first
+  uint32_t* hc = A.z.hist + (size_t)(blockIdx.x % kHistCopies) * kMaxDigits * kRadix;
+  const bool many = (total >> 31) > kSegDirect;   // uniform
+  if (many) {
+    for (int i = t; i < kMaxDigits * kRadix; i += kPThreads) lh[i] = 0;
+    __syncthreads();
+  }
+  uint64_t or_e = 0, or_c = 0;
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < kSegItems; ++i) {
     const int64_t idx = base + i * kWave + lane;
     if (idx >= A.L) continue;
     const uint64_t x = start + pre[i];
@@ -721,28 +782,29 @@ __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
       A.el[seg] = SegElem{key, seg, 0};
       A.segRP[seg] = rp;
       or_e |= key;
-      and_e &= key;
-      for (int dg = 0; dg < A.n_digits; ++dg) atomicAdd(&lh[dg * kRadix + ((key >> (8 * dg)) & 255u)], 1u);
+      or_c |= ~key;
+      for (int dg = 0; dg < A.n_digits; ++dg) {
+        const uint32_t at = dg * kRadix + (uint32_t)((key >> (8 * dg)) & 255u);
+        if (many) atomicAdd(&lh[at], 1u);
+        else atomicAdd(&hc[at], 1u);
+      }
     }
   }
+  if ((total >> 31) == 0) return;
 #pragma unroll
   for (int k = 1; k < kWave; k <<= 1) {
     or_e |= __shfl_xor(or_e, k);
-    and_e &= __shfl_xor(and_e, k);
+    or_c |= __shfl_xor(or_c, k);
   }
-  if (lane == 0) {
-    atomicOr(&red[0], (unsigned long long)or_e);
-    atomicAnd(&red[1], (unsigned long long)and_e);
+  if (lane == 0 && (or_e | or_c) != 0) {
+    uint64_t* o = A.z.orand + 2 * (blockIdx.x % kOrCopies);
+    atomicOr((unsigned long long*)&o[0], (unsigned long long)or_e);
+    atomicOr((unsigned long long*)&o[1], (unsigned long long)or_c);
   }
+  if (!many) return;
   __syncthreads();
-  uint32_t* hc = A.z.hist + (size_t)(blockIdx.x % kHistCopies) * kMaxDigits * kRadix;
   for (int i = t; i < A.n_digits * kRadix; i += kPThreads)
     if (lh[i]) atomicAdd(&hc[i], lh[i]);
-  if (t == 0) {
-    uint64_t* o = A.z.orand + 2 * (blockIdx.x % kOrCopies);
-    atomicOr((unsigned long long*)&o[0], red[0]);
-    atomicAnd((unsigned long long*)&o[1], red[1]);
-  }
 }
 
 struct SortArgs {
@@ -759,20 +821,6 @@ struct SortArgs {
   Counters z;
 };
 
-// Segments move between passes inside one launch, so they are written
-// through to where every XCD sees them, and read from there.
-__device__ __forceinline__ SegElem load_shared(const SegElem* p) {
-  const uint64_t* w = reinterpret_cast<const uint64_t*>(p);
-  const uint64_t k = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  const uint64_t g = __hip_atomic_load(w + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  return SegElem{k, (int32_t)(uint32_t)g, 0};
-}
-__device__ __forceinline__ void store_shared(SegElem* p, const SegElem& v) {
-  uint64_t* w = reinterpret_cast<uint64_t*>(p);
-  __hip_atomic_store(w, v.ke, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  __hip_atomic_store(w + 1, (uint64_t)(uint32_t)v.seg, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
 struct PassLds {
   uint32_t cnt[kRadix];
   uint32_t part[2][kRadix];
@@ -780,14 +828,17 @@ struct PassLds {
   uint32_t wsum[kRadix / kWave];
   uint32_t whist[kPWaves][kRadix];
 };
+// Segments that are counted rather than sorted: 8192 of them take 17 us more
+// than 4096, two radix passes and their prefix over 40.
+constexpr int kRankSegs = 8192;
 struct RankLds {
-  uint64_t key[kPTile];
-  uint32_t run[kPTile];
+  uint64_t key[kRankSegs];
+  uint32_t run[kRankSegs];
 };
 
 // Every segment's start, counted: the run lengths of the segments before it
 // in (E, leaf) order. Every workgroup stages all keys and run lengths (at
-// most 48 KB) and its wavefronts count kOwn segments at a time.
+// most 96 KB) and its wavefronts count kOwn segments at a time.
 __device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
   constexpr int kOwn = 2;
   const int t = threadIdx.x, lane = t & (kWave - 1);
@@ -822,8 +873,8 @@ __device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
 }
 
 // One tile of the radix pass over byte p, src to dst.
-__device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, bool first, int p, int32_t tile,
-                           int32_t tiles, int32_t L, PassLds& sh) {
+__device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, int p, int32_t tile, int32_t tiles,
+                           int32_t L, PassLds& sh) {
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   const int d = t & (kRadix - 1), half = t / kRadix;
   // the digit's histogram is loaded alongside the tile
@@ -844,7 +895,7 @@ __device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, 
   for (int q = 0; q < kPItems; ++q) {
     const int64_t idx = base + q * kWave + lane;
     valid[q] = idx < L;
-    v[q] = first ? src[valid[q] ? idx : L - 1] : load_shared(src + (valid[q] ? idx : L - 1));
+    v[q] = src[valid[q] ? idx : L - 1];
   }
 #pragma unroll
   for (int q = 0; q < kPItems; ++q) dg[q] = valid[q] ? (uint32_t)(v[q].ke >> (8 * p)) & 255u : 0;
@@ -888,7 +939,7 @@ __device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, 
   for (int q = 0; q < kPItems; ++q) {
     if (!valid[q]) continue;
     const uint32_t pos = sh.gbase[dg[q]] + sh.whist[w][dg[q]] + rk[q];
-    if (pos < (uint32_t)L) store_shared(dst + pos, v[q]);
+    if (pos < (uint32_t)L) dst[pos] = v[q];
   }
 }
 
@@ -901,7 +952,7 @@ __device__ void scan_tile(const SortArgs& A, const SegElem* el, int32_t tile, in
   const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
   int32_t seg[kPItems], r0[kPItems], r1[kPItems];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) seg[i] = load_shared(el + min(base + i * kWave + lane, (int64_t)L - 1)).seg;
+  for (int i = 0; i < kPItems; ++i) seg[i] = el[min(base + i * kWave + lane, (int64_t)L - 1)].seg;
 #pragma unroll
   for (int i = 0; i < kPItems; ++i) {
     const int32_t sc = (uint32_t)seg[i] < (uint32_t)L ? seg[i] : 0;
@@ -944,16 +995,15 @@ __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
     RankLds rank;
     PassLds pass;
   } sh;
-  __shared__ uint64_t oa[2], wsum[kPWaves], s_excl;
+  __shared__ uint64_t wsum[kPWaves], s_excl, s_diff;
   __shared__ int32_t s_ticket;
   const int t = threadIdx.x;
   const int32_t L = *A.z.nseg;
-  if (L <= kPTile) {
+  if (L <= kRankSegs) {
     rank_segments(A, L, sh.rank);
     return;
   }
-  fold_orand(A.z.orand, oa);
-  const uint64_t diff = oa[0] ^ oa[1];
+  const uint64_t diff = fold_orand(A.z.orand, &s_diff);
   int passes = 0;
   for (int q = 0; q < A.n_digits; ++q) passes += pass_runs(diff, q) ? 1 : 0;
   const int32_t tiles = (L + kPTile - 1) / kPTile;
@@ -965,18 +1015,21 @@ __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
     if (ticket >= (passes + 1) * tiles) return;
     const int k = ticket / tiles;   // the pass; after the last one the prefix
     const int32_t tile = ticket % tiles;
-    if (k > 0 && t == 0) {
-      uint32_t* done = &A.z.ticket[kTicketDone + k - 1];
-      for (uint32_t spins = 0; __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)tiles;
-           ++spins) {
-        if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
-          atomicOr(A.z.err, 1u);
-          break;
+    if (k > 0) {
+      if (t == 0) {
+        uint32_t* done = &A.z.ticket[kTicketDone + k - 1];
+        for (uint32_t spins = 0;
+             __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)tiles; ++spins) {
+          if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
+            atomicOr(A.z.err, 1u);
+            break;
+          }
+          __builtin_amdgcn_s_sleep(2);
         }
-        __builtin_amdgcn_s_sleep(2);
       }
+      __syncthreads();
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    __syncthreads();
     SegElem* src = (k & 1) ? A.b : A.a;
     if (k == passes) {
       scan_tile(A, src, tile, L, wsum, &s_excl);
@@ -985,11 +1038,16 @@ __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
     int p = -1;
     for (int q = 0, seen = 0; q < A.n_digits; ++q)
       if (pass_runs(diff, q) && seen++ == k) p = q;
-    radix_tile(A, src, (k & 1) ? A.a : A.b, k == 0, p, tile, tiles, L, sh.pass);
-    // the written-through segments have arrived once the stores are answered
+    radix_tile(A, src, (k & 1) ? A.a : A.b, p, tile, tiles, L, sh.pass);
+    // every thread's stores are in this XCD's L2 once answered; one thread
+    // then writes it back (storing each segment through instead took twice
+    // as long: scattered 16-byte writes)
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (t == 0) __hip_atomic_fetch_add(&A.z.ticket[kTicketDone + k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (t == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(&A.z.ticket[kTicketDone + k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
 }
 
@@ -1284,7 +1342,8 @@ ELayout elayout(int64_t nn) {
   L.orand = take(sizeof(uint64_t) * 2 * kOrCopies);
   L.cnt = take(sizeof(uint32_t) * (kTickets + 2));
   // per pass (and for the segment pass and the scan): tile and group status
-  L.status = take(sizeof(uint64_t) * (size_t)(kMaxDigits * kRadix + 2) * (size_t)(L.tiles + L.groups));
+  L.status = take(sizeof(uint64_t) * (size_t)(kMaxDigits * kRadix + 1 + kPItems / kSegFew) *
+                  (size_t)(L.tiles + L.groups));
   L.ej_a = take(sizeof(int64_t) * n);   // pointer jumping (deep trees)
   L.ej_b = take(sizeof(int64_t) * n);
   L.j_a = take(sizeof(int32_t) * n);
@@ -1345,11 +1404,16 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
   }
   EKey* top = (EKey*)(w + L.top);
   uint64_t* status = (uint64_t*)(w + L.status);
-  const int64_t n_status = (int64_t)n_digits * per_pass + 2 * tiles;
+  const bool few = n_leaves <= kSegFewMax;
+  const int32_t seg_tile = kPThreads * (few ? kSegFew : kSegMany);
+  const int32_t seg_tiles = (n_leaves + seg_tile - 1) / seg_tile;
+  // cleared by k_ev_blocks, one region: histograms, OR copies, tickets, status
+  const int64_t n_zero = (int64_t)((L.status - L.hist) / sizeof(uint64_t)) + (int64_t)n_digits * per_pass + seg_tiles + tiles;
   // E goes straight to the score output when there is one
   int64_t* E = score ? score : (int64_t*)(w + L.e);
   const bool packed = (e_bound >> 58) == 0;
-  BlockOut bo{E, w + L.pre, w + L.suf, (EKey*)(w + L.sbt), top, status, ordered ? n_status : 0, ordered ? 1 : 0};
+  BlockOut bo{E, w + L.pre, w + L.suf, (EKey*)(w + L.sbt), top, (uint64_t*)(w + L.hist),
+              ordered ? n_zero : 0, ordered ? 1 : 0};
   const dim3 bg((unsigned)L.nsb), bt(kBlkThreads);
   if (t.shallow && packed)
     hipLaunchKernelGGL((k_ev_blocks<true, true>), bg, bt, 0, st, t, demand, Ej, nn, L.nb, bo);
@@ -1364,10 +1428,10 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     Counters z{cnt, (uint32_t*)(w + L.hist), (uint64_t*)(w + L.orand), cnt + kTickets,
                (int32_t*)(cnt + kTickets + 1)};
     if (L.nsb <= kTabChunk)
-      hipLaunchKernelGGL(k_ev_top_small, dim3(1), dim3(kTabChunk), 0, st, top, L.nsb, L.top_levels, z);
+      hipLaunchKernelGGL(k_ev_top_small, dim3(1), dim3(kTabChunk), 0, st, top, L.nsb, L.top_levels);
     else
       hipLaunchKernelGGL(k_ev_top, dim3((unsigned)((L.nsb + kTabChunk - 1) / kTabChunk)), dim3(1024), 0, st, top,
-                         L.nsb, L.top_levels, z);
+                         L.nsb, L.top_levels);
     for (int k = kTabLocalLevels; k < L.top_levels; ++k)
       hipLaunchKernelGGL(k_ev_top_level, dim3(blocks_of(L.nsb)), dim3(256), 0, st, top, L.nsb, k);
     int32_t* krank = (int32_t*)(w + L.krank);
@@ -1387,9 +1451,12 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     SegElem* el_a = (SegElem*)(w + L.el_a);
     SegElem* el_b = (SegElem*)(w + L.el_b);
     uint64_t* ss = status + (size_t)n_digits * per_pass;
-    SegArgs ga{Er, runr, n_leaves, nn, tiles, n_digits, seg_of, RP, el_a, segRP, ss, z};
-    hipLaunchKernelGGL(k_ev_segs, dim3((unsigned)tiles), dim3(kPThreads), 0, st, ga);
-    SortArgs sa{el_a, el_b, n_digits, status, per_pass, (int64_t)kRadix * tiles, ss + tiles, segRP, Sseg, nn, z};
+    SegArgs ga{Er, runr, n_leaves, nn, seg_tiles, n_digits, seg_of, RP, el_a, segRP, ss, z};
+    if (few)
+      hipLaunchKernelGGL(k_ev_segs<kSegFew>, dim3((unsigned)seg_tiles), dim3(kPThreads), 0, st, ga);
+    else
+      hipLaunchKernelGGL(k_ev_segs<kSegMany>, dim3((unsigned)seg_tiles), dim3(kPThreads), 0, st, ga);
+    SortArgs sa{el_a, el_b, n_digits, status, per_pass, (int64_t)kRadix * tiles, ss + seg_tiles, segRP, Sseg, nn, z};
     // a workgroup per tile there can be; 64 at least, to count few segments
     const unsigned sort_blocks = (unsigned)std::min(std::max(tiles, 64), 1024);
     hipLaunchKernelGGL(k_ev_sort, dim3(sort_blocks), dim3(kPThreads), 0, st, sa);
