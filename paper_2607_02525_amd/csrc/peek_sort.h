@@ -180,8 +180,24 @@ __global__ __launch_bounds__(kScatterThreads) void k_bucket_scatter(Src src, con
   }
 }
 
-template <typename T>
-__device__ __forceinline__ T shfl_xor_elem(const T& v, int mask) {
+// Word v of lane ^ kMask (every lane active). Inside a row of 16 lanes the
+// move is part of a VALU instruction (DPP); only 16 and 32 go through LDS.
+template <int kMask>
+__device__ __forceinline__ int32_t xor_word(int32_t v) {
+  constexpr int kSwap1 = 0xB1, kSwap2 = 0x4E, kReverse4 = 0x1B;   // quad_perm
+  constexpr int kHalfMirror = 0x141, kRor8 = 0x128;
+  if constexpr (kMask == 1) return __builtin_amdgcn_update_dpp(v, v, kSwap1, 0xF, 0xF, false);
+  if constexpr (kMask == 2) return __builtin_amdgcn_update_dpp(v, v, kSwap2, 0xF, 0xF, false);
+  if constexpr (kMask == 4) {   // ^ 7, then ^ 3
+    const int32_t m = __builtin_amdgcn_update_dpp(v, v, kHalfMirror, 0xF, 0xF, false);
+    return __builtin_amdgcn_update_dpp(m, m, kReverse4, 0xF, 0xF, false);
+  }
+  if constexpr (kMask == 8) return __builtin_amdgcn_update_dpp(v, v, kRor8, 0xF, 0xF, false);
+  return __shfl_xor(v, kMask);
+}
+
+template <int kMask, typename T>
+__device__ __forceinline__ T xor_elem(const T& v) {
   static_assert(sizeof(T) % 4 == 0, "whole words");
   union {
     T e;
@@ -189,22 +205,27 @@ __device__ __forceinline__ T shfl_xor_elem(const T& v, int mask) {
   } u;
   u.e = v;
 #pragma unroll
-  for (size_t k = 0; k < sizeof(T) / 4; ++k) u.w[k] = __shfl_xor(u.w[k], mask);
+  for (size_t k = 0; k < sizeof(T) / 4; ++k) u.w[k] = xor_word<kMask>(u.w[k]);
   return u.e;
 }
 
-// Bitonic sort of 64 elements held one per lane, ascending.
+// Bitonic sort of 64 elements held one per lane, ascending: K is the width
+// being merged, J the distance of the lanes compared.
+template <int K, int J, typename T, typename Less>
+__device__ __forceinline__ void wave_merge(T& v, int lane, Less less) {
+  const T o = xor_elem<J>(v);
+  const bool low = ((lane & J) == 0) == ((lane & K) == 0);   // this lane keeps the smaller one
+  if (low == less(o, v)) v = o;
+  if constexpr (J > 1) wave_merge<K, J / 2>(v, lane, less);
+}
 template <typename T, typename Less>
 __device__ __forceinline__ void wave_sort(T& v, int lane, Less less) {
-#pragma unroll
-  for (int k = 2; k <= 64; k <<= 1) {
-#pragma unroll
-    for (int j = k >> 1; j > 0; j >>= 1) {
-      const T o = shfl_xor_elem(v, j);
-      const bool low = ((lane & j) == 0) == ((lane & k) == 0);   // this lane keeps the smaller one
-      if (low == less(o, v)) v = o;
-    }
-  }
+  wave_merge<2, 1>(v, lane, less);
+  wave_merge<4, 2>(v, lane, less);
+  wave_merge<8, 4>(v, lane, less);
+  wave_merge<16, 8>(v, lane, less);
+  wave_merge<32, 16>(v, lane, less);
+  wave_merge<64, 32>(v, lane, less);
 }
 
 // Place of v, at place `own` of run r, among `runs` sorted runs of 64 that lie
