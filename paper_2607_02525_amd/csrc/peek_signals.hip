@@ -1529,9 +1529,10 @@ struct TableBlocks {
 // requests) into LDS, with the minima of every kBlockGroup blocks and sparse
 // tables over those. No launch builds tables then (5 us at 4096 requests, 6.7
 // at 65,536), and a search that leaves its block waits on LDS instead of on
-// up to eleven loads one after another; loading costs the query kernel 3 to 4
-// us, which the cLPM queries win back. Signals of 8192 agentic requests 93 ->
-// 85 us (with the insert kernel's 2.6), offline order of 5000 84 -> 79 us.
+// up to eleven loads one after another. Query kernel, table launch included:
+// 4096 requests 12.3 -> 8.9 us, 65,536 16.0 -> 10.5, cLPM 8192 20.7 -> 12.4,
+// 20,000 21.3 -> 13.9; offline pieces of 5000 requests 14.3 -> 10.8 (1.5 to 4
+// us of it from reading a group with four 16-byte loads).
 // Beyond kLdsBlocks blocks every workgroup would load too much, and the
 // tables are built once.
 constexpr int kLdsBlocks = 1040;
@@ -1541,20 +1542,43 @@ constexpr int kLdsLevels = 7;
 static_assert((1 << kLdsLevels) > kLdsGroups, "the top level spans every group");
 
 struct BlockLds {
-  int32_t a1[kLdsBlocks];
-  uint64_t a2[kLdsBlocks];
+  alignas(16) int32_t a1[kLdsBlocks];
+  alignas(16) uint64_t a2[kLdsBlocks];
   int32_t b1[kLdsLevels][kLdsGroups];
   uint64_t b2[kLdsLevels][kLdsGroups];
 };
 
-// The whole workgroup; what lies past the blocks never is a minimum.
-__device__ __forceinline__ void load_blocks(BlockLds& S, const int32_t* __restrict__ st1,
-                                            const uint64_t* __restrict__ st2, int32_t nb1, int32_t nb2) {
-  const int t = threadIdx.x, nt = blockDim.x;
+// A thread's block minima on their way from memory; what lies past the blocks
+// never is a minimum.
+constexpr int kIndexThreads = 256;
+struct BlockLoads {
+  static constexpr int kEach = (kLdsBlocks + kIndexThreads - 1) / kIndexThreads;
+  int32_t m1[kEach];
+  uint64_t m2[kEach];
+  __device__ __forceinline__ void fetch(const int32_t* __restrict__ st1, const uint64_t* __restrict__ st2, int32_t nb1,
+                                        int32_t nb2) {
+#pragma unroll
+    for (int q = 0; q < kEach; ++q) {
+      const int32_t b = q * kIndexThreads + (int32_t)threadIdx.x;
+      const int32_t x = st1[min(b, nb1 - 1)];
+      const uint64_t y = st2[min(b, nb2 - 1)];
+      m1[q] = b < nb1 ? x : INT32_MAX;
+      m2[q] = b < nb2 ? y : ~0ull;
+    }
+  }
+};
+
+// The whole workgroup of kIndexThreads.
+__device__ __forceinline__ void build_blocks(BlockLds& S, const BlockLoads& loads, int32_t nb1) {
+  const int t = threadIdx.x;
   const int32_t ng = (nb1 + kBlockGroup - 1) / kBlockGroup;   // nb2 <= nb1
-  for (int32_t b = t; b < ng * kBlockGroup; b += nt) {
-    S.a1[b] = b < nb1 ? st1[b] : INT32_MAX;
-    S.a2[b] = b < nb2 ? st2[b] : ~0ull;
+#pragma unroll
+  for (int q = 0; q < BlockLoads::kEach; ++q) {
+    const int32_t b = q * kIndexThreads + t;
+    if (b < kLdsBlocks) {
+      S.a1[b] = loads.m1[q];
+      S.a2[b] = loads.m2[q];
+    }
   }
   __syncthreads();
   if (t < kWave) {   // one wavefront: its LDS accesses keep their order
@@ -1588,25 +1612,28 @@ struct LdsIndexBlocks {
   const BlockLds* S;
   int32_t nb1;
 
+  // a bit per block of group g whose minimum is below s
+  __device__ __forceinline__ uint32_t below_in_group(int32_t g, int32_t s) const {
+    static_assert(kBlockGroup == 16, "four 16-byte reads");
+    const int4* a = reinterpret_cast<const int4*>(S->a1 + g * kBlockGroup);
+    uint32_t m = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int4 v = a[q];
+      m |= ((uint32_t)(v.x < s) | ((uint32_t)(v.y < s) << 1) | ((uint32_t)(v.z < s) << 2) | ((uint32_t)(v.w < s) << 3))
+           << (4 * q);
+    }
+    return m;
+  }
   // the last block of group g at or before hi below s, or -1
   __device__ __forceinline__ int32_t last_in_group(int32_t g, int32_t hi, int32_t s) const {
-    int32_t at = -1;
-#pragma unroll
-    for (int q = 0; q < kBlockGroup; ++q) {
-      const int32_t b = g * kBlockGroup + q;
-      if (b <= hi && S->a1[b] < s) at = b;
-    }
-    return at;
+    const uint32_t m = below_in_group(g, s) & ((2u << (hi - g * kBlockGroup)) - 1);
+    return m ? g * kBlockGroup + 31 - __clz((int)m) : -1;
   }
   // the first block of group g at or after lo below s, or -1
   __device__ __forceinline__ int32_t first_in_group(int32_t g, int32_t lo, int32_t s) const {
-    int32_t at = -1;
-#pragma unroll
-    for (int q = kBlockGroup - 1; q >= 0; --q) {
-      const int32_t b = g * kBlockGroup + q;
-      if (b >= lo && S->a1[b] < s) at = b;
-    }
-    return at;
+    const uint32_t m = below_in_group(g, s) & ~((1u << (lo - g * kBlockGroup)) - 1);
+    return m ? g * kBlockGroup + __ffs((int)m) - 1 : -1;
   }
   __device__ __forceinline__ void pair(bool needL, int32_t& pl, int32_t sL, bool needR, int32_t& pr, int32_t sR) const {
     const int32_t ng = (nb1 + kBlockGroup - 1) / kBlockGroup;
@@ -1626,7 +1653,7 @@ struct LdsIndexBlocks {
     }
     if (needR) {
       int32_t g = min(pr, nb1 - 1) / kBlockGroup;   // pr <= nb1 - 1: the last block answers
-      int32_t at = first_in_group(g, pr, sR);
+      int32_t at = first_in_group(g, min(pr, nb1 - 1), sR);
       if (at < 0) {
         ++g;
         for (int k = kLdsLevels - 1; k >= 0; --k) {
@@ -1644,12 +1671,14 @@ struct LdsIndexBlocks {
   __device__ __forceinline__ uint64_t key_min(int32_t x, int32_t y) const {
     const int32_t gx = x / kBlockGroup, gy = y / kBlockGroup;
     uint64_t m = ~0ull;
+    const ulonglong2* ax = reinterpret_cast<const ulonglong2*>(S->a2 + gx * kBlockGroup);
+    const ulonglong2* ay = reinterpret_cast<const ulonglong2*>(S->a2 + gy * kBlockGroup);
 #pragma unroll
-    for (int q = 0; q < kBlockGroup; ++q) {
+    for (int q = 0; q < kBlockGroup; q += 2) {
       const int32_t bx = gx * kBlockGroup + q, by = gy * kBlockGroup + q;
-      const uint64_t vx = S->a2[bx], vy = S->a2[by];
-      m = umin64(m, bx >= x && bx <= y ? vx : ~0ull);
-      m = umin64(m, by >= x && by <= y ? vy : ~0ull);
+      const ulonglong2 vx = ax[q / 2], vy = ay[q / 2];
+      m = umin64(m, umin64(bx >= x && bx <= y ? vx.x : ~0ull, bx + 1 >= x && bx + 1 <= y ? vx.y : ~0ull));
+      m = umin64(m, umin64(by >= x && by <= y ? vy.x : ~0ull, by + 1 >= x && by + 1 <= y ? vy.y : ~0ull));
     }
     if (gy - gx >= 2) {
       const int k = 31 - __clz(gy - gx - 1);
@@ -1658,6 +1687,41 @@ struct LdsIndexBlocks {
     return m;
   }
 };
+
+// A pair of searches (LcpIndex::pair_from) between its steps: after the
+// in-block rounds at its own places (open), with the blocks that hold what
+// lies elsewhere (locate), and after the in-block rounds there (close). A side
+// that needs no other block still loads inside the tables; its results are
+// not used.
+struct OpenPair {
+  int32_t L, R, sL, sR, pl, pr;
+  bool needL, needR;
+};
+__device__ __forceinline__ OpenPair open_pair(const int32_t* ib1, int64_t stride, int32_t n, int32_t iL, int32_t sL,
+                                              int32_t iR, int32_t sR) {
+  const int32_t bL = iL >> 6, bR = iR >> 6;
+  const int32_t bendR = min((bR << 6) + 63, n);
+  OpenPair p;
+  p.L = last_below(ib1, stride, bL << 6, iL, sL);
+  p.R = first_below(ib1, stride, iR, bendR, sR);
+  p.sL = sL;
+  p.sR = sR;
+  p.needL = p.L < (bL << 6);
+  p.needR = p.R > bendR;
+  p.pl = bL - 1;
+  p.pr = bR + 1;
+  return p;
+}
+template <typename Blocks>
+__device__ __forceinline__ void locate_pair(OpenPair& p, const Blocks& blocks) {
+  blocks.pair(p.needL, p.pl, p.sL, p.needR, p.pr, p.sR);
+}
+__device__ __forceinline__ void close_pair(OpenPair& p, const int32_t* ib1, int64_t stride, int32_t n) {
+  const int32_t l2 = last_below(ib1, stride, p.pl << 6, min((p.pl << 6) + 63, n), p.sL);
+  const int32_t r2 = first_below(ib1, stride, p.pr << 6, min((p.pr << 6) + 63, n), p.sR);
+  if (p.needL) p.L = l2;
+  if (p.needR) p.R = r2;
+}
 
 // Range queries over lcp[0..n] from the in-block tables and a search over
 // the 64-position blocks.
@@ -1673,23 +1737,16 @@ struct LcpIndex {
   // computed together: the two chains of dependent loads (in-block rounds,
   // then the search over the blocks, then the in-block rounds of the block
   // found) advance in the same steps, so the pair waits about as long as one
-  // of them. The side that needs no other block still loads inside the
-  // tables; its results are not used.
+  // of them.
   __device__ __forceinline__ void pair_from(int32_t iL, int32_t sL, int32_t iR, int32_t sR, int32_t& L,
                                             int32_t& R) const {
-    const int32_t bL = iL >> 6, bR = iR >> 6;
-    const int32_t bendR = min((bR << 6) + 63, n);
-    L = last_below(ib1, stride, bL << 6, iL, sL);
-    R = first_below(ib1, stride, iR, bendR, sR);
-    const bool needL = L < (bL << 6), needR = R > bendR;
-    if (needL || needR) {
-      int32_t pl = bL - 1, pr = bR + 1;
-      blocks.pair(needL, pl, sL, needR, pr, sR);
-      const int32_t l2 = last_below(ib1, stride, pl << 6, min((pl << 6) + 63, n), sL);
-      const int32_t r2 = first_below(ib1, stride, pr << 6, min((pr << 6) + 63, n), sR);
-      if (needL) L = l2;
-      if (needR) R = r2;
+    OpenPair p = open_pair(ib1, stride, n, iL, sL, iR, sR);
+    if (p.needL || p.needR) {
+      locate_pair(p, blocks);
+      close_pair(p, ib1, stride, n);
     }
+    L = p.L;
+    R = p.R;
   }
 
   // Last j <= i with lcp[j] < s, for s >= 1 (lcp[0] = 0, so one exists).
@@ -1730,50 +1787,91 @@ struct LcpIndex {
 // One thread per sorted position i: cluster id and size of its request;
 // with cLPM signals requested also the weight of the pending-tree node
 // whose leftmost inner position is i, and the section run of position i.
-// `own` is key2[i], `lcp_i` lcp[i].
-template <typename Ix>
-__device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, uint64_t own, int32_t lcp_i,
-                                            const int32_t* lcp, const ClElem* el, const Ix& ix, int32_t* cid,
-                                            int32_t* csz, const ClpmArgs& cl) {
+// All of a position's searches advance together: their in-block rounds, then
+// `make` (every thread of the workgroup calls it once, told whether any of
+// them needs it) gives the index over the blocks, then the rounds in the
+// blocks found.
+template <typename Make>
+__device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, const uint64_t* key2,
+                                            const int32_t* lcp, const ClElem* el, const int32_t* ib1, int64_t stride,
+                                            const Make& make, int32_t* cid, int32_t* csz, const ClpmArgs& cl) {
   const bool valid = i < n;
-  uint32_t req = 0;
-  if (valid) {
-    const int32_t s = (int32_t)(own >> 32);
-    req = (uint32_t)own;
-    if (s < threshold) {
-      cid[req] = -1;
-      csz[req] = 1;
-    } else {
-      // [L, R): the widest range around i whose inner lcps are >= s
-      int32_t L, R;
-      ix.pair_from(i, s, i + 1, s, L, R);
-      // id: minimum of (share, request) over [L, R)
-      const uint64_t m = ix.key_min(L, R - 1);
-      cid[req] = (int32_t)(uint32_t)m;
-      csz[req] = R - L;
+  const int32_t ic = min(i, n - 1);
+  const uint64_t own = key2[ic];
+  const int32_t lcp_i = lcp[ic];
+  const int32_t s = (int32_t)(own >> 32);
+  const uint32_t req = (uint32_t)own;
+  // [L, R): the widest range around i whose inner lcps are >= s
+  const bool shared = valid && s >= threshold;
+  // the node of depth D = lcp[i] > 0 is counted once, at its leftmost inner
+  // position: the previous position with lcp <= D must have lcp < D (its R is
+  // only used then)
+  const int32_t D = i >= 1 ? lcp_i : 0;
+  const bool node = cl.on && valid && D > 0;
+  int32_t cut = 0;
+  bool warm = true;
+  if (cl.on) {
+    cut = min(cl.theta, (int32_t)el[ic].len);
+    warm = cl.h == nullptr || cl.h[req] > cl.tau;
+  }
+  const bool sect = cl.on && valid && cut > 0;
+  OpenPair a{}, b{}, c{};
+  if (cl.on) {
+    a = open_pair(ib1, stride, n, ic, max(s, 1), ic + 1, max(s, 1));
+    b = open_pair(ib1, stride, n, max(ic - 1, 0), max(D, 0) + 1, ic + 1, max(D, 1));
+    c.L = last_below(ib1, stride, ic & ~63, ic, max(cut, 1));
+    c.sL = max(cut, 1);
+    c.pl = (ic >> 6) - 1;
+    c.needL = sect && c.L < (ic & ~63);
+  } else if (shared) {
+    a = open_pair(ib1, stride, n, ic, s, ic + 1, s);
+  }
+  a.needL &= shared;
+  a.needR &= shared;
+  b.needL &= node;
+  b.needR &= node;
+  // a range that leaves no block needs no index
+  const auto ix = make(__syncthreads_or(a.needL | a.needR | b.needL | b.needR | c.needL) != 0);
+  if (a.needL | a.needR) locate_pair(a, ix.blocks);
+  if (b.needL | b.needR) locate_pair(b, ix.blocks);
+  if (c.needL) locate_pair(c, ix.blocks);
+  if (__ballot(a.needL | a.needR | b.needL | b.needR | c.needL) != 0) {
+    // sides that stay at home search block 0
+    if (!a.needL) a.pl = 0;
+    if (!a.needR) a.pr = 0;
+    close_pair(a, ib1, stride, n);
+    if (cl.on) {
+      if (!b.needL) b.pl = 0;
+      if (!b.needR) b.pr = 0;
+      if (!c.needL) c.pl = 0;
+      close_pair(b, ib1, stride, n);
+      const int32_t l2 = last_below(ib1, stride, c.pl << 6, min((c.pl << 6) + 63, n), c.sL);
+      if (c.needL) c.L = l2;
     }
   }
+  if (valid && !shared) {
+    cid[req] = -1;
+    csz[req] = 1;
+  }
+  if (shared) {
+    // id: minimum of (share, request) over [L, R)
+    cid[req] = (int32_t)(uint32_t)ix.key_min(a.L, a.R - 1);
+    csz[req] = a.R - a.L;
+  }
   if (!cl.on) return;
+  if (node) {
+    const int32_t lL = lcp[b.L];
+    if (lL < D) {
+      const int64_t wgt = (int64_t)(b.R - b.L) * (D - max(lL, lcp[b.R]));
+      atomicAdd((unsigned long long*)&cl.diff[b.L], (unsigned long long)wgt);
+      atomicAdd((unsigned long long*)&cl.diff[b.R], (unsigned long long)(-wgt));
+    }
+  }
   int32_t start = 0, cold = INT32_MAX;
   if (valid) {
-    // the node of depth D = lcp[i] > 0 is counted once, at its leftmost
-    // inner position: the previous position with lcp <= D must have lcp < D
-    const int32_t D = i >= 1 ? lcp_i : 0;
-    if (D > 0) {
-      int32_t L, R;   // R is only used when L is the node's leftmost position
-      ix.pair_from(i - 1, D + 1, i + 1, D, L, R);
-      const int32_t lL = lcp[L];
-      if (lL < D) {
-        const int64_t wgt = (int64_t)(R - L) * (D - max(lL, lcp[R]));
-        atomicAdd((unsigned long long*)&cl.diff[L], (unsigned long long)wgt);
-        atomicAdd((unsigned long long*)&cl.diff[R], (unsigned long long)(-wgt));
-      }
-    }
-    const int32_t len = (int32_t)el[i].len;
-    const int32_t cut = min(cl.theta, len);
-    start = cut <= 0 ? 0 : ix.last_below_from(i, cut);
+    start = sect ? c.L : 0;
     cl.run[i] = start;
-    if (cl.h != nullptr && cl.h[req] <= cl.tau) cold = (int32_t)req;
+    if (!warm) cold = (int32_t)req;
   }
   // The smallest cold request of each run: a minimum over the wavefront's
   // lanes of equal run start first, then one atomic per run and wavefront
@@ -1802,25 +1900,28 @@ struct IndexArgs {
   __device__ __forceinline__ LcpIndex<TableBlocks> tables() const {
     return LcpIndex<TableBlocks>{ib1, ib2, stride, n, TableBlocks{st1, st2, nb1, nb2, levels}};
   }
-  __device__ __forceinline__ LcpIndex<LdsIndexBlocks> lds(BlockLds& S) const {
-    load_blocks(S, st1, st2, nb1, nb2);
+  __device__ __forceinline__ LcpIndex<LdsIndexBlocks> lds(BlockLds& S, const BlockLoads& loads, bool build) const {
+    if (build) build_blocks(S, loads, nb1);
     return LcpIndex<LdsIndexBlocks>{ib1, ib2, stride, n, LdsIndexBlocks{&S, nb1}};
   }
 };
 
 template <bool kLds>
-__global__ __launch_bounds__(256) void k_final_query(int32_t n, int32_t threshold, const uint64_t* __restrict__ key2,
-                                                    const int32_t* __restrict__ lcp, const ClElem* __restrict__ el,
-                                                    IndexArgs ix, int32_t* __restrict__ cid, int32_t* __restrict__ csz,
-                                                    ClpmArgs cl) {
+__global__ __launch_bounds__(kIndexThreads) void k_final_query(int32_t n, int32_t threshold,
+                                                              const uint64_t* __restrict__ key2,
+                                                              const int32_t* __restrict__ lcp,
+                                                              const ClElem* __restrict__ el, IndexArgs ix,
+                                                              int32_t* __restrict__ cid, int32_t* __restrict__ csz,
+                                                              ClpmArgs cl) {
   const int32_t i = (int32_t)(blockIdx.x * blockDim.x + threadIdx.x);
-  const uint64_t own = key2[min(i, n - 1)];
-  const int32_t lcp_i = lcp[min(i, n)];
   if constexpr (kLds) {
     __shared__ BlockLds S;
-    final_query(i, n, threshold, own, lcp_i, lcp, el, ix.lds(S), cid, csz, cl);
+    BlockLoads loads;
+    loads.fetch(ix.st1, ix.st2, ix.nb1, ix.nb2);
+    final_query(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool any) { return ix.lds(S, loads, any); }, cid,
+                csz, cl);
   } else {
-    final_query(i, n, threshold, own, lcp_i, lcp, el, ix.tables(), cid, csz, cl);
+    final_query(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool) { return ix.tables(); }, cid, csz, cl);
   }
 }
 
@@ -2070,7 +2171,7 @@ __device__ __forceinline__ void small_final(const SmallArgs& A, SmallLds& S) {
     __syncthreads();
   }
   const LcpIndex<TableBlocks> ix{S.ib1, S.ib2, stride, n, TableBlocks{S.st1, S.st2, nb1, nb2, levels}};
-  final_query(t, n, A.threshold, S.key2[t], S.lcp[t], S.lcp, S.el, ix, A.cid, A.csz, cl);
+  final_query(t, n, A.threshold, S.key2, S.lcp, S.el, S.ib1, stride, [&](bool) { return ix; }, A.cid, A.csz, cl);
   if (!cl.on) return;
   __syncthreads();
   // cLPM's score and section (k_clpm_scan and k_clpm_score in one)
@@ -2320,11 +2421,13 @@ struct OffSource {
 // searches) made that pass the longest of the sort; on their own they run
 // one chain per thread (offline order 4-6 us faster on the workload queues).
 template <bool kLds>
-__global__ __launch_bounds__(256) void k_off_make(OffArgs a, OffElem* __restrict__ out, int64_t np) {
+__global__ __launch_bounds__(kIndexThreads) void k_off_make(OffArgs a, OffElem* __restrict__ out, int64_t np) {
   const int64_t j = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if constexpr (kLds) {
     __shared__ BlockLds S;
-    const OffSource<LcpIndex<LdsIndexBlocks>> src{a, a.ix.lds(S)};
+    BlockLoads loads;
+    loads.fetch(a.ix.st1, a.ix.st2, a.ix.nb1, a.ix.nb2);
+    const OffSource<LcpIndex<LdsIndexBlocks>> src{a, a.ix.lds(S, loads, true)};
     if (j < np) out[j] = src((size_t)j);
   } else {
     const OffSource<LcpIndex<TableBlocks>> src{a, a.ix.tables()};

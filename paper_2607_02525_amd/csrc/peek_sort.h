@@ -85,19 +85,18 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_sort(Src src, T* __restri
 // ---------------------------------------------------------------- by buckets
 // Samples are jittered (one hashed place in each of S equal stretches of the
 // input), so a bucket's size depends on the hash and not on how the input is
-// laid out. With 2 samples to a bucket (65,536 elements, 512 buckets) one over
-// 16 times the mean has odds of about 1e-12, with 4 (131,072 elements) one
-// over 8 times of 1e-10. A bucket that is larger all the same (an input made
+// laid out. With 4 samples to a bucket one over 8 times the mean has odds of
+// about 1e-10. A bucket that is larger all the same (an input made
 // for it) is ordered in global memory.
 // All three launches are bound by chains of dependent accesses and by the
 // comparisons in LDS; 24-byte keys, us (merge sort / sample + scatter +
 // bucket sort): 4500 elements 31 / 12.4, 16,384 36 / 14.5, 65,536 52 / 17 to
 // 24 (random keys; a queue's 19).
-// 2048 samples instead of 1024 cost 2 us more up to 65,536 elements, and
-// above they save as much in smaller buckets.
+// 2048 samples instead of 1024 cost 2 us more; from 65,536 elements (512
+// buckets) on they save 6 us in smaller buckets on a mixed queue.
 constexpr int64_t kSampleMax = int64_t(1) << 17;
 constexpr int32_t kFewSamples = 1024, kManySamples = 2048;
-constexpr int32_t kFewSamplesMax = 65536;   // elements
+constexpr int32_t kFewSamplesMax = 65535;   // elements: four samples to a bucket
 constexpr int kMaxBuckets = 512;
 constexpr int kBucketMax = 2048;      // elements a bucket's workgroup orders in LDS
 constexpr int kCountPad = 16;         // a bucket's counter has a 64-byte line of its own

@@ -1,6 +1,6 @@
 """The cluster and offline sorts at the sizes where they change form: up to 4096
-elements an element's place is counted, up to 131072 (samples: 1024 up to 65536,
-2048 above) buckets are ordered on their own, beyond that they are merged. The
+elements an element's place is counted, up to 131072 (samples: 1024 below 65536,
+2048 from there) buckets are ordered on their own, beyond that they are merged. The
 cluster sort has one element per request, the offline sort two. Outputs are whole
 numbers and must equal the oracle's. A queue whose sampled requests all sort last
 leaves every other request in the first bucket, which then does not fit LDS."""
@@ -42,7 +42,7 @@ def short_queue(n, seed, samples_last=False):
 
 @pytest.mark.parametrize("n,samples_last", [(1, False), (63, False), (64, False), (513, False), (1024, False),
                                             (1025, False), (2048, False), (2049, False), (4096, False), (4097, False),
-                                            (16385, False), (32769, False), (65536, False), (65537, False),
+                                            (16385, False), (32769, False), (65536, False), (65535, False), (65537, False),
                                             (8191, True), (40000, True)])
 def test_sorts_at_every_form(n, samples_last):
     w = short_queue(n, 3, samples_last)
