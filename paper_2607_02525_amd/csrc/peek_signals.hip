@@ -1927,34 +1927,92 @@ __global__ __launch_bounds__(kIndexThreads) void k_final_query(int32_t n, int32_
 
 constexpr int kScanThreads = 1024;
 
-// Inclusive block scan of diff (kScanThreads positions per block) into
-// `local` with the block totals in cl.part; also the section of every
-// position (its run's pioneer is known once the query kernel is done).
-__global__ __launch_bounds__(kScanThreads) void k_clpm_scan(int32_t n, const uint64_t* __restrict__ key2,
-                                                            int64_t* __restrict__ local, ClpmArgs cl) {
-  __shared__ int64_t wsum[kScanThreads / kWave];
-  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  const int32_t i = (int32_t)blockIdx.x * kScanThreads + t;
-  int64_t v = i < n ? cl.diff[i] : 0;
+// Inclusive scan of v over the workgroup's threads (kScanThreads); wsum: a word
+// per wavefront. Ends without a barrier after its reads of wsum.
+__device__ __forceinline__ int64_t scan_threads(int64_t v, int64_t* wsum) {
+  const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x / kWave;
   for (int d = 1; d < kWave; d <<= 1) {
     const int64_t o = __shfl(v, lane >= d ? lane - d : lane);
     if (lane >= d) v += o;
   }
   if (lane == kWave - 1) wsum[wave] = v;
   __syncthreads();
-  int64_t before = 0;
-  for (int w = 0; w < wave; ++w) before += wsum[w];
-  v += before;
-  if (i < n) local[i] = v;
-  if (t == kScanThreads - 1) cl.part[blockIdx.x] = v;
-  if (i < n && cl.section != nullptr) {
-    const uint32_t req = (uint32_t)key2[i];
-    cl.section[req] = cl.h[req] > cl.tau ? 0 : (cl.pmin[cl.run[i]] == (int32_t)req ? 1 : 2);
-  }
+  for (int w = 0; w < wave; ++w) v += wsum[w];
+  return v;
+}
+
+__device__ __forceinline__ int64_t wave_sum(int64_t v) {
+  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  return v;
+}
+
+// Whether the request of sorted position i is warm (0), its run's pioneer (1)
+// or another cold one (2): the run's pioneer is known once the query kernel is
+// done.
+__device__ __forceinline__ int32_t section_of(int32_t i, uint32_t req, const ClpmArgs& cl) {
+  return cl.h[req] > cl.tau ? 0 : (cl.pmin[cl.run[i]] == (int32_t)req ? 1 : 2);
 }
 
 // score = own leaf (len - share when positive) + every node above it:
 // the prefix sum of diff up to the position.
+__device__ __forceinline__ int64_t own_leaf(uint64_t k2, uint32_t len) {
+  const int64_t share = (int64_t)(k2 >> 32);
+  return (int64_t)len > share ? (int64_t)len - share : 0;
+}
+
+// Elements before a workgroup's that its threads load at once (indices
+// clamped): a loop of single loads would wait for each.
+constexpr int kBeforeLoads = 8;
+
+// Score and section in one launch: a workgroup sums all of diff before its
+// positions itself, which takes less than a launch as long as that is little.
+// 8192 requests: 5.5 us, where the two launches below take 9.6 at 65,536 and
+// one more gap (whole call 150.0 -> 148.3 us; a cycle of 19,997 216.5 -> 215.7).
+constexpr int32_t kClpmWhole = 32768;   // requests
+
+__global__ __launch_bounds__(kScanThreads) void k_clpm_whole(int32_t n, const uint64_t* __restrict__ key2,
+                                                             const ClElem* __restrict__ el, ClpmArgs cl) {
+  __shared__ int64_t wsum[kScanThreads / kWave], red[kScanThreads / kWave];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int32_t base = (int32_t)blockIdx.x * kScanThreads, i = base + t, ic = min(i, n - 1);
+  const int64_t own = cl.diff[ic];
+  const uint64_t k2 = key2[ic];
+  const uint32_t len = el[ic].len;
+  int64_t before = 0;
+  for (int32_t b = 0; b < base; b += kBeforeLoads * kScanThreads) {
+    int64_t x[kBeforeLoads];
+#pragma unroll
+    for (int q = 0; q < kBeforeLoads; ++q) x[q] = cl.diff[min(b + q * kScanThreads, base - kScanThreads) + t];
+#pragma unroll
+    for (int q = 0; q < kBeforeLoads; ++q) before += b + q * kScanThreads < base ? x[q] : 0;
+  }
+  const int32_t section = cl.section != nullptr ? section_of(ic, (uint32_t)k2, cl) : 0;
+  before = wave_sum(before);
+  if (lane == 0) red[wave] = before;
+  int64_t v = scan_threads(i < n ? own : 0, wsum);
+  for (int w = 0; w < kScanThreads / kWave; ++w) v += red[w];
+  if (i >= n) return;
+  if (cl.score != nullptr) cl.score[(uint32_t)k2] = own_leaf(k2, len) + v;
+  if (cl.section != nullptr) cl.section[(uint32_t)k2] = section;
+}
+
+// Longer queues take two: an inclusive block scan of diff (kScanThreads
+// positions per block) into `local` with the block totals in cl.part, and the
+// sections; then the scores.
+__global__ __launch_bounds__(kScanThreads) void k_clpm_scan(int32_t n, const uint64_t* __restrict__ key2,
+                                                            int64_t* __restrict__ local, ClpmArgs cl) {
+  __shared__ int64_t wsum[kScanThreads / kWave];
+  const int t = threadIdx.x;
+  const int32_t i = (int32_t)blockIdx.x * kScanThreads + t;
+  const int64_t v = scan_threads(i < n ? cl.diff[i] : 0, wsum);
+  if (i < n) local[i] = v;
+  if (t == kScanThreads - 1) cl.part[blockIdx.x] = v;
+  if (i < n && cl.section != nullptr) {
+    const uint32_t req = (uint32_t)key2[i];
+    cl.section[req] = section_of(i, req, cl);
+  }
+}
+
 __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const uint64_t* __restrict__ key2,
                                                              const ClElem* __restrict__ el,
                                                              const int64_t* __restrict__ local, ClpmArgs cl) {
@@ -1962,7 +2020,7 @@ __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const ui
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
   int64_t v = 0;
   for (int32_t b = t; b < (int32_t)blockIdx.x; b += kScanThreads) v += cl.part[b];
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
+  v = wave_sum(v);
   if (lane == 0) red[wave] = v;
   __syncthreads();
   int64_t offset = 0;
@@ -1970,10 +2028,7 @@ __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const ui
   const int32_t i = (int32_t)blockIdx.x * kScanThreads + t;
   if (i >= n || cl.score == nullptr) return;
   const uint64_t k2 = key2[i];
-  const uint32_t req = (uint32_t)k2;
-  const int64_t share = (int64_t)(k2 >> 32);
-  const int64_t len = el[i].len;
-  cl.score[req] = (len > share ? len - share : 0) + offset + local[i];
+  cl.score[(uint32_t)k2] = own_leaf(k2, el[i].len) + offset + local[i];
 }
 
 // ---------------------------------------------------------------- small queues
@@ -2174,7 +2229,7 @@ __device__ __forceinline__ void small_final(const SmallArgs& A, SmallLds& S) {
   final_query(t, n, A.threshold, S.key2, S.lcp, S.el, S.ib1, stride, [&](bool) { return ix; }, A.cid, A.csz, cl);
   if (!cl.on) return;
   __syncthreads();
-  // cLPM's score and section (k_clpm_scan and k_clpm_score in one)
+  // cLPM's score and section (as k_clpm_whole)
   int64_t x = t < n ? S.diff[t] : 0;
   for (int d = 1; d < kWave; d <<= 1) {
     const int64_t o = __shfl(x, lane >= d ? lane - d : lane);
@@ -2439,60 +2494,78 @@ __device__ __forceinline__ int64_t off_size(const OffElem& e, int32_t n) {
   return e.node == INT32_MAX ? 0 : (e.k1 == 0 ? 1 : (int64_t)n + 1 - e.k1);
 }
 
-// Inclusive block scan of piece sizes (kScanThreads pieces per block) into
-// `local`, block totals into `part`.
-__global__ __launch_bounds__(kScanThreads) void k_off_scan(int32_t m, int32_t n, const OffElem* __restrict__ el,
-                                                           int64_t* __restrict__ local, int64_t* __restrict__ part) {
-  __shared__ int64_t wsum[kScanThreads / kWave];
-  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  const int32_t j = (int32_t)blockIdx.x * kScanThreads + t;
-  int64_t v = j < m ? off_size(el[j], n) : 0;
-  for (int d = 1; d < kWave; d <<= 1) {
-    const int64_t o = __shfl(v, lane >= d ? lane - d : lane);
-    if (lane >= d) v += o;
-  }
-  if (lane == kWave - 1) wsum[wave] = v;
-  __syncthreads();
-  int64_t before = 0;
-  for (int w = 0; w < wave; ++w) before += wsum[w];
-  v += before;
-  if (j < m) local[j] = v;
-  if (t == kScanThreads - 1) part[blockIdx.x] = v;
-}
-
-// Exclusive prefix of piece sizes; the first piece of each node records the
-// prefix at its node's start in `base` (indexed by node).
-__global__ __launch_bounds__(kScanThreads) void k_off_prefix(int32_t m, int32_t n, const OffElem* __restrict__ el,
-                                                             int64_t* __restrict__ local,
-                                                             const int64_t* __restrict__ part,
-                                                             int64_t* __restrict__ base) {
+// What the last node of every workgroup's pieces (kScanThreads of them, all
+// but the last workgroup's) has among them.
+__global__ __launch_bounds__(kScanThreads) void k_off_tails(int32_t n, const OffElem* __restrict__ el,
+                                                            int64_t* __restrict__ tail) {
   __shared__ int64_t red[kScanThreads / kWave];
-  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
-  int64_t v = 0;
-  for (int32_t b = t; b < (int32_t)blockIdx.x; b += kScanThreads) v += part[b];
-  for (int off = kWave / 2; off > 0; off >>= 1) v += __shfl_xor(v, off);
-  if (lane == 0) red[wave] = v;
+  const int t = threadIdx.x;
+  const int32_t base = (int32_t)blockIdx.x * kScanThreads;
+  const int32_t node = el[base + kScanThreads - 1].node;
+  const OffElem e = el[base + t];
+  const int64_t v = wave_sum(e.node == node ? off_size(e, n) : 0);
+  if ((t & (kWave - 1)) == 0) red[t / kWave] = v;
   __syncthreads();
-  int64_t offset = 0;
-  for (int w = 0; w < kScanThreads / kWave; ++w) offset += red[w];
-  const int32_t j = (int32_t)blockIdx.x * kScanThreads + t;
-  if (j >= m) return;
-  const OffElem e = el[j];
-  if (e.node == INT32_MAX) return;
-  const int64_t ex = offset + local[j] - off_size(e, n);
-  local[j] = ex;
-  if (j == 0 || el[j - 1].node != e.node) base[e.node] = ex;
+  if (t > 0) return;
+  int64_t sum = 0;
+  for (int w = 0; w < kScanThreads / kWave; ++w) sum += red[w];
+  tail[blockIdx.x] = sum;
 }
 
-// Offset of every piece inside its node, to its owner.
-__global__ void k_off_scatter(int32_t m, const OffElem* __restrict__ el, const int64_t* __restrict__ ex,
-                              const int64_t* __restrict__ base, int64_t* __restrict__ start,
-                              int64_t* __restrict__ roff) {
-  const int32_t j = blockIdx.x * blockDim.x + threadIdx.x;
-  if (j >= m) return;
-  const OffElem e = el[j];
-  if (e.node == INT32_MAX) return;
-  const int64_t off = ex[j] - base[e.node];
+// Offset of every piece inside its node, to its owner: the sizes of the
+// node's pieces before it. Pieces are ordered by node, so of the pieces before
+// a workgroup's only those of its first piece's node matter. Up to kOffWhole
+// pieces a workgroup looks at all of them itself (kWhole), which takes less
+// than a launch; beyond, each earlier workgroup's share is its tail, if its
+// last piece is of that node. The prefix of all sizes and each node's place in
+// it took three launches; with these and the last jumps taken by the placement
+// the order of 5000 requests went from 78.9 to 75.2 us, of 65,536 from 158.7
+// to 156.0.
+constexpr int32_t kOffWhole = 16384;   // pieces, two for each request
+
+template <bool kWhole>
+__global__ __launch_bounds__(kScanThreads) void k_off_offsets(int32_t m, int32_t n, const OffElem* __restrict__ el,
+                                                              const int64_t* __restrict__ tail,
+                                                              int64_t* __restrict__ start, int64_t* __restrict__ roff) {
+  constexpr int kWaves = kScanThreads / kWave;
+  __shared__ int64_t wsum[kWaves], whead[kWaves], red[kWaves];
+  const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
+  const int32_t base = (int32_t)blockIdx.x * kScanThreads, j = base + t, jc = min(j, m - 1);
+  const int32_t node0 = el[base].node;
+  const OffElem e = el[jc];
+  const int32_t left = el[max(jc - 1, 0)].node;
+  int64_t before = 0;
+  if constexpr (kWhole) {
+    for (int32_t b = 0; b < base; b += kBeforeLoads * kScanThreads) {
+      OffElem o[kBeforeLoads];
+#pragma unroll
+      for (int q = 0; q < kBeforeLoads; ++q) o[q] = el[min(b + q * kScanThreads, base - kScanThreads) + t];
+#pragma unroll
+      for (int q = 0; q < kBeforeLoads; ++q)
+        before += b + q * kScanThreads < base && o[q].node == node0 ? off_size(o[q], n) : 0;
+    }
+  } else {
+    for (int32_t b = t; b < (int32_t)blockIdx.x; b += kScanThreads)
+      before += el[(b + 1) * kScanThreads - 1].node == node0 ? tail[b] : 0;
+  }
+  before = wave_sum(before);
+  if (lane == 0) red[wave] = before;
+  const int64_t size = j < m ? off_size(e, n) : 0;
+  const int64_t ex = scan_threads(size, wsum) - size;
+  // prefixes never decrease: the largest at a node's first piece so far is
+  // that of this piece's node
+  int64_t first = t == 0 || left != e.node ? ex : 0;
+  for (int d = 1; d < kWave; d <<= 1) {
+    const int64_t o = __shfl(first, lane >= d ? lane - d : lane);
+    first = max(first, o);
+  }
+  if (lane == kWave - 1) whead[wave] = first;
+  __syncthreads();
+  for (int w = 0; w < wave; ++w) first = max(first, whead[w]);
+  if (j >= m || e.node == INT32_MAX) return;
+  int64_t off = ex - first;
+  if (e.node == node0)
+    for (int w = 0; w < kWaves; ++w) off += red[w];
   if (e.owner > 0)
     start[e.owner] = off;
   else
@@ -2522,17 +2595,27 @@ __global__ void k_off_jump(int32_t n, const int64_t* __restrict__ A, const int32
   P2[c] = p;
 }
 
-// perm[start of the request's node + its offset] = request.
+// perm[start of the request's node + its offset] = request. The last round of
+// jumps is taken here, for each request's own node.
 __global__ void k_off_place(int32_t n, const ClElem* __restrict__ el, const int32_t* __restrict__ rnode,
-                            const int64_t* __restrict__ roff, const int64_t* __restrict__ start,
-                            int32_t* __restrict__ perm) {
+                            const int64_t* __restrict__ roff, const int64_t* __restrict__ A,
+                            const int32_t* __restrict__ P, int32_t* __restrict__ perm) {
   const int32_t i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   if (n == 1) {
     perm[0] = (int32_t)el[0].req;
     return;
   }
-  const int64_t pos = start[rnode[i]] + roff[i];
+  int32_t p = rnode[i];
+  int64_t pos = roff[i] + A[p];
+  p = P[p];
+#pragma unroll
+  for (int q = 1; q < kJump; ++q) {
+    if (p >= 0) {
+      pos += A[p];
+      p = P[p];
+    }
+  }
   if (pos >= 0 && pos < n) perm[pos] = (int32_t)el[i].req;   // always in range; the check guards the caller's buffer
 }
 
@@ -2557,7 +2640,7 @@ struct Layout {
       keys_b, prefix, keyed, diff, pmin, run, local, part, sharing, anc_a, anc_b, hrep, hbest, hmulti, hslot, hcap,
       head, tact, tdep, tsize, total, flags_bytes;
   // PEEK-offline Phase 1 only
-  size_t oel_a, oel_b, olocal, opart, obase, start_a, start_b, npar_a, npar_b, rnode, roff, onp;
+  size_t oel_a, oel_b, otail, start_a, start_b, npar_a, npar_b, rnode, roff, onp;
   int64_t ib_stride;
   int32_t nb1, nb2;
   int levels;
@@ -2620,9 +2703,7 @@ Layout layout(int32_t n, int64_t num_nodes, bool offline = false) {
     L.onp = onp;
     L.oel_a = take(sizeof(OffElem) * onp);
     L.oel_b = take(sizeof(OffElem) * onp);
-    L.olocal = take(sizeof(int64_t) * m2);
-    L.opart = take(sizeof(int64_t) * ((m2 + kScanThreads - 1) / kScanThreads + 1));
-    L.obase = take(sizeof(int64_t) * nn);
+    L.otail = take(sizeof(int64_t) * ((m2 + kScanThreads - 1) / kScanThreads));
     L.start_a = take(sizeof(int64_t) * nn);
     L.start_b = take(sizeof(int64_t) * nn);
     L.npar_a = take(sizeof(int32_t) * nn);
@@ -2870,23 +2951,26 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
       const OffElem* sorted =
           msort::sort_distinct(msort::FromArray<OffElem>{oel}, oel, (OffElem*)(w + L.oel_b), m2, L.onp,
                                OffElem{INT32_MAX, INT32_MAX, INT32_MAX, 0}, OffLess{}, sort_ws, sort_ws_bytes, st);
-      int64_t* olocal = (int64_t*)(w + L.olocal);
-      int64_t* opart = (int64_t*)(w + L.opart);
-      int64_t* obase = (int64_t*)(w + L.obase);
+      int64_t* tail = (int64_t*)(w + L.otail);
       const unsigned sb = blocks_for(m2, kScanThreads);
-      hipLaunchKernelGGL(k_off_scan, dim3(sb), dim3(kScanThreads), 0, st, m2, n, sorted, olocal, opart);
-      hipLaunchKernelGGL(k_off_prefix, dim3(sb), dim3(kScanThreads), 0, st, m2, n, sorted, olocal, opart, obase);
-      hipLaunchKernelGGL(k_off_scatter, dim3(blocks_for(m2)), dim3(256), 0, st, m2, sorted, olocal, obase, start[0],
-                         roff);
-      // a node's chain to the top has at most min(D, n) + 1 links
+      if (m2 <= kOffWhole) {
+        hipLaunchKernelGGL(k_off_offsets<true>, dim3(sb), dim3(kScanThreads), 0, st, m2, n, sorted, tail, start[0],
+                           roff);
+      } else {
+        hipLaunchKernelGGL(k_off_tails, dim3(sb - 1), dim3(kScanThreads), 0, st, n, sorted, tail);
+        hipLaunchKernelGGL(k_off_offsets<false>, dim3(sb), dim3(kScanThreads), 0, st, m2, n, sorted, tail, start[0],
+                           roff);
+      }
+      // a node's chain to the top has at most min(D, n) + 1 links; the placement takes the last kJump
       const int64_t links = (int64_t)std::min(off->depth_limit, n) + 2;
-      for (int64_t span = 1; span < links; span *= kJump) {
+      for (int64_t span = kJump; span < links; span *= kJump) {
         hipLaunchKernelGGL(k_off_jump, dim3(blocks_for(n)), dim3(256), 0, st, n, start[pc], npar[pc],
                            start[pc ^ 1], npar[pc ^ 1]);
         pc ^= 1;
       }
     }
-    hipLaunchKernelGGL(k_off_place, dim3(blocks_for(n)), dim3(256), 0, st, n, el, rnode, roff, start[pc], off->perm);
+    hipLaunchKernelGGL(k_off_place, dim3(blocks_for(n)), dim3(256), 0, st, n, el, rnode, roff, start[pc], npar[pc],
+                       off->perm);
   } else {
     if (lds_blocks)
       hipLaunchKernelGGL(k_final_query<true>, dim3(blocks_for(n)), dim3(256), 0, st, n, threshold, key2, lcp, el, ix,
@@ -2896,9 +2980,14 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
                          cid, csz, cl);
     if (cl.on) {
       const unsigned sb = blocks_for(n, kScanThreads);
-      hipLaunchKernelGGL(k_clpm_scan, dim3(sb), dim3(kScanThreads), 0, st, n, key2, local, cl);
-      if (cl.score != nullptr)
-        hipLaunchKernelGGL(k_clpm_score, dim3(sb), dim3(kScanThreads), 0, st, n, key2, el, local, cl);
+      if (n <= kClpmWhole) {
+        if (cl.score != nullptr || cl.section != nullptr)
+          hipLaunchKernelGGL(k_clpm_whole, dim3(sb), dim3(kScanThreads), 0, st, n, key2, el, cl);
+      } else {
+        hipLaunchKernelGGL(k_clpm_scan, dim3(sb), dim3(kScanThreads), 0, st, n, key2, local, cl);
+        if (cl.score != nullptr)
+          hipLaunchKernelGGL(k_clpm_score, dim3(sb), dim3(kScanThreads), 0, st, n, key2, el, local, cl);
+      }
     }
   }
   PEEK_HIP_TRY(hipGetLastError());

@@ -36,7 +36,7 @@ struct FromArray {
 // ---------------------------------------------------------------- by rank
 // Bound by the comparisons, n^2 / 64 of them per launch. 1024 elements take
 // 3.1 us (the merge sort: 13.5), 2048 6.6 us (18.5), 4096 12.2 us (25); the
-// bucket sort takes 12.4 us there, so the line lies at 4096. Above 2048
+// bucket sort takes 12.4 us there, so the line lies at 4096. Above 1024
 // elements a wavefront counts for two of them at once, which halves the LDS
 // reads; four at once left one wavefront per SIMD and took 15.9 us at 4096.
 constexpr int kRankMax = 4096;
@@ -521,8 +521,6 @@ T* sort_distinct(Src src, T* a, T* b, int32_t n, size_t np, T pad, Less less, vo
     // elements per wavefront: 1024 wavefronts (one per SIMD) are enough
     if (n <= 1024)
       hipLaunchKernelGGL((k_rank_sort<1, T, Less, Src>), grid(1), dim3(kRankThreads), 0, st, src, b, n, less);
-    else if (n <= 2048)
-      hipLaunchKernelGGL((k_rank_sort<2, T, Less, Src>), grid(2), dim3(kRankThreads), 0, st, src, b, n, less);
     else
       hipLaunchKernelGGL((k_rank_sort<2, T, Less, Src>), grid(2), dim3(kRankThreads), 0, st, src, b, n, less);
     return b;
