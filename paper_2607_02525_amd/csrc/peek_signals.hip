@@ -439,6 +439,14 @@ struct AncLess {
   __device__ __forceinline__ bool operator()(const AncElem& a, const AncElem& b) const {
     return (a.hi < b.hi) | ((a.hi == b.hi) & ((a.mid < b.mid) | ((a.mid == b.mid) & (a.lo < b.lo))));
   }
+  // the lanes on which a < b: the key as one 192-bit number
+  __device__ __forceinline__ uint64_t lanes(const AncElem& a, const AncElem& b) const {
+    const uint32_t x[6] = {(uint32_t)a.lo,          (uint32_t)(a.lo >> 32), (uint32_t)a.mid,
+                           (uint32_t)(a.mid >> 32), (uint32_t)a.hi,         (uint32_t)(a.hi >> 32)};
+    const uint32_t y[6] = {(uint32_t)b.lo,          (uint32_t)(b.lo >> 32), (uint32_t)b.mid,
+                           (uint32_t)(b.mid >> 32), (uint32_t)b.hi,         (uint32_t)(b.hi >> 32)};
+    return msort::borrow_lanes(x, y);
+  }
 };
 // the compare's output as the sort's input, padded past n with keys that sort last
 struct AncSrc {
@@ -2400,6 +2408,12 @@ struct OffElem {
 struct OffLess {   // branch-free, as AncLess
   __device__ __forceinline__ bool operator()(const OffElem& a, const OffElem& b) const {
     return (a.node < b.node) | ((a.node == b.node) & ((a.k1 < b.k1) | ((a.k1 == b.k1) & (a.k2 < b.k2))));
+  }
+  // the lanes on which a < b (no field is negative)
+  __device__ __forceinline__ uint64_t lanes(const OffElem& a, const OffElem& b) const {
+    const uint32_t x[3] = {(uint32_t)a.k2, (uint32_t)a.k1, (uint32_t)a.node};
+    const uint32_t y[3] = {(uint32_t)b.k2, (uint32_t)b.k1, (uint32_t)b.node};
+    return msort::borrow_lanes(x, y);
   }
 };
 

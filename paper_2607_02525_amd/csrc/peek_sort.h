@@ -33,6 +33,49 @@ struct FromArray {
   __device__ __forceinline__ T operator()(size_t i) const { return p[i]; }
 };
 
+// The lanes on which x < y, numbers of N 32-bit words, lowest first: the borrow
+// of their difference, a word an instruction, which is the mask that counting
+// wants. Compares of 64-bit words run at a fraction of the rate, and the mask of
+// a combined result costs two more instructions. An instruction that reads a
+// mask follows the one that wrote it by two wait states. With the counted sort's
+// LDS reads four ahead: 4096 document prompts 13.1 -> 11.9 us (12.3 without
+// those), ranking 1024 samples 4.6 -> 4.1.
+__device__ __forceinline__ uint64_t borrow_lanes(const uint32_t (&x)[3], const uint32_t (&y)[3]) {
+  uint64_t m;
+  uint32_t d;
+  asm("v_sub_co_u32 %1, vcc, %2, %5\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %3, %6, vcc\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %4, %7, vcc\n\t"
+      "s_mov_b64 %0, vcc"
+      : "=s"(m), "=&v"(d)
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(y[0]), "v"(y[1]), "v"(y[2])
+      : "vcc");
+  return m;
+}
+__device__ __forceinline__ uint64_t borrow_lanes(const uint32_t (&x)[6], const uint32_t (&y)[6]) {
+  uint64_t m;
+  uint32_t d;
+  asm("v_sub_co_u32 %1, vcc, %2, %8\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %3, %9, vcc\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %4, %10, vcc\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %5, %11, vcc\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %6, %12, vcc\n\t"
+      "s_nop 1\n\t"
+      "v_subb_co_u32 %1, vcc, %7, %13, vcc\n\t"
+      "s_mov_b64 %0, vcc"
+      : "=s"(m), "=&v"(d)
+      : "v"(x[0]), "v"(x[1]), "v"(x[2]), "v"(x[3]), "v"(x[4]), "v"(x[5]), "v"(y[0]), "v"(y[1]), "v"(y[2]), "v"(y[3]),
+        "v"(y[4]), "v"(y[5])
+      : "vcc");
+  return m;
+}
+
 // ---------------------------------------------------------------- by rank
 // Bound by the comparisons, n^2 / 64 of them per launch. 1024 elements take
 // 3.1 us (the merge sort: 13.5), 2048 6.6 us (18.5), 4096 12.2 us (25); the
@@ -42,7 +85,13 @@ struct FromArray {
 constexpr int kRankMax = 4096;
 constexpr int kRankThreads = 512;
 constexpr int kRankTile = 1024;   // elements staged in LDS at a time
+static_assert(kRankTile % 256 == 0, "read by four wavefronts' widths");
 constexpr int kRankLoads = kRankTile / kRankThreads;
+
+// The lanes 0 .. k - 1.
+__device__ __forceinline__ uint64_t lanes_below(int32_t k) {
+  return k >= 64 ? ~0ull : (1ull << max(k, 0)) - 1;
+}
 
 template <int I, typename T, typename Less, typename Src>
 __global__ __launch_bounds__(kRankThreads) void k_rank_sort(Src src, T* __restrict__ dst, int32_t n, Less less) {
@@ -70,11 +119,18 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_sort(Src src, T* __restri
         next[q] = src((size_t)min(base + kRankTile + q * kRankThreads + t, n - 1));
     }
     const int32_t m = min(kRankTile, n - base);
-    for (int32_t j = 0; j < m; j += 64) {
-      const T e = s[j + lane];
-      const bool in = j + lane < m;
+    // four at a time: with one or two wavefronts to a SIMD each would wait
+    // for its LDS read (the tile is filled to its end)
+    for (int32_t j = 0; j < m; j += 256) {
+      T e[4];
 #pragma unroll
-      for (int q = 0; q < I; ++q) rank[q] += __popcll(__ballot(in & less(e, own[q])));
+      for (int k = 0; k < 4; ++k) e[k] = s[j + 64 * k + lane];
+#pragma unroll
+      for (int k = 0; k < 4; ++k) {
+        const uint64_t in = lanes_below(m - j - 64 * k);   // the lanes within the input
+#pragma unroll
+        for (int q = 0; q < I; ++q) rank[q] += __popcll(in & less.lanes(e[k], own[q]));
+      }
     }
   }
 #pragma unroll
@@ -143,7 +199,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_rank(Src src, T* __re
   const T own = s[(int)blockIdx.x * (kSampleThreads / 64) + t / 64];
   int32_t rank = 0;
 #pragma unroll 4
-  for (int j = 0; j < S; j += 64) rank += __popcll(__ballot(less(s[j + lane], own)));
+  for (int j = 0; j < S; j += 64) rank += __popcll(less.lanes(s[j + lane], own));
   if (lane == 0 && rank != 0 && rank % per == 0) split[rank / per - 1] = own;
 }
 
