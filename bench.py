@@ -403,14 +403,15 @@ def main():
                          "frac": round(b_alg / lpm_avg_s / 1e9 / HBM_PEAK_GBS, 4),
                          "algorithmic_bytes_per_launch": b_alg, "bytes_breakdown": parts,
                          "bytes_from": "oracle outputs"})
-        # sort passes over the queue in one signals call: the first round's
-        # merge sort (a tile pass over 512-element tiles, then merge passes)
-        # and the sort of the second round's segments
-        np2 = 512
-        while np2 < w.n:
-            np2 <<= 1
-        tile = 1024 if np2 >= (1 << 19) else 512   # sorts of 512K elements and up use 1024-element tiles
-        passes = 1 + int(np.log2(np2 // tile)) + 1
+        # sort passes over the queue in one signals call: the first round's sort
+        # (one up to 4096 requests, a scatter and the buckets up to 2^17, then a
+        # merge sort: a tile pass and merge passes) and the sort of the second
+        # round's segments
+        passes = 2 if w.n <= 4096 else 3
+        if w.n > (1 << 17):
+            np2 = 1 << (w.n - 1).bit_length()
+            tile = 1024 if np2 >= (1 << 19) else 512   # sorts of 512K elements and up use 1024-element tiles
+            passes = 1 + int(np.log2(np2 // tile)) + 1
         sb, sparts = signals_algorithmic_bytes(w.lengths.astype(np.int64), oc.share.astype(np.int64),
                                                ol.m.astype(np.int64), hp.num_nodes, passes)
         sig_s = float(sig_ms.mean()) / 1e3
