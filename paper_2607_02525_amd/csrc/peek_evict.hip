@@ -38,8 +38,8 @@
 //     that is left to sort.
 //  5. k_ev_sort: where each segment starts in the victim order. Up to 8192
 //     segments every one is counted against all; more go through stable
-//     least-significant-digit radix passes over 4096-segment tiles, a byte on
-//     which all keys agree being skipped, and a prefix of the run lengths.
+//     least-significant-digit radix passes over tiles, a byte on which all keys
+//     agree being skipped, and a prefix of the run lengths.
 //     All passes are one launch: workgroups take (pass, tile) tickets in
 //     order and a tile waits until the pass before it is complete.
 //  6. k_ev_place: every node to S(K.id) + level(K.id) - level(c).
@@ -275,11 +275,14 @@ constexpr int kMaxDigits = 8;
 constexpr int kRadix = 256;
 
 // Counters::ticket: tickets of the segment kernel and of the sort, then the
-// finished tiles of each radix pass.
+// finished tiles of each radix pass. Each has a 128-byte line of its own:
+// workgroups that wait poll one of them while others add to the next, and on
+// one line they held each other up (65,536 segments 101 -> 87 us).
+constexpr int kCounterPad = 32;
 constexpr int kTicketSegs = 0;
-constexpr int kTicketSort = 1;
-constexpr int kTicketDone = 2;
-constexpr int kTickets = kTicketDone + kMaxDigits;
+constexpr int kTicketSort = kCounterPad;
+constexpr int kTicketDone = 2 * kCounterPad;
+constexpr int kTickets = kTicketDone + kMaxDigits * kCounterPad;
 
 // All of it cleared by k_ev_blocks.
 struct Counters {
@@ -482,8 +485,12 @@ __global__ __launch_bounds__(kKeyThreads) void k_ev_keys(KeyArgs a) {
 
 constexpr int kPThreads = 512;
 constexpr int kPWaves = kPThreads / kWave;
-constexpr int kPItems = 8;
-constexpr int kPTile = kPThreads * kPItems;   // items per tile
+// Segments per thread of a radix tile: few, so that more CUs take part, until
+// the tiles are so many that waiting for the counts of the earlier ones is the
+// longest part (ranking 65,536 distinct scores: 83 us with 2 per thread, 80 with
+// 4, 87 with 8; 131,072: 109, 95, 101).
+constexpr int kFewItems = 4, kManyItems = 8;
+constexpr int32_t kFewSegs = 131072;   // segments
 static_assert(kPThreads == 2 * kRadix, "two threads per digit");
 // Prefix over tiles in two levels: tiles publish their own totals, the last
 // tile of each group of kGrp tiles also publishes the group's total, and a
@@ -556,14 +563,13 @@ __device__ uint64_t sum_published(const uint64_t* st, int64_t stride, int32_t i0
 }
 
 // Exclusive prefix of `own` over the tiles before `tile`. Two callers per
-// value: half 0 publishes the tile's total, sums its group's earlier tiles
-// and, on the group's last tile, publishes the group total; half 1 sums the
-// earlier groups. agg: [tiles] stride-spaced words, grp: [groups] likewise.
+// value: half 0, which has published the tile's total `own`, sums its group's
+// earlier tiles and, on the group's last tile, publishes the group total;
+// half 1 sums the earlier groups. agg: [tiles] stride-spaced words, grp: [groups] likewise.
 __device__ uint64_t two_level_part(uint64_t* agg, uint64_t* grp, int64_t stride, int32_t tile, int32_t tiles,
                                    uint64_t own, int half, uint32_t* err) {
   const int32_t g = tile / kGrp, first = g * kGrp;
   if (half == 0) {
-    publish(&agg[(int64_t)tile * stride], own);
     const uint64_t in = sum_published(agg, stride, first, tile - first, err);
     if (tile == first + kGrp - 1 && tile + 1 < tiles) publish(&grp[(int64_t)g * stride], in + own);
     return in;
@@ -625,11 +631,12 @@ __device__ __forceinline__ uint64_t same_digit(uint32_t dg, uint64_t m) {
 // same digit, and the wave's count per digit (whist_w[d]). Items are blocked
 // per wave (item q of lane l is element base + q*64 + l), so the ranks
 // follow element order.
-__device__ __forceinline__ void wave_rank(const uint32_t (&dg)[kPItems], const bool (&valid)[kPItems],
-                                          uint32_t (&rk)[kPItems], uint32_t* whist_w, int lane) {
+template <int I>
+__device__ __forceinline__ void wave_rank(const uint32_t (&dg)[I], const bool (&valid)[I], uint32_t (&rk)[I],
+                                          uint32_t* whist_w, int lane) {
   const uint64_t below = (uint64_t(1) << lane) - 1;
 #pragma unroll
-  for (int q = 0; q < kPItems; ++q) {
+  for (int q = 0; q < I; ++q) {
     const uint64_t m = same_digit(dg[q], __ballot(valid[q]));
     const int lead = valid[q] ? __ffsll((unsigned long long)m) - 1 : lane;
     uint32_t old = 0;
@@ -679,19 +686,18 @@ __device__ __forceinline__ uint64_t tile_prefix(const uint64_t (&val)[I], uint64
   return total;
 }
 
-// One segment in the sort: its E and its index (segments in leaf order).
-struct SegElem {
-  uint64_t ke;
-  int32_t seg;
-  int32_t pad;
+// Segments in the sort, as two arrays: E and the segment's index (segments in
+// leaf order).
+struct SegList {
+  uint64_t* ke;
+  int32_t* seg;
 };
-static_assert(sizeof(SegElem) == 16, "SegElem is 16 bytes");
 
 // Segments: maximal runs of consecutive leaves (by leaf rank) with equal E.
 // Sorting the leaves by (E, id) is sorting the segments by E stably, so only
 // segments are sorted. Per leaf rank: its segment and the exclusive prefix RP
-// of run lengths in leaf order; per segment: its sort element, RP at its
-// first leaf, the byte histograms of E, the OR of E and of its complement.
+// of run lengths in leaf order; per segment: its E, RP at its first leaf, the
+// byte histograms of E, the OR of E and of its complement.
 // Prefix values pack the segment count (bits 31..61) and the run lengths
 // (bits 0..30).
 struct SegArgs {
@@ -703,7 +709,7 @@ struct SegArgs {
   int n_digits;
   int32_t* seg_of;    // [L]
   int32_t* RP;        // [L]
-  SegElem* el;        // [segments]
+  uint64_t* ke;       // [segments]
   int32_t* segRP;     // [segments]
   uint64_t* agg;      // [tiles]
   Counters z;
@@ -779,7 +785,7 @@ __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
     A.RP[idx] = rp;
     if (head[i]) {
       const uint64_t key = (uint64_t)e[i];
-      A.el[seg] = SegElem{key, seg, 0};
+      A.ke[seg] = key;
       A.segRP[seg] = rp;
       or_e |= key;
       or_c |= ~key;
@@ -808,8 +814,8 @@ __global__ __launch_bounds__(kPThreads) void k_ev_segs(SegArgs A) {
 }
 
 struct SortArgs {
-  SegElem* a;
-  SegElem* b;
+  SegList a;             // a.ke: E of every segment, in leaf order
+  SegList b;
   int n_digits;
   uint64_t* status;      // per byte of E: [tiles][kRadix], then [groups][kRadix] status words
   int64_t per_pass;      // words of one byte
@@ -821,15 +827,21 @@ struct SortArgs {
   Counters z;
 };
 
+template <int I>
 struct PassLds {
   uint32_t cnt[kRadix];
   uint32_t part[2][kRadix];
   uint32_t gbase[kRadix];
-  uint32_t wsum[kRadix / kWave];
+  uint32_t lbase[kRadix];
+  uint32_t wsum[2][kRadix / kWave];
   uint32_t whist[kPWaves][kRadix];
+  uint64_t ke[kPThreads * I];
+  int32_t seg[kPThreads * I];
 };
-// Segments that are counted rather than sorted: 8192 of them take 17 us more
-// than 4096, two radix passes and their prefix over 40.
+// Segments that are counted rather than sorted: 8192 distinct scores are ranked
+// in 41 us so, 16,384 sorted in 66. Counting 8192 is 22 us of it (96 with a
+// workgroup on every fourth CU only, whose wavefronts went over all of them four
+// times as often).
 constexpr int kRankSegs = 8192;
 struct RankLds {
   uint64_t key[kRankSegs];
@@ -840,11 +852,26 @@ struct RankLds {
 // in (E, leaf) order. Every workgroup stages all keys and run lengths (at
 // most 96 KB) and its wavefronts count kOwn segments at a time.
 __device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
-  constexpr int kOwn = 2;
+  constexpr int kOwn = 2, kLoads = 4;
   const int t = threadIdx.x, lane = t & (kWave - 1);
-  for (int i = t; i < L; i += kPThreads) {
-    sh.key[i] = A.a[i].ke;   // a[i] is segment i
-    sh.run[i] = (uint32_t)((i + 1 < L ? A.segRP[i + 1] : A.nn) - A.segRP[i]);
+  for (int i0 = t; i0 < L; i0 += kLoads * kPThreads) {
+    uint64_t key[kLoads];
+    int32_t r0[kLoads], r1[kLoads];
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      const int i = min(i0 + q * kPThreads, L - 1);
+      key[q] = A.a.ke[i];
+      r0[q] = A.segRP[i];
+      r1[q] = A.segRP[min(i + 1, L - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < kLoads; ++q) {
+      const int i = i0 + q * kPThreads;
+      if (i < L) {
+        sh.key[i] = key[q];
+        sh.run[i] = (uint32_t)((i + 1 < L ? r1[q] : A.nn) - r0[q]);
+      }
+    }
   }
   __syncthreads();
   const int32_t waves = (int32_t)gridDim.x * kPWaves;
@@ -857,12 +884,31 @@ __device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
       own[q] = sh.key[min(i0 + q, L - 1)];
       sum[q] = 0;
     }
-    for (int32_t j0 = 0; j0 < L; j0 += kWave) {
-      const int32_t j = j0 + lane;
-      const uint64_t k = sh.key[min(j, L - 1)];
-      const uint32_t r = j < L ? sh.run[min(j, L - 1)] : 0;
+    // among equal keys the segments before it count: one compare decides for
+    // the places that lie wholly before or after (E + 1 does not overflow)
+    const int32_t at = i0 & ~(kWave - 1);
+    int32_t j0 = 0;
+#pragma unroll 2
+    for (; j0 < at; j0 += kWave) {
+      const uint64_t k = sh.key[j0 + lane];
+      const uint32_t r = sh.run[j0 + lane];
+#pragma unroll
+      for (int q = 0; q < kOwn; ++q) sum[q] += k < own[q] + 1 ? r : 0;
+    }
+    {
+      const int32_t j = j0 + lane, jc = min(j, L - 1);
+      const uint64_t k = sh.key[jc];
+      const uint32_t r = j < L ? sh.run[jc] : 0;
 #pragma unroll
       for (int q = 0; q < kOwn; ++q) sum[q] += (k < own[q]) | ((k == own[q]) & (j < i0 + q)) ? r : 0;
+    }
+#pragma unroll 2
+    for (j0 += kWave; j0 < L; j0 += kWave) {
+      const int32_t j = j0 + lane, jc = min(j, L - 1);
+      const uint64_t k = sh.key[jc];
+      const uint32_t r = j < L ? sh.run[jc] : 0;
+#pragma unroll
+      for (int q = 0; q < kOwn; ++q) sum[q] += k < own[q] ? r : 0;
     }
 #pragma unroll
     for (int q = 0; q < kOwn; ++q) {
@@ -872,11 +918,39 @@ __device__ void rank_segments(const SortArgs& A, int32_t L, RankLds& sh) {
   }
 }
 
-// One tile of the radix pass over byte p, src to dst.
-__device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, int p, int32_t tile, int32_t tiles,
-                           int32_t L, PassLds& sh) {
+// A store that goes through to memory, where every XCD sees it.
+template <typename T>
+__device__ __forceinline__ void store_through(T* p, T v) {
+  __hip_atomic_store(p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
+// One tile of the radix pass over byte p, src to dst; in the first pass
+// (`first`) a segment's index is its place. The tile's segments are ordered by
+// digit in LDS and go out in runs, written through to memory, where every XCD
+// sees them (with plain stores and an L2 write-back by every tile, a million
+// distinct scores took 284 us, not 238).
+template <int I>
+__device__ void radix_tile(const SortArgs& A, const SegList& src, const SegList& dst, bool first, int p, int32_t tile,
+                           int32_t tiles, int32_t L, PassLds<I>& sh) {
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
   const int d = t & (kRadix - 1), half = t / kRadix;
+  constexpr int kTile = kPThreads * I;
+  const int64_t tile0 = (int64_t)tile * kTile;
+  const int64_t base = tile0 + (int64_t)w * (kWave * I);
+  uint64_t ke[I];
+  int32_t seg[I];
+  uint32_t dg[I], rk[I];
+  bool valid[I];
+  // loads clamped to the last segment rather than skipped, so all of them
+  // are in flight at once
+#pragma unroll
+  for (int q = 0; q < I; ++q) {
+    const int64_t idx = base + q * kWave + lane;
+    valid[q] = idx < L;
+    const int64_t at = valid[q] ? idx : L - 1;
+    ke[q] = src.ke[at];
+    seg[q] = first ? (int32_t)at : src.seg[at];
+  }
   // the digit's histogram is loaded alongside the tile
   uint32_t h = 0;
   if (half == 0) {
@@ -885,25 +959,13 @@ __device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, 
   }
   for (int i = t; i < kPWaves * kRadix; i += kPThreads) (&sh.whist[0][0])[i] = 0;
   __syncthreads();
-  const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
-  SegElem v[kPItems];
-  uint32_t dg[kPItems], rk[kPItems];
-  bool valid[kPItems];
-  // loads clamped to the last segment rather than skipped, so all of them
-  // are in flight at once
 #pragma unroll
-  for (int q = 0; q < kPItems; ++q) {
-    const int64_t idx = base + q * kWave + lane;
-    valid[q] = idx < L;
-    v[q] = src[valid[q] ? idx : L - 1];
-  }
-#pragma unroll
-  for (int q = 0; q < kPItems; ++q) dg[q] = valid[q] ? (uint32_t)(v[q].ke >> (8 * p)) & 255u : 0;
-  wave_rank(dg, valid, rk, sh.whist[w], lane);
+  for (int q = 0; q < I; ++q) dg[q] = valid[q] ? (uint32_t)(ke[q] >> (8 * p)) & 255u : 0;
+  wave_rank<I>(dg, valid, rk, sh.whist[w], lane);
   __syncthreads();
+  uint32_t cnt = 0;
   if (half == 0) {
     // the waves' exclusive offsets of digit d and the tile's count
-    uint32_t cnt = 0;
 #pragma unroll
     for (int j = 0; j < kPWaves; ++j) {
       const uint32_t c = sh.whist[j][d];
@@ -914,54 +976,82 @@ __device__ void radix_tile(const SortArgs& A, const SegElem* src, SegElem* dst, 
   }
   __syncthreads();
   uint64_t* agg = A.status + (int64_t)p * A.per_pass;
-  sh.part[half][d] = (uint32_t)two_level_part(agg + d, agg + A.grp_at + d, kRadix, tile, tiles, sh.cnt[d], half,
-                                              A.z.err);
+  if (half == 0) publish(&agg[(int64_t)tile * kRadix + d], cnt);
   if (half == 0) {
-    // the digit's start over all segments: counts of smaller digits
-    // (exclusive scan of the histogram over the 4 waves of half 0)
-    uint32_t x = h;
+    // the digit's start over all segments (counts of smaller digits) and in
+    // the tile: exclusive scans over the 4 waves of half 0
+    uint32_t x = h, y = cnt;
 #pragma unroll
     for (int e = 1; e < kWave; e <<= 1) {
       const uint32_t o = __shfl(x, lane >= e ? lane - e : lane);
-      if (lane >= e) x += o;
+      const uint32_t u = __shfl(y, lane >= e ? lane - e : lane);
+      if (lane >= e) {
+        x += o;
+        y += u;
+      }
     }
-    if (lane == kWave - 1) sh.wsum[w] = x;
+    if (lane == kWave - 1) {
+      sh.wsum[0][w] = x;
+      sh.wsum[1][w] = y;
+    }
     sh.gbase[d] = x - h;
+    sh.lbase[d] = y - cnt;
   }
+  sh.part[half][d] =
+      (uint32_t)two_level_part(agg + d, agg + A.grp_at + d, kRadix, tile, tiles, sh.cnt[d], half, A.z.err);
   __syncthreads();
   if (half == 0) {
-    uint32_t g = sh.gbase[d] + sh.part[0][d] + sh.part[1][d];
-    for (int j = 0; j < w; ++j) g += sh.wsum[j];
-    sh.gbase[d] = g;
+    uint32_t g = sh.gbase[d] + sh.part[0][d] + sh.part[1][d], l = sh.lbase[d];
+    for (int j = 0; j < w; ++j) {
+      g += sh.wsum[0][j];
+      l += sh.wsum[1][j];
+    }
+    sh.gbase[d] = g - l;   // from a place in the tile's order to one in dst
+    sh.lbase[d] = l;
   }
   __syncthreads();
 #pragma unroll
-  for (int q = 0; q < kPItems; ++q) {
+  for (int q = 0; q < I; ++q) {
     if (!valid[q]) continue;
-    const uint32_t pos = sh.gbase[dg[q]] + sh.whist[w][dg[q]] + rk[q];
-    if (pos < (uint32_t)L) dst[pos] = v[q];
+    const uint32_t at = sh.lbase[dg[q]] + sh.whist[w][dg[q]] + rk[q];
+    sh.ke[at] = ke[q];
+    sh.seg[at] = seg[q];
+  }
+  __syncthreads();
+  const int m = (int)min((int64_t)kTile, L - tile0);
+#pragma unroll
+  for (int q = 0; q < I; ++q) {
+    const int at = q * kPThreads + t;
+    if (at >= m) continue;
+    const uint64_t k = sh.ke[at];
+    const uint32_t pos = sh.gbase[(uint32_t)(k >> (8 * p)) & 255u] + (uint32_t)at;
+    if (pos < (uint32_t)L) {
+      store_through(&dst.ke[pos], k);
+      store_through(&dst.seg[pos], sh.seg[at]);
+    }
   }
 }
 
 // One tile of the prefix of run lengths over the sorted segments, which is
 // every segment's start in the victim order. A segment's run total is RP at
 // the next segment's first leaf (or the node count) minus RP at its own.
-__device__ void scan_tile(const SortArgs& A, const SegElem* el, int32_t tile, int32_t L, uint64_t* wsum,
+template <int I>
+__device__ void scan_tile(const SortArgs& A, const int32_t* sorted, int32_t tile, int32_t L, uint64_t* wsum,
                           uint64_t* s_excl) {
   const int t = threadIdx.x, lane = t & (kWave - 1), w = t / kWave;
-  const int64_t base = (int64_t)tile * kPTile + (int64_t)w * (kWave * kPItems);
-  int32_t seg[kPItems], r0[kPItems], r1[kPItems];
+  const int64_t base = (int64_t)tile * (kPThreads * I) + (int64_t)w * (kWave * I);
+  int32_t seg[I], r0[I], r1[I];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) seg[i] = el[min(base + i * kWave + lane, (int64_t)L - 1)].seg;
+  for (int i = 0; i < I; ++i) seg[i] = sorted[min(base + i * kWave + lane, (int64_t)L - 1)];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < I; ++i) {
     const int32_t sc = (uint32_t)seg[i] < (uint32_t)L ? seg[i] : 0;
     r0[i] = A.segRP[sc];
     r1[i] = A.segRP[sc + 1 < L ? sc + 1 : sc];
   }
-  uint64_t val[kPItems], pre[kPItems];
+  uint64_t val[I], pre[I];
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < I; ++i) {
     const bool in = base + i * kWave + lane < L;
     const int32_t hi = seg[i] + 1 < L ? r1[i] : A.nn;
     val[i] = in ? (uint64_t)(uint32_t)(hi - r0[i]) : 0;
@@ -975,49 +1065,45 @@ __device__ void scan_tile(const SortArgs& A, const SegElem* el, int32_t tile, in
   __syncthreads();
   const uint64_t start = *s_excl;
 #pragma unroll
-  for (int i = 0; i < kPItems; ++i) {
+  for (int i = 0; i < I; ++i) {
     const int64_t idx = base + i * kWave + lane;
     if (idx < L && (uint32_t)seg[i] < (uint32_t)L) A.Sseg[seg[i]] = (int32_t)(start + pre[i]);
   }
 }
 
-// The start of every segment in the victim order. Whether the segments are
-// few is known on the device only, so one launch holds both ways. Measured
-// on a million nodes (some 3,500 segments): 4.4 us, where a launch per byte of E,
-// the first of which sorted the segments in one workgroup, and one for the
-// prefix took 31 us.
-// The passes need no launch each and no resident grid: a workgroup that
-// waits holds one ticket, and what it waits for (the tiles of the pass
-// before, earlier tiles of its own pass) holds lower tickets, whose
-// workgroups are running and wait for still lower ones only.
-__global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
-  __shared__ union {
+struct SortLds {
+  union {
     RankLds rank;
-    PassLds pass;
-  } sh;
-  __shared__ uint64_t wsum[kPWaves], s_excl, s_diff;
-  __shared__ int32_t s_ticket;
+    PassLds<kFewItems> few;
+    PassLds<kManyItems> many;
+  };
+  uint64_t wsum[kPWaves], excl, diff;
+  int32_t ticket;
+};
+
+// The radix passes and the prefix. They need no launch each and no resident
+// grid: a workgroup that waits holds one ticket, and what it waits for (the
+// tiles of the pass before, earlier tiles of its own pass) holds lower
+// tickets, whose workgroups are running and wait for still lower ones only.
+template <int I>
+__device__ __forceinline__ void sort_segments(const SortArgs& A, int32_t L, PassLds<I>& pass, SortLds& sh) {
   const int t = threadIdx.x;
-  const int32_t L = *A.z.nseg;
-  if (L <= kRankSegs) {
-    rank_segments(A, L, sh.rank);
-    return;
-  }
-  const uint64_t diff = fold_orand(A.z.orand, &s_diff);
+  const uint64_t diff = fold_orand(A.z.orand, &sh.diff);
   int passes = 0;
   for (int q = 0; q < A.n_digits; ++q) passes += pass_runs(diff, q) ? 1 : 0;
-  const int32_t tiles = (L + kPTile - 1) / kPTile;
+  const int32_t tiles = (L + kPThreads * I - 1) / (kPThreads * I);
+  if ((int32_t)blockIdx.x >= tiles) return;   // more would only wait for these
   while (true) {
     __syncthreads();   // the tile before is done with LDS
-    if (t == 0) s_ticket = (int32_t)atomicAdd(&A.z.ticket[kTicketSort], 1u);
+    if (t == 0) sh.ticket = (int32_t)atomicAdd(&A.z.ticket[kTicketSort], 1u);
     __syncthreads();
-    const int32_t ticket = s_ticket;
+    const int32_t ticket = sh.ticket;
     if (ticket >= (passes + 1) * tiles) return;
     const int k = ticket / tiles;   // the pass; after the last one the prefix
     const int32_t tile = ticket % tiles;
     if (k > 0) {
       if (t == 0) {
-        uint32_t* done = &A.z.ticket[kTicketDone + k - 1];
+        uint32_t* done = &A.z.ticket[kTicketDone + (k - 1) * kCounterPad];
         for (uint32_t spins = 0;
              __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)tiles; ++spins) {
           if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
@@ -1030,25 +1116,38 @@ __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
       __syncthreads();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
-    SegElem* src = (k & 1) ? A.b : A.a;
+    const SegList &src = (k & 1) ? A.b : A.a, &dst = (k & 1) ? A.a : A.b;
     if (k == passes) {
-      scan_tile(A, src, tile, L, wsum, &s_excl);
+      scan_tile<I>(A, src.seg, tile, L, sh.wsum, &sh.excl);
       continue;
     }
     int p = -1;
     for (int q = 0, seen = 0; q < A.n_digits; ++q)
       if (pass_runs(diff, q) && seen++ == k) p = q;
-    radix_tile(A, src, (k & 1) ? A.a : A.b, p, tile, tiles, L, sh.pass);
-    // every thread's stores are in this XCD's L2 once answered; one thread
-    // then writes it back (storing each segment through instead took twice
-    // as long: scattered 16-byte writes)
+    radix_tile<I>(A, src, dst, k == 0, p, tile, tiles, L, pass);
+    // written through, so there once answered
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
     __syncthreads();
-    if (t == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
-      __hip_atomic_fetch_add(&A.z.ticket[kTicketDone + k], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
+    if (t == 0)
+      __hip_atomic_fetch_add(&A.z.ticket[kTicketDone + k * kCounterPad], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   }
+}
+
+// The start of every segment in the victim order. Whether the segments are
+// few is known on the device only, so one launch holds both ways. With a
+// launch for each byte of E and one for the prefix, 400,000 distinct scores
+// took 118 us and a million 167, here 142 and 238; but every one of those
+// launches costs every call 1.5 us (few segments on a million nodes: 65 us
+// instead of 58), and a queue of n requests makes hardly more than 2n segments,
+// so that such numbers do not come from a queue of up to 65,536: there the one
+// launch is the faster one (65,536 distinct scores 80 us against 86, with three
+// distinct scores 41 against 57).
+__global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
+  __shared__ SortLds sh;
+  const int32_t L = *A.z.nseg;
+  if (L <= kRankSegs) rank_segments(A, L, sh.rank);
+  else if (L <= kFewSegs) sort_segments<kFewItems>(A, L, sh.few, sh);
+  else sort_segments<kManyItems>(A, L, sh.many, sh);
 }
 
 // ---- 7. placement ----
@@ -1303,11 +1402,19 @@ int levels_for(int64_t n) {
 }
 
 struct ELayout {
-  size_t e, pre, suf, sbt, top, krank, kdl, Er, runr, seg_of, RP, segRP, Sseg, el_a, el_b, hist, orand, cnt, status,
+  size_t e, pre, suf, sbt, top, krank, kdl, Er, runr, seg_of, RP, segRP, Sseg, ke_a, ke_b, sg_a, sg_b, hist, orand, cnt, status,
       ej_a, ej_b, j_a, j_b, total;
   int32_t nb, nsb, tiles, groups;
   int top_levels;
 };
+
+// Tiles of a radix pass (and groups of them) that n leaves can need.
+void status_rows(int64_t n, int32_t& tiles, int32_t& groups) {
+  const int64_t few = std::min<int64_t>(n, kFewSegs);
+  tiles = (int32_t)std::max((few + kPThreads * kFewItems - 1) / (kPThreads * kFewItems),
+                            (n + kPThreads * kManyItems - 1) / (kPThreads * kManyItems));
+  groups = (tiles + kGrp - 1) / kGrp;
+}
 
 ELayout elayout(int64_t nn) {
   ELayout L{};
@@ -1315,8 +1422,7 @@ ELayout elayout(int64_t nn) {
   L.nb = (int32_t)((n + kWave - 1) / kWave);
   L.nsb = (L.nb + kSbBlocks - 1) / kSbBlocks;
   L.top_levels = levels_for(L.nsb);
-  L.tiles = (int32_t)((n + kPTile - 1) / kPTile);   // leaves (and segments) <= nodes
-  L.groups = (L.tiles + kGrp - 1) / kGrp;
+  status_rows(n, L.tiles, L.groups);   // leaves (and segments) <= nodes
   size_t o = 0;
   auto take = [&](size_t bytes) {
     const size_t at = o;
@@ -1336,14 +1442,16 @@ ELayout elayout(int64_t nn) {
   L.RP = take(sizeof(int32_t) * n);
   L.segRP = take(sizeof(int32_t) * n);
   L.Sseg = take(sizeof(int32_t) * n);
-  L.el_a = take(sizeof(SegElem) * n);
-  L.el_b = take(sizeof(SegElem) * n);
+  L.ke_a = take(sizeof(uint64_t) * n);
+  L.ke_b = take(sizeof(uint64_t) * n);
+  L.sg_a = take(sizeof(int32_t) * n);
+  L.sg_b = take(sizeof(int32_t) * n);
   L.hist = take(sizeof(uint32_t) * kHistCopies * kMaxDigits * kRadix);
   L.orand = take(sizeof(uint64_t) * 2 * kOrCopies);
   L.cnt = take(sizeof(uint32_t) * (kTickets + 2));
-  // per pass (and for the segment pass and the scan): tile and group status
-  L.status = take(sizeof(uint64_t) * (size_t)(kMaxDigits * kRadix + 1 + kPItems / kSegFew) *
-                  (size_t)(L.tiles + L.groups));
+  // tile and group status per pass, a word per tile for the segment pass and the scan
+  L.status = take(sizeof(uint64_t) * ((size_t)kMaxDigits * kRadix * (size_t)(L.tiles + L.groups) +
+                                      n / (kPThreads * kSegFew) + 1 + (size_t)L.tiles));
   L.ej_a = take(sizeof(int64_t) * n);   // pointer jumping (deep trees)
   L.ej_b = take(sizeof(int64_t) * n);
   L.j_a = take(sizeof(int32_t) * n);
@@ -1383,8 +1491,8 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     return PEEK_OK;
   }
   const int32_t n_leaves = std::max(t.n_leaves, 1);
-  const int32_t tiles = (n_leaves + kPTile - 1) / kPTile;
-  const int32_t groups = (tiles + kGrp - 1) / kGrp;
+  int32_t tiles, groups;
+  status_rows(n_leaves, tiles, groups);
   const int64_t per_pass = (int64_t)kRadix * (tiles + groups);   // status words of one pass
 
   const int64_t* Ej = nullptr;
@@ -1448,17 +1556,17 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     int32_t* RP = (int32_t*)(w + L.RP);
     int32_t* segRP = (int32_t*)(w + L.segRP);
     int32_t* Sseg = (int32_t*)(w + L.Sseg);
-    SegElem* el_a = (SegElem*)(w + L.el_a);
-    SegElem* el_b = (SegElem*)(w + L.el_b);
+    const SegList sl_a{(uint64_t*)(w + L.ke_a), (int32_t*)(w + L.sg_a)};
+    const SegList sl_b{(uint64_t*)(w + L.ke_b), (int32_t*)(w + L.sg_b)};
     uint64_t* ss = status + (size_t)n_digits * per_pass;
-    SegArgs ga{Er, runr, n_leaves, nn, seg_tiles, n_digits, seg_of, RP, el_a, segRP, ss, z};
+    SegArgs ga{Er, runr, n_leaves, nn, seg_tiles, n_digits, seg_of, RP, sl_a.ke, segRP, ss, z};
     if (few)
       hipLaunchKernelGGL(k_ev_segs<kSegFew>, dim3((unsigned)seg_tiles), dim3(kPThreads), 0, st, ga);
     else
       hipLaunchKernelGGL(k_ev_segs<kSegMany>, dim3((unsigned)seg_tiles), dim3(kPThreads), 0, st, ga);
-    SortArgs sa{el_a, el_b, n_digits, status, per_pass, (int64_t)kRadix * tiles, ss + seg_tiles, segRP, Sseg, nn, z};
-    // a workgroup per tile there can be; 64 at least, to count few segments
-    const unsigned sort_blocks = (unsigned)std::min(std::max(tiles, 64), 1024);
+    SortArgs sa{sl_a, sl_b, n_digits, status, per_pass, (int64_t)kRadix * tiles, ss + seg_tiles, segRP, Sseg, nn, z};
+    // a workgroup per tile there can be; one per CU at least, to count few segments
+    const unsigned sort_blocks = (unsigned)std::min(std::max(tiles, 256), 1024);
     hipLaunchKernelGGL(k_ev_sort, dim3(sort_blocks), dim3(kPThreads), 0, st, sa);
     PlaceArgs la{krank, kdl, seg_of, RP, segRP, Sseg, nn, n_leaves, order};
     hipLaunchKernelGGL(k_ev_place, dim3(blocks_of(nn - 1)), dim3(256), 0, st, la);
