@@ -1,6 +1,10 @@
 // Host side of libpeek: error reporting, tree validation and canonical
 // flattening, the sequences-to-tree helper, and the C ABI entry points.
+#include <sys/random.h>
+
 #include <algorithm>
+#include <atomic>
+#include <chrono>
 #include <cstdarg>
 #include <cstdio>
 #include <cstdlib>
@@ -283,6 +287,24 @@ int64_t seq_lcp(const SeqRef& a, const SeqRef& b) {
 }
 
 }  // namespace
+
+#ifdef PEEK_SAMPLE_SEED   // a build for tests, which make inputs for known places
+uint32_t sample_seed() { return PEEK_SAMPLE_SEED; }
+#else
+static uint64_t first_seed() {
+  uint64_t s = 0;
+  if (getrandom(&s, sizeof(s), GRND_NONBLOCK) == (ssize_t)sizeof(s)) return s;
+  return (uint64_t)std::chrono::steady_clock::now().time_since_epoch().count() ^ (uint64_t)(uintptr_t)&s;
+}
+
+uint32_t sample_seed() {
+  static std::atomic<uint64_t> next{first_seed()};
+  uint64_t z = next.fetch_add(0x9E3779B97F4A7C15ull, std::memory_order_relaxed);
+  z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+  z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+  return (uint32_t)(z >> 32);
+}
+#endif
 
 peek_status check_device(int* dev_out) {
   int dev = 0;

@@ -145,6 +145,9 @@ peek_status guarded(F&& body) noexcept {
   }
 }
 
+// A seed for the sorts' sampled places, another one at every call. Any thread.
+uint32_t sample_seed();
+
 // Current device id if it is a gfx950, else UNSUPPORTED_DEVICE.
 peek_status check_device(int* dev_out);
 

@@ -2899,7 +2899,7 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
   void* sort_ws = w + L.ib1;
   const size_t sort_ws_bytes = L.st1 - L.ib1;
   const AncElem* sorted = msort::sort_distinct(AncSrc{anc_a, n}, anc_a, anc_b, n, np, AncElem{~0ull, ~0ull, ~0ull},
-                                               AncLess{}, sort_ws, sort_ws_bytes, st);
+                                               AncLess{}, sort_ws, sort_ws_bytes, sample_seed(), st);
   // The order is sorted by last node first, so demand reads it directly:
   // the segment kernel marks where each last node's run starts, the second
   // round's compare carries the fill of the prefix P over all nodes, the
@@ -2967,7 +2967,8 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
       OffElem* oel = (OffElem*)(w + L.oel_a);
       const OffElem* sorted =
           msort::sort_distinct(msort::FromArray<OffElem>{oel}, oel, (OffElem*)(w + L.oel_b), m2, L.onp,
-                               OffElem{INT32_MAX, INT32_MAX, INT32_MAX, 0}, OffLess{}, sort_ws, sort_ws_bytes, st);
+                               OffElem{INT32_MAX, INT32_MAX, INT32_MAX, 0}, OffLess{}, sort_ws, sort_ws_bytes,
+                               sample_seed(), st);
       int64_t* tail = (int64_t*)(w + L.otail);
       const unsigned sb = blocks_for(m2, kScanThreads);
       if (m2 <= kOffWhole) {

@@ -37,8 +37,8 @@ struct FromArray {
 // of their difference, a word an instruction, which is the mask that counting
 // wants. Compares of 64-bit words run at a fraction of the rate, and the mask of
 // a combined result costs two more instructions. An instruction that reads a
-// mask follows the one that wrote it by two wait states. With the counted sort's
-// LDS reads four ahead: 4096 document prompts 13.1 -> 11.9 us (12.3 without
+// mask follows the one that wrote it by two wait states. Every lane of the wave
+// is active. With the counted sort's LDS reads four ahead: 4096 document prompts 13.1 -> 11.9 us (12.3 without
 // those), ranking 1024 samples 4.6 -> 4.1.
 __device__ __forceinline__ uint64_t borrow_lanes(const uint32_t (&x)[3], const uint32_t (&y)[3]) {
   uint64_t m;
@@ -139,11 +139,16 @@ __global__ __launch_bounds__(kRankThreads) void k_rank_sort(Src src, T* __restri
 }
 
 // ---------------------------------------------------------------- by buckets
-// Samples are jittered (one hashed place in each of S equal stretches of the
-// input), so a bucket's size depends on the hash and not on how the input is
-// laid out. With 4 samples to a bucket one over 8 times the mean has odds of
-// about 1e-10. A bucket that is larger all the same (an input made
-// for it) is ordered in global memory.
+// Samples are jittered: one hashed place in each of S equal stretches of the
+// input. The hash takes a seed that is drawn anew for every call, so a bucket's
+// size depends on that draw and not on how the input is laid out: no queue can
+// be made, or happen, to fall into few buckets. With 4 samples to a bucket one
+// over 8 times the mean has odds of about 1e-10. A bucket that is larger all the
+// same is ordered in global memory by its one workgroup, which is slow where it
+// holds nearly everything: with the places known beforehand (the hash once had
+// no seed) a queue made for them took 3.9 ms at 40,000 requests and 14.3 ms at
+// 131,072, where the merge sort's call took 0.13 and 0.21 ms; drawn places sort
+// those queues in calls of 0.09 and 0.18 ms.
 // All three launches are bound by chains of dependent accesses and by the
 // comparisons in LDS; 24-byte keys, us (merge sort / sample + scatter +
 // bucket sort): 4500 elements 31 / 12.4, 16,384 36 / 14.5, 65,536 52 / 17 to
@@ -164,12 +169,14 @@ struct Buckets {
   int32_t n;
   int32_t nb;       // buckets, a power of two
   int32_t cap;      // slots of a bucket
+  uint32_t seed;    // of the sampled places
   int32_t* count;   // [nb * kCountPad]
   int32_t* slots;   // [nb * cap] elements of each bucket, by input index
 };
 
-__device__ __forceinline__ uint32_t sample_hash(uint32_t x) {
+__device__ __forceinline__ uint32_t sample_hash(uint32_t x, uint32_t seed) {
   x *= 0x9E3779B1u;
+  x ^= seed;
   x ^= x >> 15;
   x *= 0x85EBCA77u;
   x ^= x >> 13;
@@ -190,7 +197,7 @@ __global__ __launch_bounds__(kSampleThreads) void k_sample_rank(Src src, T* __re
     const uint32_t j = (uint32_t)(q * kSampleThreads + t);
     const uint32_t lo = (uint32_t)(((uint64_t)j * (uint32_t)B.n) / S);
     const uint32_t hi = (uint32_t)(((uint64_t)(j + 1) * (uint32_t)B.n) / S);
-    v[q] = src((size_t)(lo + sample_hash(j) % (hi - lo)));   // n > S: no stretch is empty
+    v[q] = src((size_t)(lo + sample_hash(j, B.seed) % (hi - lo)));   // n > S: no stretch is empty
   }
 #pragma unroll
   for (int q = 0; q < kLoads; ++q) s[q * kSampleThreads + t] = v[q];
@@ -567,10 +574,11 @@ T* merge_sort(Src src, T* a, T* b, size_t np, Less less, hipStream_t st) {
 // up to a power of two (at least kTile), the room of a and b, and `src` gives
 // `pad`, which no key exceeds, from n on. Returns a or b, whichever holds the
 // result. `src` may read a. `scratch` (any contents) is 36 bytes or more an
-// element: room for buckets of 7 times their mean and more.
+// element: room for buckets of more than 6 times their mean. `seed`: see the
+// samples above.
 template <typename T, typename Less, typename Src>
 T* sort_distinct(Src src, T* a, T* b, int32_t n, size_t np, T pad, Less less, void* scratch, size_t scratch_bytes,
-                 hipStream_t st) {
+                 uint32_t seed, hipStream_t st) {
   if (n <= kRankMax) {
     constexpr int waves = kRankThreads / 64;
     auto grid = [&](int per) { return dim3((unsigned)((n + waves * per - 1) / (waves * per))); };
@@ -584,6 +592,7 @@ T* sort_distinct(Src src, T* a, T* b, int32_t n, size_t np, T pad, Less less, vo
   if (n > kSampleMax) return merge_sort(src, a, b, np, less, st);
   Buckets B{};
   B.n = n;
+  B.seed = seed;
   B.nb = kMaxBuckets;
   while (B.nb > 32 && n / B.nb < 128) B.nb >>= 1;
   T* split = (T*)scratch;

@@ -2,8 +2,13 @@
 elements an element's place is counted, up to 131072 (samples: 1024 below 65536,
 2048 from there) buckets are ordered on their own, beyond that they are merged. The
 cluster sort has one element per request, the offline sort two. Outputs are whole
-numbers and must equal the oracle's. A queue whose sampled requests all sort last
-leaves every other request in the first bucket, which then does not fit LDS."""
+numbers and must equal the oracle's. Places are sampled under a seed that is drawn
+for every call; in a build with seed 0, queues whose sampled elements all sort last
+leave every other one in the first bucket, which then does not fit LDS. With drawn
+seeds the same queues take no longer than others."""
+import ctypes
+import os
+
 import numpy as np
 import pytest
 
@@ -15,7 +20,7 @@ pytestmark = pytest.mark.gpu
 
 
 def sampled_places(n, samples):
-    """Where the sort samples its input: a hashed place in each of `samples` stretches."""
+    """Where the sort samples its input under seed 0: a hashed place in each of `samples` stretches."""
     j = np.arange(samples, dtype=np.uint64)
     lo, hi = j * n // samples, (j + 1) * n // samples
     x = (j.astype(np.uint32) * np.uint32(0x9E3779B1)).astype(np.uint32)
@@ -34,7 +39,7 @@ def short_queue(n, seed, samples_last=False):
     tok = rng.integers(0, 40, int(off[-1])).astype(np.int32)
     tok[off[:-1]] = rng.integers(-n // 8 - 1, n // 8 + 1, n)
     if samples_last:
-        at = sampled_places(n, 1024)
+        at = sampled_places(n, 1024 if n <= 65535 else 2048)
         tok[off[at]] = 1000000 + np.arange(len(at))
     cached = [tok[off[i]:off[i + 1]] for i in rng.integers(0, n, min(n, 64))]
     return W.Workload("sort", seed, tok, off, 2, 2, cache_sequences=W.pack(cached))
@@ -52,3 +57,77 @@ def test_sorts_at_every_form(n, samples_last):
         assert_parity(w, res, s)
     for depth in (1, 3):
         check_offline(hp, w, depth)
+
+
+def star_queue(n):
+    """n prompts of one token each, children of one offline node in an order in which the
+    sampled ones of its 2n pieces (the first n are the requests in order) come last."""
+    at = sampled_places(2 * n, 1024 if 2 * n <= 65535 else 2048)
+    at = at[at < n]
+    request = np.empty(n, np.int64)          # by place in the order of tokens
+    rest = np.setdiff1d(np.arange(n), at)
+    request[at] = np.arange(n - len(at), n)
+    request[rest] = np.arange(n - len(at))
+    tok = np.empty(n, np.int32)
+    tok[request] = np.arange(n)
+    return W.Workload("star", 0, tok, np.arange(n + 1, dtype=np.int64), 2, 2, cache_sequences=W.pack([tok[:1]]))
+
+
+@pytest.fixture
+def seed_zero(monkeypatch):
+    """The library built with sampled places known beforehand."""
+    import paper_2607_02525_amd as P
+    import paper_2607_02525_amd.runner as R
+    lib = ctypes.CDLL(os.path.join(os.path.dirname(P.LIB_PATH), "libpeek_forced.so"))
+    for name, res, args in P.EXPORTS:
+        fn = getattr(lib, name)
+        fn.restype, fn.argtypes = res, args
+    monkeypatch.setattr(P, "_lib", lib)
+    monkeypatch.setattr(R, "_lib", lib)
+
+
+@pytest.mark.parametrize("n", [8191, 40000, 65535, 65536, 100000])
+def test_bucket_that_fits_nowhere(seed_zero, n):
+    w = short_queue(n, 3, True)
+    hp, outs = gpu_run(w)
+    assert_parity(w, outs[0], O.run(w))
+
+
+@pytest.mark.parametrize("n", [5000, 32767, 32768, 40000])
+def test_offline_bucket_that_fits_nowhere(seed_zero, n):
+    w = star_queue(n)
+    hp, outs = gpu_run(w)
+    check_offline(hp, w, 1)
+
+
+def call_us(f):
+    import torch
+    f()
+    torch.cuda.synchronize()
+    best = float("inf")
+    for _ in range(5):
+        a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        a.record()
+        for _ in range(5):
+            f()
+        b.record()
+        torch.cuda.synchronize()
+        best = min(best, a.elapsed_time(b) * 1e3 / 5)
+    return best
+
+
+def test_no_layout_is_slow():
+    """The queues made for seed 0 (and so for a hash without one) against plain ones: the
+    sort's time does not depend on the layout. It was 40 and 20 times as long."""
+    made, hp1 = short_queue(40000, 3, True), gpu_run(short_queue(40000, 3))[0]
+    hp2 = gpu_run(made)[0]
+    a, b = call_us(hp1.signals), call_us(hp2.signals)
+    print(f"[gpu] signals of 40000: plain {a:.1f} us, made {b:.1f} us", flush=True)
+    assert b < 3 * a
+    star = star_queue(40000)
+    mixed = star_queue(40000)
+    mixed.tokens[:] = np.random.default_rng(1).permutation(40000)
+    hp1, hp2 = gpu_run(mixed)[0], gpu_run(star)[0]
+    a, b = call_us(lambda: hp1.offline(1)), call_us(lambda: hp2.offline(1))
+    print(f"[gpu] offline order of 40000: plain {a:.1f} us, made {b:.1f} us", flush=True)
+    assert b < 3 * a
