@@ -179,6 +179,10 @@ peek_status peek_lpm_batch(const peek_cache* cache, int32_t n, const int32_t* d_
  * so the workspace and every output must stay untouched until `stream` has
  * run the work. Calls on different streams need distinct workspaces.
  * threshold >= 1. Errors: INVALID_ARGUMENT, WORKSPACE_TOO_SMALL, DEVICE.
+ * Up to 512 requests, workgroups wait for others of the same kernel. Such a
+ * wait always ends; were it to last seconds all the same, the kernel gives it
+ * up and fills cluster_id and cluster_size (and peek_clpm_signals' outputs)
+ * with -1, which no finished call leaves in cluster_size.
  * ---------------------------------------------------------------------- */
 size_t peek_queue_signals_workspace(int32_t n, int64_t num_nodes);
 
@@ -254,7 +258,9 @@ peek_status peek_clpm_signals(const peek_cache* cache, int32_t n, const int32_t*
  * d_demand is peek_queue_signals' demand (int32[num_nodes], device). Either
  * output may be NULL, not both. Scratch comes only from d_workspace (device,
  * 256-byte aligned, at least peek_evict_rank_workspace(num_nodes) bytes).
- * Asynchronous on `stream`.
+ * Asynchronous on `stream`. As with the signals of few requests, a wait
+ * between workgroups that lasts seconds is given up: d_order is then -1
+ * throughout (d_score needs no wait).
  * Errors: INVALID_ARGUMENT, WORKSPACE_TOO_SMALL, DEVICE.
  * ---------------------------------------------------------------------- */
 size_t peek_evict_rank_workspace(int64_t num_nodes);

@@ -14,9 +14,10 @@ CSRC = os.path.join(HERE, "csrc")
 INCLUDE = os.path.join(os.path.dirname(HERE), "include")
 LIB = os.path.join(HERE, "libpeek.so")
 CALIB_LIB = os.path.join(HERE, "libpeek_calib.so")   # measurement helper for bench.py
-# The same library with what a test cannot bring about otherwise: sampled places known beforehand
+# The same library with what a test cannot bring about otherwise: sampled places known
+# beforehand, and waits between workgroups that give up at once
 FORCED_LIB = os.path.join(HERE, "libpeek_forced.so")
-FORCED = ["-DPEEK_SAMPLE_SEED=0"]
+FORCED = ["-DPEEK_SAMPLE_SEED=0", "-DPEEK_WAIT_SPINS=0"]
 BUILD_DIR = os.path.join(HERE, "_build")
 
 SOURCES = ["peek_host.hip", "peek_walk.hip", "peek_signals.hip", "peek_evict.hip", "peek_blocks.hip",

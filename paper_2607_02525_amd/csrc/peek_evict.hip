@@ -289,7 +289,7 @@ struct Counters {
   uint32_t* ticket;   // [kTickets]
   uint32_t* hist;     // [kHistCopies][kMaxDigits][kRadix]: segments per byte value of E
   uint64_t* orand;    // [kOrCopies][2]: OR of the keys and of their complements
-  uint32_t* err;      // set when a wait gives up
+  uint32_t* err;      // set when a wait gives up (see k_ev_place)
   int32_t* nseg;      // segments (written by the segment pass)
 };
 
@@ -499,7 +499,6 @@ static_assert(kPThreads == 2 * kRadix, "two threads per digit");
 constexpr int kGrp = 16;
 constexpr uint64_t kStSet = uint64_t(1) << 62;
 constexpr uint64_t kStVal = kStSet - 1;
-constexpr uint32_t kSpinCap = 1u << 24;
 
 // The bits on which the keys differ, from the copies (the first wave loads
 // them, every thread of the workgroup calls this).
@@ -537,8 +536,11 @@ __device__ __forceinline__ void publish(uint64_t* w, uint64_t v) {
 __device__ uint64_t sum_published(const uint64_t* st, int64_t stride, int32_t i0, int n, uint32_t* err) {
   uint64_t sum = 0;
   uint32_t pending = n > 0 ? (uint32_t)((1ull << n) - 1) : 0u;
-  uint32_t spins = 0;
-  while (pending) {
+  for (uint32_t spins = 0; pending; ++spins) {
+    if (spins >= kWaitSpins) {
+      atomicOr(err, 1u);
+      break;
+    }
     uint64_t s[kGrp];
 #pragma unroll
     for (int i = 0; i < kGrp; ++i)
@@ -551,13 +553,7 @@ __device__ uint64_t sum_published(const uint64_t* st, int64_t stride, int32_t i0
         pending &= ~(1u << i);
       }
     }
-    if (pending) {
-      if (++spins > kSpinCap) {   // never expected; ends the wait instead of hanging
-        atomicOr(err, 1u);
-        break;
-      }
-      __builtin_amdgcn_s_sleep(2);
-    }
+    if (pending) __builtin_amdgcn_s_sleep(2);
   }
   return sum;
 }
@@ -590,6 +586,10 @@ __device__ uint64_t sum_before(const uint64_t* st, int32_t tile, uint32_t* err) 
 #pragma unroll
     for (int k = 0; k < 4; ++k) pend[k] = j0 + k * kWave + lane < tile;
     for (uint32_t spins = 0;; ++spins) {
+      if (spins >= kWaitSpins) {
+        if (lane == 0) atomicOr(err, 1u);
+        break;
+      }
       uint64_t s[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k)
@@ -605,10 +605,6 @@ __device__ uint64_t sum_before(const uint64_t* st, int32_t tile, uint32_t* err) 
         any = any || pend[k];
       }
       if (__ballot(any) == 0) break;
-      if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
-        if (lane == 0) atomicOr(err, 1u);
-        break;
-      }
       __builtin_amdgcn_s_sleep(2);
     }
   }
@@ -1104,12 +1100,12 @@ __device__ __forceinline__ void sort_segments(const SortArgs& A, int32_t L, Pass
     if (k > 0) {
       if (t == 0) {
         uint32_t* done = &A.z.ticket[kTicketDone + (k - 1) * kCounterPad];
-        for (uint32_t spins = 0;
-             __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < (uint32_t)tiles; ++spins) {
-          if (spins > kSpinCap) {   // never expected; ends the wait instead of hanging
+        for (uint32_t spins = 0;; ++spins) {
+          if (spins >= kWaitSpins) {
             atomicOr(A.z.err, 1u);
             break;
           }
+          if (__hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= (uint32_t)tiles) break;
           __builtin_amdgcn_s_sleep(2);
         }
       }
@@ -1150,11 +1146,12 @@ __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
   else sort_segments<kManyItems>(A, L, sh.many, sh);
 }
 
-// ---- 7. placement ----
+// ---- 6. placement ----
 
 // Node c goes to S(K.id) + level(K.id) - level(c), where S of the leaf at
 // rank r is its segment's start plus the run lengths of the segment's
-// leaves before it.
+// leaves before it. When a wait has given up, what these hold is in no order:
+// every place is filled with -1 instead.
 struct PlaceArgs {
   const int32_t* krank;
   const int32_t* kdl;
@@ -1165,12 +1162,17 @@ struct PlaceArgs {
   int32_t nn;
   int32_t L;
   int32_t* order;
+  const uint32_t* err;
 };
 
 __global__ void k_ev_place(PlaceArgs A) {
   const int32_t c = blockIdx.x * blockDim.x + threadIdx.x + 1;   // the root goes last and stays out
   if (c >= A.nn) return;
   const int32_t r = A.krank[c], dl = A.kdl[c];
+  if (*A.err != 0) {
+    A.order[c - 1] = -1;
+    return;
+  }
   if ((uint32_t)r >= (uint32_t)A.L) return;
   const int32_t sg = A.seg_of[r], rp = A.RP[r];
   if ((uint32_t)sg >= (uint32_t)A.L) return;
@@ -1568,7 +1570,7 @@ peek_status run_evict(const peek_cache* c, const int32_t* demand, int64_t* score
     // a workgroup per tile there can be; one per CU at least, to count few segments
     const unsigned sort_blocks = (unsigned)std::min(std::max(tiles, 256), 1024);
     hipLaunchKernelGGL(k_ev_sort, dim3(sort_blocks), dim3(kPThreads), 0, st, sa);
-    PlaceArgs la{krank, kdl, seg_of, RP, segRP, Sseg, nn, n_leaves, order};
+    PlaceArgs la{krank, kdl, seg_of, RP, segRP, Sseg, nn, n_leaves, order, z.err};
     hipLaunchKernelGGL(k_ev_place, dim3(blocks_of(nn - 1)), dim3(256), 0, st, la);
   }
   PEEK_HIP_TRY(hipGetLastError());

@@ -158,6 +158,15 @@ peek_status check_device(int* dev_out);
                                               hipGetErrorString(e_));                   \
   } while (0)
 
+// Times a kernel looks before it gives up a wait for another workgroup: some
+// seconds. What it waits for is always running, so a wait that gives up is
+// never expected; it ends instead of hanging, and the outputs that depended on
+// it are filled with -1. (Tests build with 0.)
+#ifndef PEEK_WAIT_SPINS
+#define PEEK_WAIT_SPINS (1u << 24)
+#endif
+constexpr uint32_t kWaitSpins = PEEK_WAIT_SPINS;
+
 // Launchers (asynchronous on `stream`).
 hipError_t launch_lpm_walk(const DeviceTree& t, int32_t n, const int32_t* tokens,
                            const int64_t* offsets, int32_t block_size, int32_t* h,

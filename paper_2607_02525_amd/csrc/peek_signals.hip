@@ -309,7 +309,7 @@ struct ClElem {
 
 // Flags after the first round: [any active segment, a segment the second
 // round takes]; then the small queue's counters (see k_small_refine).
-constexpr int kFlags = 5;
+constexpr int kFlags = 6;
 
 constexpr uint64_t kLenMax = 0x7FFFFFFFull;   // also the mask of a request in a key's low 31 bits
 
@@ -2135,6 +2135,7 @@ struct SmallArgs {
 
 constexpr int kSmallRange = 16;   // positions whose segments one tail ticket settles
 constexpr int kFlagTicket = 2, kFlagCompared = 3, kFlagSettled = 4;   // k_small_refine's counters
+constexpr int kFlagLate = 5;                                          // a wait gave up
 
 struct SmallLds {
   union {
@@ -2320,8 +2321,21 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_signals(SmallArgs A, in
 // ticket, and what it waits for holds lower ones, whose workgroups are
 // running and do not wait: it needs no resident grid. The compare's keys are
 // written through and the tail's results released (an L2 write-back), so that
-// the next workgroup sees them on whichever XCD it runs.
+// the next workgroup sees them on whichever XCD it runs. When a wait gives up,
+// nothing is settled from keys that may not be there: every output of the
+// clusters is filled with -1, which no finished call leaves in cluster_size.
 constexpr unsigned kSmallRefineBlocks = 64;
+
+__device__ __forceinline__ void small_failed(const SmallArgs& A) {
+  const int t = threadIdx.x;
+  if (t < A.n) {
+    A.cid[t] = -1;
+    A.csz[t] = -1;
+    if (A.cl.score != nullptr) A.cl.score[t] = -1;
+    if (A.cl.section != nullptr) A.cl.section[t] = -1;
+  }
+  if (t == 0 && A.sharing != nullptr) *A.sharing = -1;
+}
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_refine(SmallArgs A, int32_t* flags) {
   __shared__ SmallLds S;
@@ -2361,22 +2375,31 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_refine(SmallArgs A, int
       if (t == 0) atomicAdd(&flags[kFlagCompared], 1);
       continue;
     }
+    bool late = false;
     if (t == 0) {
-      // bounded: never expected to run out
-      for (uint32_t spins = 0; spins < (1u << 24); ++spins) {
+      for (uint32_t spins = 0;; ++spins) {
+        if (spins >= kWaitSpins) {
+          late = true;
+          atomicOr(&flags[kFlagLate], 1);
+          break;
+        }
         if (__hip_atomic_load(&flags[kFlagCompared], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) >= compares) break;
         __builtin_amdgcn_s_sleep(2);
       }
     }
-    __syncthreads();
+    late = __syncthreads_or(late) != 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    refine_tail(T, (ticket - compares) * kSmallRange, S.tail);
+    if (!late) refine_tail(T, (ticket - compares) * kSmallRange, S.tail);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (t == 0) S.ticket = atomicAdd(&flags[kFlagSettled], 1);
     __syncthreads();
     if (S.ticket != tails - 1) continue;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+    if (__hip_atomic_load(&flags[kFlagLate], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+      small_failed(A);
+      return;
+    }
     if (t < n) S.el[t] = T.el[t];
     S.lcp[t] = T.lcp[min(t, n)];
     if (t == 0) S.lcp[n] = 0;

@@ -6,9 +6,6 @@ numbers and must equal the oracle's. Places are sampled under a seed that is dra
 for every call; in a build with seed 0, queues whose sampled elements all sort last
 leave every other one in the first bucket, which then does not fit LDS. With drawn
 seeds the same queues take no longer than others."""
-import ctypes
-import os
-
 import numpy as np
 import pytest
 
@@ -73,28 +70,15 @@ def star_queue(n):
     return W.Workload("star", 0, tok, np.arange(n + 1, dtype=np.int64), 2, 2, cache_sequences=W.pack([tok[:1]]))
 
 
-@pytest.fixture
-def seed_zero(monkeypatch):
-    """The library built with sampled places known beforehand."""
-    import paper_2607_02525_amd as P
-    import paper_2607_02525_amd.runner as R
-    lib = ctypes.CDLL(os.path.join(os.path.dirname(P.LIB_PATH), "libpeek_forced.so"))
-    for name, res, args in P.EXPORTS:
-        fn = getattr(lib, name)
-        fn.restype, fn.argtypes = res, args
-    monkeypatch.setattr(P, "_lib", lib)
-    monkeypatch.setattr(R, "_lib", lib)
-
-
 @pytest.mark.parametrize("n", [8191, 40000, 65535, 65536, 100000])
-def test_bucket_that_fits_nowhere(seed_zero, n):
+def test_bucket_that_fits_nowhere(forced_library, n):
     w = short_queue(n, 3, True)
     hp, outs = gpu_run(w)
     assert_parity(w, outs[0], O.run(w))
 
 
 @pytest.mark.parametrize("n", [5000, 32767, 32768, 40000])
-def test_offline_bucket_that_fits_nowhere(seed_zero, n):
+def test_offline_bucket_that_fits_nowhere(forced_library, n):
     w = star_queue(n)
     hp, outs = gpu_run(w)
     check_offline(hp, w, 1)
