@@ -490,9 +490,13 @@ __global__ void k_first_clear(HeadTable T, int32_t n, int32_t* __restrict__ lcp,
 // prompts 12.0 / 10.8 / 10.2 / 10.3, 16,384 prompts of their own 23.0 / 18.1 /
 // 16.3 / 16.1, 20,000 mixed 12.6 / 12.7 / 10.2 / 11.3). At 65,536 requests
 // there are enough of them either way, and the more workgroups the more of
-// them meet at one group's word (16.5 / 15.9 / 18.6 / 29.3).
-constexpr int kInsFew = 256, kInsMany = 512;
-constexpr int32_t kInsFewMax = 32768;   // requests
+// them meet at one group's word (16.5 / 15.9 / 18.6 / 29.3). Beyond 131,072 that
+// decides (1024 / 512, four groups of prompts: 131,073 requests 13.4 / 18.1,
+// 300,000 26.3 / 39.1; two thousand groups, 500,000 requests: 50 / 56). In
+// between the whole call takes the same with either (100,000 requests of 4,
+// 2000 and 25,000 groups: 180 / 186, 195 / 195, 153 / 147).
+constexpr int kInsFew = 256, kInsMany = 512, kInsMost = 1024;
+constexpr int32_t kInsFewMax = 32768, kInsManyMax = 131072;   // requests
 
 template <int kInsThreads>
 __global__ __launch_bounds__(kInsThreads) void k_first_insert(AnchorIn in, HeadTable T, int32_t n) {
@@ -1138,21 +1142,36 @@ __device__ __forceinline__ void tail_wg_round(const TailArgs& A, int32_t s, int3
   __syncthreads();
 }
 
+// The tail's LDS. Arrays of their own and not one struct: the compiler then
+// knows that none of them overlaps another (the tail of 500,000 requests 299 us
+// instead of 301).
 template <int kRange, int kCap>
 struct TailLds {
-  uint64_t sa[kCap];
-  uint64_t sb[kCap];
-  uint32_t sp[kCap];
-  uint64_t cmask[kCap / kWave];
-  int32_t root_s[kRange / 2], root_e[kRange / 2];   // segments of >= 2 members starting in the range
-  int32_t small_l[kTailList], big_l[kTailList];
-  int32_t n_roots, n_small, n_big;
+  uint64_t *sa, *sb;       // [kCap]
+  uint32_t* sp;            // [kCap]
+  uint64_t* cmask;         // [kCap / kWave]
+  int32_t *root_s, *root_e;     // [kRange / 2] segments of >= 2 members starting in the range
+  int32_t *small_l, *big_l;     // [kTailList]
+  int32_t* n;                   // [3] roots, small, big
 };
+#define PEEK_TAIL_LDS(name, range, cap)                                             \
+  __shared__ uint64_t name##_sa[cap], name##_sb[cap], name##_cmask[(cap) / kWave];  \
+  __shared__ uint32_t name##_sp[cap];                                               \
+  __shared__ int32_t name##_rs[(range) / 2], name##_re[(range) / 2];                \
+  __shared__ int32_t name##_small[kTailList], name##_big[kTailList], name##_n[3];   \
+  const TailLds<range, cap> name {                                                  \
+    name##_sa, name##_sb, name##_sp, name##_cmask, name##_rs, name##_re, name##_small, name##_big, name##_n \
+  }
 
 // The segments that start in positions [p0, p0 + kRange), by one workgroup.
 template <int kRange, int kCap>
-__device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailLds<kRange, kCap>& S) {
+__device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, const TailLds<kRange, kCap>& S) {
   static_assert(kRange <= kTailThreads, "one position per thread in the root scan");
+  // one body for the two places that call it: with a copy at each the tail took
+  // 241 VGPRs instead of 186, of 500,000 requests 309 us instead of 301
+  auto round = [&](int32_t s, int32_t size, int32_t d, bool with_keys) {
+    tail_wg_round<kCap>(A, s, size, d, S.sa, S.sb, S.sp, S.cmask, with_keys);
+  };
   const int32_t f0 = A.flags[0];        // tested once the root loads below are issued
   const bool keyed = A.flags[1] != 0;   // the second round compared its segments
   const int32_t* depth = A.depth;
@@ -1166,15 +1185,15 @@ __device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailL
   const uint8_t ac = active[pc];
   const int32_t gz = A.gsize[pc];
   if (f0 == 0) return;
-  if (t == 0) S.n_roots = 0;
+  if (t == 0) S.n[0] = 0;
   __syncthreads();
   if (p < p1 && sg == p && ac) {
-    const int k = atomicAdd(&S.n_roots, 1);
+    const int k = atomicAdd(&S.n[0], 1);
     S.root_s[k] = p;
     S.root_e[k] = p + gz;
   }
   __syncthreads();
-  const int nr = S.n_roots;
+  const int nr = S.n[0];
   if (nr == 0) return;
   // the second round's segments of at most 64 members, from the keys it
   // wrote: each is settled completely by one wavefront and leaves the list
@@ -1203,7 +1222,7 @@ __device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailL
   if (keyed) {
     for (int k = 0; k < nr; ++k) {
       const int32_t s = S.root_s[k], sz = S.root_e[k] - s;
-      if (sz > kWave && round_takes(sz)) tail_wg_round<kCap>(A, s, sz, depth[s], S.sa, S.sb, S.sp, S.cmask, true);
+      if (sz > kWave && round_takes(sz)) round(s, sz, depth[s], true);
     }
   }
   // Each pass settles at least one small segment or gives at least one large
@@ -1212,8 +1231,8 @@ __device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailL
   // bound only guards the device against a broken invariant.
   for (int64_t pass = 0; pass <= 2 * (int64_t)A.n + 2; ++pass) {
     if (t == 0) {
-      S.n_small = 0;
-      S.n_big = 0;
+      S.n[1] = 0;
+      S.n[2] = 0;
     }
     __syncthreads();
     for (int k = 0; k < nr; ++k) {
@@ -1223,17 +1242,17 @@ __device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailL
         const int32_t z = A.tsize[q];
         if (ac) {
           if (z <= kWave) {
-            const int x = atomicAdd(&S.n_small, 1);
+            const int x = atomicAdd(&S.n[1], 1);
             if (x < kTailList) S.small_l[x] = q;
           } else {
-            const int x = atomicAdd(&S.n_big, 1);
+            const int x = atomicAdd(&S.n[2], 1);
             if (x < kTailList) S.big_l[x] = q;
           }
         }
       }
     }
     __syncthreads();
-    const int ns = min(S.n_small, kTailList), nb = min(S.n_big, kTailList);
+    const int ns = min(S.n[1], kTailList), nb = min(S.n[2], kTailList);
     if (ns == 0 && nb == 0) break;
     for (int x = wave; x < ns; x += kTailWaves) {
       const int32_t q = S.small_l[x];
@@ -1243,14 +1262,14 @@ __device__ __forceinline__ void refine_tail(const TailArgs& A, int32_t p0, TailL
     __syncthreads();
     for (int x = 0; x < nb; ++x) {
       const int32_t q = S.big_l[x];
-      tail_wg_round<kCap>(A, q, A.tsize[q], A.tdep[q], S.sa, S.sb, S.sp, S.cmask, false);
+      round(q, A.tsize[q], A.tdep[q], false);
     }
     __syncthreads();
   }
 }
 
 __global__ __launch_bounds__(kTailThreads) void k_refine_tail(TailArgs A) {
-  __shared__ TailLds<kTailRange, kTailCap> S;
+  PEEK_TAIL_LDS(S, kTailRange, kTailCap);
   refine_tail(A, (int32_t)blockIdx.x * kTailRange, S);
 }
 
@@ -1799,11 +1818,13 @@ struct LcpIndex {
 // One thread per sorted position i: cluster id and size of its request;
 // with cLPM signals requested also the weight of the pending-tree node
 // whose leftmost inner position is i, and the section run of position i.
-// All of a position's searches advance together: their in-block rounds, then
-// `make` (every thread of the workgroup calls it once, told whether any of
-// them needs it) gives the index over the blocks, then the rounds in the
-// blocks found.
-template <typename Make>
+// With kTogether all of a position's searches advance together: their in-block
+// rounds, then `make` (every thread of the workgroup calls it once, told whether
+// any of them needs it) gives the index over the blocks, then the rounds in the
+// blocks found. Without, each goes to its end (131,073 requests 11.1 us, 12.1
+// together: the tables' loads take fewer registers and more wavefronts cover
+// them).
+template <bool kTogether, typename Make>
 __device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t threshold, const uint64_t* key2,
                                             const int32_t* lcp, const ClElem* el, const int32_t* ib1, int64_t stride,
                                             const Make& make, int32_t* cid, int32_t* csz, const ClpmArgs& cl) {
@@ -1828,39 +1849,50 @@ __device__ __forceinline__ void final_query(int32_t i, int32_t n, int32_t thresh
   }
   const bool sect = cl.on && valid && cut > 0;
   OpenPair a{}, b{}, c{};
-  if (cl.on) {
-    a = open_pair(ib1, stride, n, ic, max(s, 1), ic + 1, max(s, 1));
-    b = open_pair(ib1, stride, n, max(ic - 1, 0), max(D, 0) + 1, ic + 1, max(D, 1));
-    c.L = last_below(ib1, stride, ic & ~63, ic, max(cut, 1));
-    c.sL = max(cut, 1);
-    c.pl = (ic >> 6) - 1;
-    c.needL = sect && c.L < (ic & ~63);
-  } else if (shared) {
-    a = open_pair(ib1, stride, n, ic, s, ic + 1, s);
-  }
-  a.needL &= shared;
-  a.needR &= shared;
-  b.needL &= node;
-  b.needR &= node;
-  // a range that leaves no block needs no index
-  const auto ix = make(__syncthreads_or(a.needL | a.needR | b.needL | b.needR | c.needL) != 0);
-  if (a.needL | a.needR) locate_pair(a, ix.blocks);
-  if (b.needL | b.needR) locate_pair(b, ix.blocks);
-  if (c.needL) locate_pair(c, ix.blocks);
-  if (__ballot(a.needL | a.needR | b.needL | b.needR | c.needL) != 0) {
-    // sides that stay at home search block 0
-    if (!a.needL) a.pl = 0;
-    if (!a.needR) a.pr = 0;
-    close_pair(a, ib1, stride, n);
-    if (cl.on) {
-      if (!b.needL) b.pl = 0;
-      if (!b.needR) b.pr = 0;
-      if (!c.needL) c.pl = 0;
-      close_pair(b, ib1, stride, n);
-      const int32_t l2 = last_below(ib1, stride, c.pl << 6, min((c.pl << 6) + 63, n), c.sL);
-      if (c.needL) c.L = l2;
+  const auto ix = [&] {
+    if constexpr (!kTogether) {
+      const auto ix = make(false);
+      if (shared) ix.pair_from(ic, s, ic + 1, s, a.L, a.R);
+      if (node) ix.pair_from(ic - 1, D + 1, ic + 1, D, b.L, b.R);
+      if (sect) c.L = ix.last_below_from(ic, cut);
+      return ix;
+    } else {
+      if (cl.on) {
+        a = open_pair(ib1, stride, n, ic, max(s, 1), ic + 1, max(s, 1));
+        b = open_pair(ib1, stride, n, max(ic - 1, 0), max(D, 0) + 1, ic + 1, max(D, 1));
+        c.L = last_below(ib1, stride, ic & ~63, ic, max(cut, 1));
+        c.sL = max(cut, 1);
+        c.pl = (ic >> 6) - 1;
+        c.needL = sect && c.L < (ic & ~63);
+      } else if (shared) {
+        a = open_pair(ib1, stride, n, ic, s, ic + 1, s);
+      }
+      a.needL &= shared;
+      a.needR &= shared;
+      b.needL &= node;
+      b.needR &= node;
+      // a range that leaves no block needs no index
+      const auto ix = make(__syncthreads_or(a.needL | a.needR | b.needL | b.needR | c.needL) != 0);
+      if (a.needL | a.needR) locate_pair(a, ix.blocks);
+      if (b.needL | b.needR) locate_pair(b, ix.blocks);
+      if (c.needL) locate_pair(c, ix.blocks);
+      if (__ballot(a.needL | a.needR | b.needL | b.needR | c.needL) != 0) {
+        // sides that stay at home search block 0
+        if (!a.needL) a.pl = 0;
+        if (!a.needR) a.pr = 0;
+        close_pair(a, ib1, stride, n);
+        if (cl.on) {
+          if (!b.needL) b.pl = 0;
+          if (!b.needR) b.pr = 0;
+          if (!c.needL) c.pl = 0;
+          close_pair(b, ib1, stride, n);
+          const int32_t l2 = last_below(ib1, stride, c.pl << 6, min((c.pl << 6) + 63, n), c.sL);
+          if (c.needL) c.L = l2;
+        }
+      }
+      return ix;
     }
-  }
+  }();
   if (valid && !shared) {
     cid[req] = -1;
     csz[req] = 1;
@@ -1930,10 +1962,10 @@ __global__ __launch_bounds__(kIndexThreads) void k_final_query(int32_t n, int32_
     __shared__ BlockLds S;
     BlockLoads loads;
     loads.fetch(ix.st1, ix.st2, ix.nb1, ix.nb2);
-    final_query(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool any) { return ix.lds(S, loads, any); }, cid,
+    final_query<true>(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool any) { return ix.lds(S, loads, any); }, cid,
                 csz, cl);
   } else {
-    final_query(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool) { return ix.tables(); }, cid, csz, cl);
+    final_query<false>(i, n, threshold, key2, lcp, el, ix.ib1, ix.stride, [&](bool) { return ix.tables(); }, cid, csz, cl);
   }
 }
 
@@ -2163,7 +2195,6 @@ struct SmallLds {
   int64_t wsum[kSmallThreads / kWave];
   int32_t flags[kFlags];
   int32_t sharing, ticket;
-  TailLds<kSmallRange, kSmallQueue> tail;
 };
 
 struct U64Less {
@@ -2239,7 +2270,7 @@ __device__ __forceinline__ void small_final(const SmallArgs& A, SmallLds& S) {
     __syncthreads();
   }
   const LcpIndex<TableBlocks> ix{S.ib1, S.ib2, stride, n, TableBlocks{S.st1, S.st2, nb1, nb2, levels}};
-  final_query(t, n, A.threshold, S.key2, S.lcp, S.el, S.ib1, stride, [&](bool) { return ix; }, A.cid, A.csz, cl);
+  final_query<true>(t, n, A.threshold, S.key2, S.lcp, S.el, S.ib1, stride, [&](bool) { return ix; }, A.cid, A.csz, cl);
   if (!cl.on) return;
   __syncthreads();
   // cLPM's score and section (as k_clpm_whole)
@@ -2339,6 +2370,7 @@ __device__ __forceinline__ void small_failed(const SmallArgs& A) {
 
 __global__ __launch_bounds__(kSmallThreads) void k_small_refine(SmallArgs A, int32_t* flags) {
   __shared__ SmallLds S;
+  PEEK_TAIL_LDS(tail, kSmallRange, kSmallQueue);
   if (A.tail.flags[0] == 0) return;
   const int t = threadIdx.x, lane = t & (kWave - 1), wave = t / kWave;
   const TailArgs& T = A.tail;
@@ -2389,7 +2421,7 @@ __global__ __launch_bounds__(kSmallThreads) void k_small_refine(SmallArgs A, int
     }
     late = __syncthreads_or(late) != 0;
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-    if (!late) refine_tail(T, (ticket - compares) * kSmallRange, S.tail);
+    if (!late) refine_tail(T, (ticket - compares) * kSmallRange, tail);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
     __syncthreads();
     if (t == 0) S.ticket = atomicAdd(&flags[kFlagSettled], 1);
@@ -2913,8 +2945,10 @@ peek_status run_signals(const peek_cache* c, int32_t n, const int32_t* tokens, c
                      cl.on ? cl.sharing : nullptr, keyed, n_keyed);
   if (n <= kInsFewMax)
     hipLaunchKernelGGL(k_first_insert<kInsFew>, dim3(blocks_for(n, kInsFew)), dim3(kInsFew), 0, st, ain, T, n);
-  else
+  else if (n <= kInsManyMax)
     hipLaunchKernelGGL(k_first_insert<kInsMany>, dim3(blocks_for(n, kInsMany)), dim3(kInsMany), 0, st, ain, T, n);
+  else
+    hipLaunchKernelGGL(k_first_insert<kInsMost>, dim3(blocks_for(n, kInsMost)), dim3(kInsMost), 0, st, ain, T, n);
   AncElem* anc_a = (AncElem*)(w + L.anc_a);
   AncElem* anc_b = (AncElem*)(w + L.anc_b);
   hipLaunchKernelGGL(k_first_compare, dim3(blocks_for(n, 4)), dim3(256), 0, st, ain, T, n, anc_a);

@@ -56,6 +56,18 @@ def test_sorts_at_every_form(n, samples_last):
         check_offline(hp, w, depth)
 
 
+@pytest.mark.parametrize("n", [66559, 66560, 131071, 131072, 131073])
+def test_lines_of_long_queues(n):
+    """Block minima kept in LDS up to 66559 requests, in tables beyond; buckets and 512
+    requests to a workgroup of the insert up to 131072, merges and 1024 beyond."""
+    w = short_queue(n, 4)
+    w.tau, w.theta = 2, 3
+    hp, outs = gpu_run(w)
+    assert_parity(w, outs[0], O.run(w))
+    for depth in (1, 3):
+        check_offline(hp, w, depth)
+
+
 def star_queue(n):
     """n prompts of one token each, children of one offline node in an order in which the
     sampled ones of its 2n pieces (the first n are the requests in order) come last."""
