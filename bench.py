@@ -218,14 +218,14 @@ def _cpu_model():
 
 
 def signals_algorithmic_bytes(lengths, share, m, n_nodes, passes):
-    """The signals pass's bytes as the survey's byte accounting counts them:
-    every prompt up to and including the token after its share (what a
-    plain pending-tree build reads), 16 bytes per request per sort pass, 4
-    of outputs, 16 per cache node (demand). Also the part of the prompt
-    bytes the walk had already proven (up to the match length), which the
-    pass here does not read again."""
-    prompt = 4 * int(np.minimum(lengths, share + 1).sum())
+    """The signals pass's bytes: every prompt from where the walk left it (its
+    match length) up to and including the token after its share, 16 bytes per
+    request per sort pass, 4 of outputs, 16 per cache node (demand). The
+    prompt bytes before that, which a plain pending-tree build would read and
+    the pass here does not, are told beside them and not counted."""
+    plain = 4 * int(np.minimum(lengths, share + 1).sum())
     proven = 4 * int(np.minimum(np.minimum(lengths, share + 1), m).sum())
+    prompt = plain - proven
     n = len(lengths)
     parts = {"prompt_bytes": prompt, "sort_bytes": 16 * n * passes, "io_bytes": 4 * n,
              "node_bytes": 16 * n_nodes, "prompt_bytes_proven_by_the_walk": proven}

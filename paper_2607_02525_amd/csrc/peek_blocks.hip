@@ -138,7 +138,8 @@ constexpr int kDppLast15 = 0x142, kDppLast31 = 0x143;         // the last lane o
 // lanes are part of a VALU instruction, where a shuffle is a round trip
 // through LDS, and the butterfly and the scan below chain six of them for each
 // step: 1000 document requests (10 steps of 512 tokens each) 17.6 -> 13.2 us.
-// The 65,536-request queue, 279 -> 269 us, is bound by its token reads.
+// The 65,536-request queue took 279 -> 269 us; reading its tokens alone takes
+// 165, so the instructions of a step bound it as much as the reads.
 template <int LPB>
 __device__ __forceinline__ void sum_over_block(uint64_t& v) {
   if constexpr (LPB > 1) v += dpp64<kDppSwap1>(v);

@@ -1564,8 +1564,13 @@ struct TableBlocks {
 // 4096 requests 12.3 -> 8.9 us, 65,536 16.0 -> 10.5, cLPM 8192 20.7 -> 12.4,
 // 20,000 21.3 -> 13.9; offline pieces of 5000 requests 14.3 -> 10.8 (1.5 to 4
 // us of it from reading a group with four 16-byte loads).
-// Beyond kLdsBlocks blocks every workgroup would load too much, and the
-// tables are built once.
+// Beyond kLdsBlocks blocks the tables are built once. The line is not where the
+// tables become faster: room for 2080 blocks gives queues of 66,560 to 133,000
+// requests 6 to 12 us (66,560: 138 -> 132), but every workgroup of a shorter
+// queue then fetches and stores twice the words (600 requests 36.4 -> 37.2 us,
+// 3000 49.0 -> 49.2, 32,768 79.7 -> 80.4). Room for 4160 costs 0.5 us there and
+// is the slower way itself above 200,000 requests (385 us with tables, 388; their
+// offline order 585 and 598).
 constexpr int kLdsBlocks = 1040;
 constexpr int kBlockGroup = 16;
 constexpr int kLdsGroups = kLdsBlocks / kBlockGroup;   // 65
@@ -2076,8 +2081,9 @@ __global__ __launch_bounds__(kScanThreads) void k_clpm_score(int32_t n, const ui
 }
 
 // ---------------------------------------------------------------- small queues
-// A queue of up to kSmallQueue requests takes three launches instead of
-// eleven, each of which would cost 2 to 4 us however little it does:
+// A queue of up to kSmallQueue requests takes three launches instead of the
+// nine of the general path (ten with cLPM's outputs), each of which would cost 2
+// to 4 us however little it does:
 //  - k_small_compare: the compare with the anchor group's head, every
 //    workgroup finding the groups by looking at all keys;
 //  - k_small_signals: one workgroup sorts and forms the segments in LDS and,

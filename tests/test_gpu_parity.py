@@ -593,11 +593,11 @@ def _big_tree(nn: int, seed: int):
 @pytest.mark.parametrize("nn", [70000, 1 << 19, 600001])
 @pytest.mark.parametrize("kind", ["zero", "huge", "signed", "ties"])
 def test_evict_rank_any_demand(kind, nn):
-    """Eviction ranking from demand vectors no queue produces: all zero (only
-    the id digits of the sort key vary), up to 2^31 - 1 (scores beyond 2^40),
-    negative entries, and a handful of distinct values (many equal keys), on
-    trees below and at or above the size where the victim order switches from
-    the merge sort to the radix sort (2^19 nodes)."""
+    """Eviction ranking from demand vectors no queue produces: all zero (one
+    segment of equal scores), up to 2^31 - 1 (scores beyond 2^40), negative
+    entries, and a handful of distinct values (many equal keys), on trees
+    whose segments are found in small tiles (up to 131072 leaves) and in
+    large ones."""
     import paper_2607_02525_amd as P
     HotPath = _hot()
     parent, eoff, etok = _big_tree(nn, 5)
@@ -647,9 +647,10 @@ def _shape_tree(shape: str, nn: int):
 @pytest.mark.parametrize("shape,nn", [("chain", 2), ("chain", 3), ("star", 2048), ("star", 2049), ("chain", 4097),
                                       ("comb", 6001)])
 def test_evict_rank_tree_shapes(shape, nn):
-    """Eviction ranking on degenerate trees at the sort's tile edges (2048
-    nodes per tile): one edge, a chain (every node in one group), a star
-    (every node a leaf) and a comb, with random and all-zero demand."""
+    """Eviction ranking on degenerate trees, ranked by one workgroup (up to
+    4096 nodes, two of them per thread up to 2048) and by the general path:
+    one edge, a chain (every node in one group), a star (every node a leaf)
+    and a comb, with random and all-zero demand."""
     import paper_2607_02525_amd as P
     HotPath = _hot()
     parent, eoff, etok = _shape_tree(shape, nn)
@@ -673,8 +674,9 @@ def test_evict_rank_tree_shapes(shape, nn):
 def test_evict_rank_segment_counts(leaves, run):
     """A star whose leaves take two demands in alternating runs, so the
     leaves' scores form exactly ceil(leaves / run) runs of equal score in
-    leaf order: 4096 (the most one workgroup sorts), 4097 (two tiles), one,
-    and 12289 (four tiles)."""
+    leaf order: 4096, 4097 and one, which are counted, and 12289, which are
+    sorted (in seven tiles). The line between the two, and the lines of the
+    tiles, are in test_gpu_evict_segments.py."""
     import paper_2607_02525_amd as P
     HotPath = _hot()
     nn = leaves + 1
