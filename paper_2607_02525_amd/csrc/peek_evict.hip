@@ -487,10 +487,11 @@ constexpr int kPThreads = 512;
 constexpr int kPWaves = kPThreads / kWave;
 // Segments per thread of a radix tile: few, so that more CUs take part, until
 // the tiles are so many that waiting for the counts of the earlier ones is the
-// longest part (ranking 65,536 distinct scores: 83 us with 2 per thread, 80 with
-// 4, 87 with 8; 131,072: 109, 95, 101).
+// longest part (250,000 distinct scores: 101 us with 4 per thread, 109 with 8;
+// 400,000: 125 and 122, 520,000: 143 and 133; with 2, 131,072 took 15% longer
+// than with 4).
 constexpr int kFewItems = 4, kManyItems = 8;
-constexpr int32_t kFewSegs = 131072;   // segments
+constexpr int32_t kFewSegs = 262144;   // segments
 static_assert(kPThreads == 2 * kRadix, "two threads per digit");
 // Prefix over tiles in two levels: tiles publish their own totals, the last
 // tile of each group of kGrp tiles also publishes the group's total, and a
@@ -835,7 +836,7 @@ struct PassLds {
   int32_t seg[kPThreads * I];
 };
 // Segments that are counted rather than sorted: 8192 distinct scores are ranked
-// in 41 us so, 16,384 sorted in 66. Counting 8192 is 22 us of it (96 with a
+// in 41 us so, 16,384 sorted in 64. Counting 8192 is 22 us of it (96 with a
 // workgroup on every fourth CU only, whose wavefronts went over all of them four
 // times as often).
 constexpr int kRankSegs = 8192;
@@ -924,7 +925,7 @@ __device__ __forceinline__ void store_through(T* p, T v) {
 // (`first`) a segment's index is its place. The tile's segments are ordered by
 // digit in LDS and go out in runs, written through to memory, where every XCD
 // sees them (with plain stores and an L2 write-back by every tile, a million
-// distinct scores took 284 us, not 238).
+// distinct scores took 46 us longer).
 template <int I>
 __device__ void radix_tile(const SortArgs& A, const SegList& src, const SegList& dst, bool first, int p, int32_t tile,
                            int32_t tiles, int32_t L, PassLds<I>& sh) {
@@ -1109,8 +1110,11 @@ __device__ __forceinline__ void sort_segments(const SortArgs& A, int32_t L, Pass
           __builtin_amdgcn_s_sleep(2);
         }
       }
+      // one wavefront's fence serves the workgroup (they share the L1): each
+      // one invalidates the XCD's L2, and with all eight a million distinct
+      // scores took 238 us, not 190
+      if (t == 0) __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
       __syncthreads();
-      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
     }
     const SegList &src = (k & 1) ? A.b : A.a, &dst = (k & 1) ? A.a : A.b;
     if (k == passes) {
@@ -1132,12 +1136,12 @@ __device__ __forceinline__ void sort_segments(const SortArgs& A, int32_t L, Pass
 // The start of every segment in the victim order. Whether the segments are
 // few is known on the device only, so one launch holds both ways. With a
 // launch for each byte of E and one for the prefix, 400,000 distinct scores
-// took 118 us and a million 167, here 142 and 238; but every one of those
+// took 118 us and a million 167, here 122 and 190; but every one of those
 // launches costs every call 1.5 us (few segments on a million nodes: 65 us
 // instead of 58), and a queue of n requests makes hardly more than 2n segments,
-// so that such numbers do not come from a queue of up to 65,536: there the one
-// launch is the faster one (65,536 distinct scores 80 us against 86, with three
-// distinct scores 41 against 57).
+// so that such numbers do not come from a queue of up to 131,072: there the one
+// launch is the faster one (65,536 distinct scores 75 us against 86, 250,000 101
+// against 105, 65,536 segments of three scores 40 against 57).
 __global__ __launch_bounds__(kPThreads) void k_ev_sort(SortArgs A) {
   __shared__ SortLds sh;
   const int32_t L = *A.z.nseg;

@@ -1,5 +1,5 @@
 """Eviction ranking by how many runs of equal score (segments) the leaves form in leaf
-order: up to 8192 are counted, more are sorted, in small tiles up to 131072 and in large
+order: up to 8192 are counted, more are sorted, in small tiles up to 262144 and in large
 ones beyond; up to 131072 leaves they are found in small tiles. Sizes on both sides of
 each line, against the oracle (whole numbers: exactly equal), and what many segments may
 cost."""
@@ -52,8 +52,8 @@ def demand_of(leaves, segments, kind):
 
 @pytest.mark.parametrize("leaves,segments", [
     (16384, 8191), (16384, 8192), (16384, 8193), (16384, 10240), (16384, 10241), (16384, 16384),
-    (131072, 1), (131072, 8192), (131072, 131072), (131073, 1), (131073, 8193), (131073, 131072), (131073, 131073),
-    (300000, 131072), (300000, 131073), (300000, 300000)])
+    (131072, 1), (131072, 8192), (131072, 131072), (131073, 1), (131073, 8193), (131073, 131073),
+    (262144, 262144), (262145, 262145), (300000, 8193), (300000, 262144), (300000, 262145), (300000, 300000)])
 def test_segment_counts(leaves, segments):
     desc, rank = ranking(leaves)
     tree = O.Tree.from_description(*desc)
@@ -71,7 +71,7 @@ def test_segment_counts(leaves, segments):
 
 
 def test_as_many_segments_as_are_counted_stay_cheap():
-    """8192 distinct scores take about twice as long as one (41 us against 21); on a few
+    """8192 distinct scores take about twice as long as one (41 us against 22); on a few
     CUs only, counting them took more than five times as long."""
     desc, rank = ranking(8192)
     us = {}
