@@ -31,11 +31,10 @@
 //     up to 1024 superblocks, one launch per level beyond the eleventh for
 //     more).
 //  3. k_ev_keys: K of every node, whether the node tops its run (its
-//     parent's K differs), and from each top the sort element of its leaf
-//     (E, leaf, run length), with the byte histograms of E and the OR and
-//     AND of all keys.
+//     parent's K differs), and from each top its leaf's E and run length.
 //  4. k_ev_segs: the segments (consecutive leaves of equal E), which is all
-//     that is left to sort.
+//     that is left to sort, with the byte histograms of E and the OR of E and
+//     of its complement.
 //  5. k_ev_sort: where each segment starts in the victim order. Up to 8192
 //     segments every one is counted against all; more go through stable
 //     least-significant-digit radix passes over tiles, a byte on which all keys
@@ -341,7 +340,7 @@ __global__ void k_ev_top_level(EKey* __restrict__ top, int32_t n, int k) {
   if (s + 2 * h <= n) top[(int64_t)k * n + s] = ekey_max(top[(int64_t)(k - 1) * n + s], top[(int64_t)(k - 1) * n + s + h]);
 }
 
-// ---- 3. K, run tops, sort elements and histograms ----
+// ---- 3. K and run tops ----
 
 struct RangeTabs {
   const void* pre;   // in-block maxima (see load_inblock)
